@@ -401,9 +401,10 @@ typedef struct {
  * Mean next-byte cross-entropy (nats) of B device sequences d_tokens[b*T + t]
  * (uint8, T >= 2; position t predicts t+1) and its gradient with respect to
  * the float32 master weights, in the flat weight layout (d_grad: device
- * float32, boa_param_count entries).  The selective scan keeps its state only
- * every chunk_t steps and recomputes it in the backward pass (Appendix A:
- * the scan evaluated over the sequence during training).  dtype selects the
+ * float32, boa_param_count entries).  The selective scan keeps its state every
+ * 8 steps and recomputes it in between in the backward pass (Appendix A: the
+ * scan evaluated over the sequence during training); chunk_t (0 = 256) does
+ * not change the result.  dtype selects the
  * projections' operands: BOA_DTYPE_F32, or BOA_DTYPE_BF16 (activations,
  * gradients and weights rounded to bf16 as they enter the matrix cores, FP32
  * accumulation); everything else is FP32.  Every reduction has a fixed order
