@@ -9,13 +9,15 @@
 // backward recomputes h in between and runs the reverse
 // recurrence  gh_t = C_t gy_t + exp(Delta_{t+1} A) gh_{t+1}.
 //
-// Every projection and its input and weight gradients run on this file's
-// MFMA GEMM (k_tg): FP32 operands on v_mfma_f32_16x16x4_f32, or BF16
-// operands (activations, gradients and the weights rounded to bf16 as they
-// are staged) on v_mfma_f32_16x16x32_bf16, both accumulating in FP32; the
-// master weights, the optimiser and every elementwise step stay FP32.
+// Every projection and its input gradient run on k_trow, the weight gradients
+// on k_tg_w (k_tg stays for feed-forward widths that k_trow is not built
+// for): FP32 operands on v_mfma_f32_16x16x4_f32, or BF16 operands
+// (activations, gradients and the weights rounded to bf16 as they are staged)
+// on v_mfma_f32_16x16x32_bf16, both accumulating in FP32; the master weights,
+// the optimiser and every elementwise step stay FP32.
 //
-// Training is deterministic: no reduction uses atomics.  Sums over rows
+// Training is deterministic: no sum depends on the order in which workgroups
+// or waves run.  Sums over rows
 // (weight gradients, bias and LayerNorm gradients, the embedding gradient,
 // the conv weights) are taken per fixed slice of rows into a partial buffer
 // and the slices are then added in increasing order; sums over channel blocks
@@ -170,6 +172,320 @@ __global__ __launch_bounds__(256) void k_tg(const float* __restrict__ A, long lo
             }
 }
 
+// ============================================================ row GEMM on prepared weights
+// C = epi(A . W^T) for many rows of A [M][lda] and a weight matrix prepared in
+// MFMA fragment order by k_tr_frags (rows padded to 64, columns to KP, both
+// with zeros): a workgroup of 4 waves stages BM rows of A in LDS once, rounded
+// to the operand type, and wave w computes the column fragments of its groups
+// of FN, reading them straight into registers with one step of prefetch.  Per
+// output the MFMA sequence is k_tg's (k increasing in steps of 4 / 32 from
+// zero).  Bound by HBM: A is read once and C written once (k_tg's 64 x 64
+// tiles of scalar loads took 1.47 ms per product of 262112 rows on average at
+// d_model 256, this one 0.37 ms, from 0.15 for the x_proj to 0.70 with the
+// gate's backward).  BM is 64 (32 for KP >= 512, the LDS of two workgroups
+// per CU), or 16 when fewer than 256 workgroups would run.
+// Epilogues: 0 store; 1 C = Cin + v (Cin may be C); 2 v += bias, C = v,
+// C2 = softplus(v); 3 the gate's backward: v = d gate, C = v silu(z),
+// C2 = v y silu'(z).
+struct TRow {
+    const float* A;
+    long long lda;
+    int M, K, N;
+    const void* W;
+    float* C;
+    long long ldc;
+    int epi;
+    const float* Cin;                 // 1: [M][ldc]
+    int span;                         // > 0: the reduction is taken in spans of `span` MFMA steps, added in order
+    const float* bias;                // 2: [N]
+    float* C2;                        // 2: [M][ldc]; 3: [M][ldc2]
+    const float* y;                   // 3: [M][ldc]
+    const float* z;                   // 3: [M][ldc2]
+    long long ldc2;
+};
+DEVI float dsilu_f(float v) {
+    float s = 1.0f / (1.0f + expf(-v));
+    return s * (1.0f + v * (1.0f - s));
+}
+
+template <int DT, int EPI, int KP, int BM, int FN>
+__global__ __launch_bounds__(256, 2) void k_trow(TRow p) {
+    constexpr int FM = BM / 16;
+    constexpr bool SPLIT = DT == 1 && BM == 16;                // spans occur with few rows only
+    constexpr int AS = DT == 0 ? KP + 4 : KP + 8;              // LDS row stride (elements)
+    using ET = typename std::conditional<DT == 0, float, uint16_t>::type;
+    extern __shared__ __align__(16) unsigned char smem[];
+    ET* As = reinterpret_cast<ET*>(smem);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = blockIdx.x * BM;
+#pragma unroll 8
+    for (int it = tid; it < BM * KP / 4; it += 256) {
+        const int r = it / (KP / 4), k = it % (KP / 4) * 4;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (m0 + r < p.M && k < p.K) v = *reinterpret_cast<const float4*>(p.A + (m0 + r) * p.lda + k);
+        if constexpr (DT == 0) {
+            *reinterpret_cast<float4*>(As + r * AS + k) = v;
+        } else {
+            uint2 u;
+            u.x = (uint32_t)f2bf_bits(v.x) | ((uint32_t)f2bf_bits(v.y) << 16);
+            u.y = (uint32_t)f2bf_bits(v.z) | ((uint32_t)f2bf_bits(v.w) << 16);
+            *reinterpret_cast<uint2*>(As + r * AS + k) = u;
+        }
+    }
+    __syncthreads();
+    const int li = lane & 15, lk = lane >> 4;
+    const int NF = (p.N + 63) / 64 * 4;
+    for (int nf0 = wv * FN; nf0 < NF; nf0 += 4 * FN) {
+        v4f acc[FM][FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        v4f tot[SPLIT ? FM : 1][SPLIT ? FN : 1];
+        int left = p.span;
+        constexpr int S = DT == 0 ? KP / 16 : KP / 32;          // 16-byte loads per fragment and lane
+        const uint4* W4 = reinterpret_cast<const uint4*>(p.W) + (long long)nf0 * S * 64 + lane;
+        uint4 bc[FN], bn[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) bc[j] = W4[(long long)j * S * 64];
+#pragma unroll 1
+        for (int s = 0; s < S; ++s) {
+            if (s + 1 < S) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) bn[j] = W4[((long long)j * S + s + 1) * 64];
+            }
+            if constexpr (DT == 0) {
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    float af[FM];
+#pragma unroll
+                    for (int i = 0; i < FM; ++i) af[i] = As[(i * 16 + li) * AS + 16 * s + 4 * jj + lk];
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        const float b = __uint_as_float(jj == 0 ? bc[j].x : jj == 1 ? bc[j].y : jj == 2 ? bc[j].z : bc[j].w);
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], b, acc[i][j], 0, 0, 0);
+                    }
+                }
+            } else {
+                v8bf af[FM];
+#pragma unroll
+                for (int i = 0; i < FM; ++i) af[i] = *reinterpret_cast<const v8bf*>(As + (i * 16 + li) * AS + 32 * s + 8 * lk);
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], *reinterpret_cast<const v8bf*>(&bc[j]),
+                                                                            acc[i][j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) bc[j] = bn[j];
+            if (SPLIT && p.span > 0 && --left == 0 && s + 1 < S) {
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        v4f& t = tot[SPLIT ? i : 0][SPLIT ? j : 0];
+                        t = s + 1 == p.span ? acc[i][j] : t + acc[i][j];
+                        acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+                    }
+                left = p.span;
+            }
+        }
+        if (SPLIT && p.span > 0 && p.span < S) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = tot[SPLIT ? i : 0][SPLIT ? j : 0] + acc[i][j];
+        }
+        // the epilogue's operands of 16 rows at a time go out together (the stores
+        // may alias them as far as the compiler knows, so it would not move the
+        // loads of one output above the store of another)
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            float e1[EPI == 1 || EPI == 3 ? FN : 1][4], e2[EPI == 3 ? FN : 1][4];
+            if constexpr (EPI == 1 || EPI == 3) {
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int n = (nf0 + j) * 16 + li;
+                        const long long m = m0 + i * 16 + 4 * lk + rr;
+                        const bool in = n < p.N && m < p.M;
+                        e1[j][rr] = in ? (EPI == 1 ? p.Cin : p.y)[m * p.ldc + n] : 0.0f;
+                        if constexpr (EPI == 3) e2[j][rr] = in ? p.z[m * p.ldc2 + n] : 0.0f;
+                    }
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int n = (nf0 + j) * 16 + li;
+                if (n >= p.N) continue;
+                const float bias = EPI == 2 ? p.bias[n] : 0.0f;
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const long long m = m0 + i * 16 + 4 * lk + rr;
+                    if (m >= p.M) continue;
+                    const float v = acc[i][j][rr];
+                    float* dst = p.C + m * p.ldc + n;
+                    if constexpr (EPI == 0) {
+                        *dst = v;
+                    } else if constexpr (EPI == 1) {
+                        *dst = e1[j][rr] + v;
+                    } else if constexpr (EPI == 2) {
+                        const float u = v + bias;
+                        *dst = u;
+                        p.C2[m * p.ldc + n] = softplus_f(u);
+                    } else {
+                        *dst = v * silu_f(e2[j][rr]);
+                        p.C2[m * p.ldc2 + n] = v * e1[j][rr] * dsilu_f(e2[j][rr]);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Weight matrices of one layer (or the head) in fragment order for k_trow:
+// job j covers the matrix X [N][K], X(n, k) = src[n sn + k sk] (a weight or its
+// transpose), padded with zeros to NP x KP; bf16 or f32 like the launch.
+struct FragJob {
+    const float* src;
+    void* dst;
+    int sn, sk, N, K, NP, KP;
+};
+constexpr int FRAG_JOBS = 12;
+struct FragJobs {
+    FragJob j[FRAG_JOBS];
+};
+template <int DT>
+__global__ __launch_bounds__(256) void k_tr_frags(FragJobs jobs) {
+    const FragJob& q = jobs.j[blockIdx.y];
+    const long long n_all = (long long)q.NP * q.KP;
+    for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n_all; i += gridDim.x * 256LL) {
+        constexpr int J = DT == 0 ? 4 : 8;
+        const int j = (int)(i % J);
+        long long t = i / J;
+        const int lane = (int)(t & 63);
+        t >>= 6;
+        const int S = q.KP / (4 * J), s = (int)(t % S), nf = (int)(t / S);
+        const int n = 16 * nf + (lane & 15);
+        const int k = DT == 0 ? 16 * s + 4 * j + (lane >> 4) : 32 * s + 8 * (lane >> 4) + j;
+        const float v = n < q.N && k < q.K ? q.src[(long long)n * q.sn + (long long)k * q.sk] : 0.0f;
+        if (DT == 0) static_cast<float*>(q.dst)[i] = v;
+        else static_cast<uint16_t*>(q.dst)[i] = f2bf_bits(v);
+    }
+}
+
+// ============================================================ weight gradients
+// part[z][N][K] = sum over the rows of slice z of dY[r][n] X[r][k]: a workgroup
+// of 8 waves owns a TA x TB tile of the gradient and walks its slice 32 rows at
+// a time, the next 32 rows in flight in registers while the current ones are
+// multiplied.  Half of the threads load dY, half X: 8 rows x 4 columns each, so
+// that a thread holds 8 consecutive rows of a column, the operand order of the
+// bf16 MFMA, and no transpose is needed.  A 256 x 256 tile reads dY of the
+// in_proj gradient once and X four times; grid.x is the slice, so that the
+// tiles of a slice share an XCD's L2.  Bound by HBM (k_tg took 1.46 ms per
+// gradient over 262112 rows on average, this one 0.16 ms).
+template <int DT, int TA, int TB>
+__global__ __launch_bounds__(512) void k_tg_w(const float* __restrict__ dY, long long ldy, int N,
+                                              const float* __restrict__ X, long long ldx, int K, long long rows,
+                                              long long per, float* __restrict__ part) {
+    using ET = typename std::conditional<DT == 0, float, uint16_t>::type;
+    constexpr int RS = DT == 0 ? 36 : 40;                       // LDS row stride: 32 rows of the reduction + pad
+    constexpr int WA = TA == 256 ? (TB == 256 ? 4 : 8) : 1, WB = 8 / WA;
+    constexpr int FA = TA / WA / 16, FB = TB / WB / 16;
+    __shared__ __align__(16) ET As[TA * RS];
+    __shared__ __align__(16) ET Bs[TB * RS];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt = (K + TB - 1) / TB;
+    const int n0 = (blockIdx.y / nt) * TA, k0 = (blockIdx.y % nt) * TB;
+    const long long r0 = blockIdx.x * per, r1 = r0 + per < rows ? r0 + per : rows;
+    const bool isA = tid < 256;
+    const int cg = (tid & 63) * 4, rg = ((tid >> 6) & 3) * 8;   // 4 columns, 8 rows
+    const float* src = isA ? dY : X;
+    const long long ld = isA ? ldy : ldx;
+    const int c0 = (isA ? n0 : k0) + cg;
+    const bool cols = cg < (isA ? TA : TB) && c0 < (isA ? N : K);
+    float4 v[8];
+    auto load = [&](long long r) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (cols && r + rg + i < r1) v[i] = *reinterpret_cast<const float4*>(src + (r + rg + i) * ld + c0);
+        }
+    };
+    v4f acc[FA][FB];
+#pragma unroll
+    for (int i = 0; i < FA; ++i)
+#pragma unroll
+        for (int j = 0; j < FB; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int li = lane & 15, lk = lane >> 4;
+    const int ra = (wv / WB) * FA * 16, rb = (wv % WB) * FB * 16;
+    load(r0);
+    for (long long r = r0; r < r1; r += 32) {
+        if (cg < (isA ? TA : TB)) {
+            ET* S = (isA ? As : Bs) + cg * RS + rg;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i] = c == 0 ? v[i].x : c == 1 ? v[i].y : c == 2 ? v[i].z : v[i].w;
+                if constexpr (DT == 0) {
+                    *reinterpret_cast<float4*>(S + c * RS) = make_float4(w[0], w[1], w[2], w[3]);
+                    *reinterpret_cast<float4*>(S + c * RS + 4) = make_float4(w[4], w[5], w[6], w[7]);
+                } else {
+                    uint4 u;
+                    u.x = (uint32_t)f2bf_bits(w[0]) | ((uint32_t)f2bf_bits(w[1]) << 16);
+                    u.y = (uint32_t)f2bf_bits(w[2]) | ((uint32_t)f2bf_bits(w[3]) << 16);
+                    u.z = (uint32_t)f2bf_bits(w[4]) | ((uint32_t)f2bf_bits(w[5]) << 16);
+                    u.w = (uint32_t)f2bf_bits(w[6]) | ((uint32_t)f2bf_bits(w[7]) << 16);
+                    *reinterpret_cast<uint4*>(S + c * RS) = u;
+                }
+            }
+        }
+        __syncthreads();
+        if (r + 32 < r1) load(r + 32);
+        if constexpr (DT == 0) {
+#pragma unroll
+            for (int ks = 0; ks < 32; ks += 4) {
+                float af[FA], bf[FB];
+#pragma unroll
+                for (int i = 0; i < FA; ++i) af[i] = As[(ra + i * 16 + li) * RS + ks + lk];
+#pragma unroll
+                for (int j = 0; j < FB; ++j) bf[j] = Bs[(rb + j * 16 + li) * RS + ks + lk];
+#pragma unroll
+                for (int i = 0; i < FA; ++i)
+#pragma unroll
+                    for (int j = 0; j < FB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+            }
+        } else {
+            v8bf af[FA];
+#pragma unroll
+            for (int i = 0; i < FA; ++i) af[i] = *reinterpret_cast<const v8bf*>(As + (ra + i * 16 + li) * RS + 8 * lk);
+#pragma unroll
+            for (int j = 0; j < FB; ++j) {
+                const v8bf bf = *reinterpret_cast<const v8bf*>(Bs + (rb + j * 16 + li) * RS + 8 * lk);
+#pragma unroll
+                for (int i = 0; i < FA; ++i)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf, acc[i][j], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+    float* out = part + (long long)blockIdx.x * N * K;
+#pragma unroll
+    for (int i = 0; i < FA; ++i)
+#pragma unroll
+        for (int j = 0; j < FB; ++j)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const int n = n0 + ra + i * 16 + 4 * lk + rr, k = k0 + rb + j * 16 + li;
+                if (n < N && k < K) out[(long long)n * K + k] = acc[i][j][rr];
+            }
+}
+
 // ============================================================ fixed-order sums
 // out[i] (+)= part[i] + part[stride + i] + ... over S slices: a workgroup owns
 // 64 columns, wave q adds the slices of the q-th quarter in increasing order
@@ -206,15 +522,31 @@ __global__ void k_sum_slices_2d(const float* __restrict__ part, int S, int M, in
     *d = accumulate ? *d + v : v;
 }
 
-// part[s * N + n] = sum over the rows of slice s (increasing) of X[r ld + off + n]
-__global__ void k_colsum_part(const float* __restrict__ X, long long rows, int ld, int off, int N, long long per,
-                              float* __restrict__ part) {
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
+// part[s * N + n] = sum over the rows of slice s of X[r ld + n]: wave w of the
+// workgroup adds rows r0 + w, r0 + w + 4, ... in order, four columns per lane,
+// then the waves are added in order.  N and ld are multiples of 4.
+__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ X, long long rows, int ld, int N,
+                                                     long long per, float* __restrict__ part) {
+    __shared__ float4 w_s[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n = blockIdx.x * 256 + 4 * lane;
     const long long r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
-    float acc = 0.f;
-    for (long long r = r0; r < r1; ++r) acc += X[r * ld + off + n];
-    part[(long long)blockIdx.y * N + n] = acc;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n < N) {
+#pragma unroll 4
+        for (long long r = r0 + wv; r < r1; r += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(X + r * ld + n);
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
+    }
+    w_s[wv][lane] = a;
+    __syncthreads();
+    if (wv == 0 && n < N) {
+        for (int k = 1; k < 4; ++k) {
+            const float4 v = w_s[k][lane];
+            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        }
+        *reinterpret_cast<float4*>(part + (long long)blockIdx.y * N + n) = a;
+    }
 }
 
 // One workgroup: *out = sum of in[0 .. n) in double; thread t sums t, t + 256,
@@ -225,6 +557,7 @@ __global__ __launch_bounds__(256) void k_sum_all(const TI* __restrict__ in, long
     __shared__ double buf[256];
     const int t = threadIdx.x;
     double acc = 0.0;
+#pragma unroll 8
     for (long long i = t; i < n; i += 256) acc += (double)in[i];
     buf[t] = acc;
     __syncthreads();
@@ -251,7 +584,9 @@ __global__ void k_tr_embed(const uint8_t* __restrict__ tok, int B, int T, const 
 
 // Embedding gradient of one slice of rows and 64 columns: one wave adds the
 // rows of its slice in order into a [256][64] LDS table (lane = column, so
-// no two lanes touch one address); the table is the slice's partial
+// no two lanes touch one address; the adds are LDS instructions without a
+// return value, in the wave's order, so a row does not wait for the sum of the
+// one before); the table is the slice's partial
 // part[s][256][D].
 __global__ __launch_bounds__(64) void k_tr_embed_bwd_part(const uint8_t* __restrict__ tok, int B, int T,
                                                           const float* __restrict__ dr, int D, long long per,
@@ -278,113 +613,178 @@ __global__ __launch_bounds__(64) void k_tr_embed_bwd_part(const uint8_t* __restr
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (ys[j] >= 0) acc[ys[j]][lane] += v[j];
+            if (ys[j] >= 0) __hip_atomic_fetch_add(&acc[ys[j]][lane], v[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
     float* dst = part + (long long)blockIdx.y * VOCAB * D + c;
     for (int y = 0; y < VOCAB; ++y) dst[(long long)y * D] = acc[y][lane];
 }
 
-// LayerNorm forward, one wave per row; keeps (mean, rstd)
-__global__ void k_tr_ln_fwd(const float* __restrict__ x, long long rows, int D, const float* __restrict__ w,
-                            const float* __restrict__ b, float* __restrict__ out, float* __restrict__ st) {
-    long long row = blockIdx.x * 4LL + threadIdx.y;
+// LayerNorm forward, one wave per row (NV = D / 64 values per lane in
+// registers, ln_stats' operations); keeps (mean, rstd)
+template <int NV>
+__global__ __launch_bounds__(256) void k_tr_ln_fwd(const float* __restrict__ x, long long rows,
+                                                   const float* __restrict__ w, const float* __restrict__ b,
+                                                   float* __restrict__ out, float* __restrict__ st) {
+    constexpr int D = 64 * NV;
+    const long long row = blockIdx.x * 4LL + (threadIdx.x >> 6);
     if (row >= rows) return;
-    int lane = threadIdx.x;
-    const float* xr = x + row * D;
+    const int lane = threadIdx.x & 63;
+    float v[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = x[row * D + lane + 64 * j];
     float mu, rs;
-    ln_stats(xr, D, lane, mu, rs);
-    for (int k = lane; k < D; k += 64) out[row * D + k] = ln_apply(xr[k], mu, rs, w[k], b[k]);
+    ln_stats_v<NV>(v, D, mu, rs);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) out[row * D + lane + 64 * j] = ln_apply(v[j], mu, rs, w[lane + 64 * j], b[lane + 64 * j]);
     if (lane == 0) { st[2 * row] = mu; st[2 * row + 1] = rs; }
 }
 
-// LayerNorm backward: dx (+)= rstd (dxh - mean(dxh) - xh mean(dxh xh)), dxh = dy w;
-// tmp = dy * xh for the weight gradient (column sums taken separately)
-__global__ void k_tr_ln_bwd(const float* __restrict__ dy, const float* __restrict__ x, const float* __restrict__ st,
-                            long long rows, int D, const float* __restrict__ w, float* __restrict__ dx, int accumulate,
-                            float* __restrict__ tmp) {
-    long long row = blockIdx.x * 4LL + threadIdx.y;
-    if (row >= rows) return;
-    int lane = threadIdx.x;
-    const float mu = st[2 * row], rs = st[2 * row + 1];
-    float s1 = 0.f, s2 = 0.f;
-    for (int k = lane; k < D; k += 64) {
-        float xh = (x[row * D + k] - mu) * rs;
-        float g = dy[row * D + k];
-        float dxh = g * w[k];
-        s1 += dxh;
-        s2 += dxh * xh;
-        tmp[row * D + k] = g * xh;
-    }
-    s1 = wave_sum(s1) / (float)D;
-    s2 = wave_sum(s2) / (float)D;
-    for (int k = lane; k < D; k += 64) {
-        float xh = (x[row * D + k] - mu) * rs;
-        float v = rs * (dy[row * D + k] * w[k] - s1 - xh * s2);
-        if (accumulate) dx[row * D + k] += v; else dx[row * D + k] = v;
-    }
-}
-
-// causal depthwise conv + SiLU over each sequence (zero before t = 0)
-__global__ void k_tr_conv_fwd(const float* __restrict__ xz, long long rows, int Tn, int Di,
-                              const float* __restrict__ cw, const float* __restrict__ cb, float* __restrict__ xc,
-                              float* __restrict__ xs) {
-    long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i >= rows * Di) return;
-    long long row = i / Di;
-    int d = (int)(i % Di), t = (int)(row % Tn);
-    float acc = cb[d];
-    for (int k = 0; k < KCONV; ++k) {
-        int back = KCONV - 1 - k;
-        if (t - back >= 0) acc = fmaf(cw[d * KCONV + k], xz[(row - back) * 2 * Di + d], acc);
-    }
-    xc[i] = acc;
-    xs[i] = silu_f(acc);
-}
-
-DEVI float dsilu_f(float v) {
-    float s = 1.0f / (1.0f + expf(-v));
-    return s * (1.0f + v * (1.0f - s));
-}
-
-// dxc = dxs * silu'(xc); dx[t] = sum_k dxc[t + back_k] w[k] written into dxz[:, :Di]
-__global__ void k_tr_conv_bwd_x(const float* __restrict__ dxs, const float* __restrict__ xc, long long rows, int Tn,
-                                int Di, const float* __restrict__ cw, float* __restrict__ dxc,
-                                float* __restrict__ dxz) {
-    long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i >= rows * Di) return;
-    long long row = i / Di;
-    int d = (int)(i % Di), t = (int)(row % Tn);
-    // dxc of rows t..t+3 (same sequence) are needed: recompute them locally
-    float acc = 0.f;
-    for (int k = 0; k < KCONV; ++k) {
-        int fwd = KCONV - 1 - k;               // output row t + fwd used input t through weight k
-        if (t + fwd < Tn) {
-            long long j = (row + fwd) * Di + d;
-            acc += dxs[j] * dsilu_f(xc[j]) * cw[d * KCONV + k];
+// LayerNorm backward of one slice of rows: dx (+)= rstd (dxh - mean(dxh) -
+// xh mean(dxh xh)), dxh = dy w, one wave per row; and the slice's partial sums
+// of dy xh and dy (the weight and bias gradients), part[s][2][D]: wave w adds
+// its rows r0 + w, r0 + w + 4, ... in order in registers, then the waves are
+// added in order.  Bound by HBM: dy, x and dx pass once (a separate dy xh tensor
+// and two column sums took 1.06 ms per LayerNorm of 262112 x 256, against
+// 0.2 ms).
+template <int NV>
+__global__ __launch_bounds__(256) void k_tr_ln_bwd(const float* __restrict__ dy, const float* __restrict__ x,
+                                                   const float* __restrict__ st, long long rows, long long per,
+                                                   const float* __restrict__ w, float* __restrict__ dx, int accumulate,
+                                                   float* __restrict__ part) {
+    constexpr int D = 64 * NV;
+    __shared__ float p_s[4][2 * D];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const long long r0 = blockIdx.x * per, r1 = r0 + per < rows ? r0 + per : rows;
+    float wk[NV], gw[NV], gb[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) { wk[j] = w[lane + 64 * j]; gw[j] = 0.f; gb[j] = 0.f; }
+#pragma unroll 2
+    for (long long row = r0 + wv; row < r1; row += 4) {
+        const float mu = st[2 * row], rs = st[2 * row + 1];
+        float xh[NV], g[NV], old[NV], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const long long at = row * D + lane + 64 * j;
+            xh[j] = x[at];
+            g[j] = dy[at];
+            old[j] = accumulate ? dx[at] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            xh[j] = (xh[j] - mu) * rs;
+            const float dxh = g[j] * wk[j];
+            s1 += dxh;
+            s2 += dxh * xh[j];
+            gw[j] += g[j] * xh[j];
+            gb[j] += g[j];
+        }
+        s1 = wave_sum(s1) / (float)D;
+        s2 = wave_sum(s2) / (float)D;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const float v = rs * (g[j] * wk[j] - s1 - xh[j] * s2);
+            dx[row * D + lane + 64 * j] = accumulate ? old[j] + v : v;
         }
     }
-    dxc[i] = dxs[i] * dsilu_f(xc[i]);
-    dxz[row * 2 * Di + d] = acc;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) { p_s[wv][lane + 64 * j] = gw[j]; p_s[wv][D + lane + 64 * j] = gb[j]; }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * D; i += 256)
+        part[(long long)blockIdx.x * 2 * D + i] = ((p_s[0][i] + p_s[1][i]) + p_s[2][i]) + p_s[3][i];
 }
 
-// conv weight and bias gradients of one slice of rows, in row order:
-// part[s][d * K + k] = sum dxc[t] x[t - back_k], part[s][Di K + d] = sum dxc[t]
-__global__ void k_tr_conv_bwd_w_part(const float* __restrict__ dxc, const float* __restrict__ xz, long long rows,
-                                     int Tn, int Di, long long per, float* __restrict__ part) {
-    int d = blockIdx.x * 256 + threadIdx.x;
+// Causal depthwise conv + SiLU over each sequence (zero before t = 0): one
+// thread per channel walks CONV_TS rows with the window in registers, so that
+// each x is read once.  Bound by HBM (0.94 ms per 262112 x 512 with one thread
+// per element, 0.32 ms now).
+constexpr int CONV_TS = 64, CONV_RB = 8;      // rows per thread, rows loaded together
+DEVI float conv_at(const float (&cw)[KCONV], float cb, const float (&w)[KCONV]) {
+    float acc = cb;
+#pragma unroll
+    for (int k = 0; k < KCONV; ++k) acc = fmaf(cw[k], w[k], acc);
+    return acc;
+}
+__global__ __launch_bounds__(256) void k_tr_conv_fwd(const float* __restrict__ xz, int Tn, int Di,
+                                                     const float* __restrict__ cw, const float* __restrict__ cb,
+                                                     float* __restrict__ xs) {
+    const int d = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.z;
     if (d >= Di) return;
-    const long long r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
-    float aw[KCONV] = {0.f, 0.f, 0.f, 0.f}, ab = 0.f;
-    for (long long r = r0; r < r1; ++r) {
-        int t = (int)(r % Tn);
-        float g = dxc[r * Di + d];
-        ab += g;
-        for (int k = 0; k < KCONV; ++k) {
-            int back = KCONV - 1 - k;
-            if (t - back >= 0) aw[k] += g * xz[(r - back) * 2 * Di + d];
+    const int t0 = blockIdx.y * CONV_TS, t1 = t0 + CONV_TS < Tn ? t0 + CONV_TS : Tn;
+    const float* x = xz + (long long)b * Tn * 2 * Di + d;
+    float* o = xs + (long long)b * Tn * Di + d;
+    float c[KCONV], w[KCONV];
+#pragma unroll
+    for (int k = 0; k < KCONV; ++k) c[k] = cw[d * KCONV + k];
+    const float bias = cb[d];
+    w[0] = 0.f;
+#pragma unroll
+    for (int k = 1; k < KCONV; ++k) w[k] = t0 - KCONV + k >= 0 ? x[(long long)(t0 - KCONV + k) * 2 * Di] : 0.f;
+    for (int t = t0; t < t1; t += CONV_RB) {
+        float v[CONV_RB];
+#pragma unroll
+        for (int j = 0; j < CONV_RB; ++j) v[j] = t + j < t1 ? x[(long long)(t + j) * 2 * Di] : 0.f;
+#pragma unroll
+        for (int j = 0; j < CONV_RB; ++j) {
+            w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = v[j];
+            if (t + j < t1) o[(long long)(t + j) * Di] = silu_f(conv_at(c, bias, w));
         }
     }
-    float* dst = part + (long long)blockIdx.y * Di * (KCONV + 1);
+}
+
+// Conv backward of one slice of CONV_TS rows, one thread per channel.  With
+// p_t = dxs_t silu'(xc_t) (xc recomputed from the window): dx_t = sum over k of
+// p_{t + 3 - k} w_k, into dxz[:, :Di]; and the slice's partial weight and bias
+// gradients in row order, part[s][d K + k] = sum p_t x_{t - back_k},
+// part[s][Di K + d] = sum p_t.  Each input is read once, but for three rows
+// on either side (two kernels that kept xc and p in memory took 2.5 ms per
+// 262112 x 512, 0.43 ms now).
+__global__ __launch_bounds__(256) void k_tr_conv_bwd(const float* __restrict__ dxs, const float* __restrict__ xz, int Tn,
+                                                     int Di, const float* __restrict__ cw,
+                                                     const float* __restrict__ cb, float* __restrict__ dxz,
+                                                     float* __restrict__ part) {
+    const int d = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.z;
+    if (d >= Di) return;
+    const int t0 = blockIdx.y * CONV_TS, t1 = t0 + CONV_TS < Tn ? t0 + CONV_TS : Tn;
+    const float* x = xz + (long long)b * Tn * 2 * Di + d;
+    const float* g = dxs + (long long)b * Tn * Di + d;
+    float* o = dxz + (long long)b * Tn * 2 * Di + d;
+    float c[KCONV], w[KCONV], p[KCONV], aw[KCONV], ab = 0.f;
+#pragma unroll
+    for (int k = 0; k < KCONV; ++k) { c[k] = cw[d * KCONV + k]; aw[k] = 0.f; p[k] = 0.f; }
+    const float bias = cb[d];
+    w[0] = 0.f;
+#pragma unroll
+    for (int k = 1; k < KCONV; ++k) w[k] = t0 - KCONV + k >= 0 ? x[(long long)(t0 - KCONV + k) * 2 * Di] : 0.f;
+    // row u enters with its p; row u - 3 then has every p it needs
+    for (int u = t0; u < t1 + KCONV - 1; u += CONV_RB) {
+        float xv[CONV_RB], gv[CONV_RB];
+#pragma unroll
+        for (int j = 0; j < CONV_RB; ++j) {
+            const bool in = u + j < Tn && u + j < t1 + KCONV - 1;
+            xv[j] = in ? x[(long long)(u + j) * 2 * Di] : 0.f;
+            gv[j] = in ? g[(long long)(u + j) * Di] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < CONV_RB; ++j) {
+            w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = xv[j];
+            p[0] = p[1]; p[1] = p[2]; p[2] = p[3];
+            p[3] = gv[j] * dsilu_f(conv_at(c, bias, w));
+            if (u + j < t1) {                       // p[3] belongs to row u + j of this slice
+                ab += p[3];
+#pragma unroll
+                for (int k = 0; k < KCONV; ++k) aw[k] += p[3] * w[k];
+            }
+            const int t = u + j - (KCONV - 1);
+            if (t >= t0 && t < t1) {
+                float acc = 0.f;
+#pragma unroll
+                for (int k = 0; k < KCONV; ++k) acc += p[KCONV - 1 - k] * c[k];
+                o[(long long)t * 2 * Di] = acc;
+            }
+        }
+    }
+    float* dst = part + ((long long)b * gridDim.y + blockIdx.y) * Di * (KCONV + 1);
+#pragma unroll
     for (int k = 0; k < KCONV; ++k) dst[d * KCONV + k] = aw[k];
     dst[Di * KCONV + d] = ab;
 }
@@ -413,23 +813,6 @@ __global__ void k_tr_gelu_bwd(float* __restrict__ dgu, const float* __restrict__
     if (i < n) dgu[i] *= dgelu_tr(u[i]);
 }
 
-// dtr += bias; dt = softplus(dtr)
-__global__ void k_tr_bias_softplus(float* __restrict__ dtr, long long rows, int Di, const float* __restrict__ b,
-                                   float* __restrict__ dt) {
-    long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i >= rows * Di) return;
-    float v = dtr[i] + b[i % Di];
-    dtr[i] = v;
-    dt[i] = softplus_f(v);
-}
-__global__ void k_tr_softplus_bwd(const float* __restrict__ ddt, const float* __restrict__ dtr, long long n,
-                                  float* __restrict__ ddtr) {
-    long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i >= n) return;
-    float v = dtr[i];
-    ddtr[i] = v > 20.0f ? ddt[i] : ddt[i] / (1.0f + expf(-v));
-}
-
 // Selective scan, split over time.  The recurrence h_t = exp(dt_t A) h_{t-1} +
 // (dt_t x_t) B_t is one multiply and one add per state and step, while the
 // output, the gate and the gradients are most of the work and need h only at
@@ -443,8 +826,8 @@ __global__ void k_tr_softplus_bwd(const float* __restrict__ ddt, const float* __
 // operations in the same order.  One wave per (sequence, 64 channels) walking
 // the whole sequence left a training step of 32 x 8192 tokens at d_inner 512
 // with 256 waves, one per compute unit: 8.6 ms forward and 18.1 ms backward
-// per layer, against 1.4 ms (states 0.7, outputs 0.7) and 3.4 ms (adjoint states
-// 0.6, gradients 2.8) now.
+// per layer, against 1.5 ms (states 0.8, outputs 0.7) and 3.6 ms (adjoint states
+// 0.6, gradients 3.0 with the softplus) now.
 // exp(dt A) = exp2(dt (A log2 e)) on the hardware exp2.
 constexpr int SCAN_CH = 64;           // channels per wave (one per lane)
 constexpr int SCAN_SB = 64;           // rows staged in LDS at a time
@@ -726,19 +1109,6 @@ __global__ __launch_bounds__(256) void k_tr_scan_y(const float* __restrict__ xs,
     }
 }
 
-// gate backward: dy = dg silu(z); dz = dg y silu'(z) (into dxz[:, Di:])
-__global__ void k_tr_gate_bwd(const float* __restrict__ dg, const float* __restrict__ y, const float* __restrict__ xz,
-                              long long rows, int Di, float* __restrict__ dy, float* __restrict__ dxz) {
-    long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i >= rows * Di) return;
-    long long row = i / Di;
-    int d = (int)(i % Di);
-    float z = xz[row * 2 * Di + Di + d];
-    float gv = dg[i];
-    dy[i] = gv * silu_f(z);
-    dxz[row * 2 * Di + Di + d] = gv * y[i] * dsilu_f(z);
-}
-
 // Sums of 32 values (16 dB, 16 dC) over the 64 lanes of a wave by a
 // transposing tree: at partner distance m = 32, 16, 8, 4, 2 every lane keeps
 // the half of its values selected by its own bit m and adds the partner's copy
@@ -791,14 +1161,15 @@ DEVI float wave_sum32_tail(float (&v)[NSTATE], int lane) {
 // recurrence runs, starting from gh at the block's end (ghb).  dB and dC (sums over channels) are reduced within
 // the wave and written as the channel block's partial pbc[block][row][32];
 // dA_log and dD (sums over time) are written per (sequence, block) slot as
-// pA[slot][d][n], pD[slot][d].  VALU bound: about 26 instructions per state
+// pA[slot][d][n], pD[slot][d].  With dtr, dt = softplus(dtr): ddt receives the
+// gradient of dtr, and pT[slot][d] its sum (the dt_proj bias).  VALU bound: about 26 instructions per state
 // and step.
 __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
     const float* __restrict__ xs, const float* __restrict__ dt, const float* __restrict__ dbc, int NO, int R,
     const float* __restrict__ A_log, const float* __restrict__ Dsk, const float* __restrict__ dy, long long rows, int Tn,
     int Di, int Tc, int NC, int TB, int nblk, const float* __restrict__ hsub, int nsub,
-    const float* __restrict__ ghb, float* __restrict__ dxs, float* __restrict__ ddt, float* __restrict__ pbc,
-    float* __restrict__ pA, float* __restrict__ pD) {
+    const float* __restrict__ ghb, const float* __restrict__ dtr, float* __restrict__ dxs, float* __restrict__ ddt,
+    float* __restrict__ pbc, float* __restrict__ pA, float* __restrict__ pD, float* __restrict__ pT) {
     __shared__ float4 A_s[NSTATE / 4][256];                  // -exp(A_log), read once per step
     extern __shared__ __align__(16) float bc_s[];            // [TB][32]
     const int b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
@@ -822,7 +1193,7 @@ __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
         gA[n] = 0.f;
     }
     const float Dv = on ? Dsk[d] : 0.f;
-    float gD = 0.f;
+    float gD = 0.f, gT = 0.f;
     constexpr int HS = SCAN_SUB / 2;
 #pragma unroll 1
     for (int s = (t1 - t0 - 1) / HS; s >= 0; --s) {              // half sub-blocks
@@ -834,7 +1205,7 @@ __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
         for (int n = 0; n < NSTATE; ++n) A2[n] = reinterpret_cast<const float*>(&A_s[n / 4][tid])[n % 4] * LOG2E_F;
         const int u0 = t0 + s * HS, nu = t1 - u0 < HS ? t1 - u0 : HS;
         const int v0 = t0 + (s / 2) * SCAN_SUB;                  // the state kept at v0 <= u0
-        float hist[HS][NSTATE], av[HS][NSTATE], dv[HS], xv[HS], gv[HS];
+        float hist[HS][NSTATE], av[HS][NSTATE], dv[HS], xv[HS], gv[HS], rv[HS];
         const float* hs = hsub + (scan_slot(b, NC, c, nsub, (v0 - c * Tc) / SCAN_SUB) * NSTATE) * Di + (on ? d : 0);
 #pragma unroll
         for (int n = 0; n < NSTATE; ++n) hist[0][n] = on ? hs[(long long)n * Di] : 0.f;
@@ -845,6 +1216,7 @@ __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
             dv[j] = in ? dt[at] : 0.f;
             xv[j] = in ? xs[at] : 0.f;
             gv[j] = in ? dy[at] : 0.f;
+            rv[j] = in && dtr ? dtr[at] : 0.f;
         }
         if (u0 > v0) {                                           // uniform: walk the first half without keeping it
             float dw[HS], xw[HS];
@@ -896,6 +1268,10 @@ __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
             }
             dx_v += Dv * g;
             gD += g * x;
+            if (dtr) {                                           // through dt = softplus(dtr)
+                ddt_v = rv[j] > 20.0f ? ddt_v : ddt_v / (1.0f + expf(-rv[j]));
+                gT += ddt_v;
+            }
             if (on) { ddt[row * Di + d] = ddt_v; dxs[row * Di + d] = dx_v; }
             // dB (index n) and dC (index 16 + n) of this row over the wave's 64 channels
             const float v = wave_sum32_tail(pv, lane);
@@ -907,6 +1283,7 @@ __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
         for (int n = 0; n < NSTATE; ++n)
             pA[(slot * Di + d) * NSTATE + n] = gA[n] * reinterpret_cast<const float*>(&A_s[n / 4][tid])[n % 4];
         pD[slot * Di + d] = gD;
+        if (dtr) pT[slot * Di + d] = gT;
     }
 }
 
@@ -1031,11 +1408,12 @@ struct TrainCtx {
     long long step = 0;
     // activations (per layer) and backward temporaries, sized for rows x widths
     int B = 0, T = 0, Tc = 0;
-    std::vector<Buf> rin, a, st, xz, xc, xs, dbc, dtr, dt, y, g, hs;
+    std::vector<Buf> rin, a, st, xz, xs, dbc, dtr, dt, y, g, hs;
     std::vector<Buf> fr, fu, fg, ff, fst;   // feed-forward: input r, W1 r + b1, GELU of it, W2 . + b2, LN stats
     Buf fdu;                                // feed-forward backward: gradient of the hidden row
-    Buf rcur, rfin, rf, stf, logits, rowloss;
-    Buf dr, tmp, t2, dg, dyb, dxz, ddbc, ddt, ddtr, dxs, dxc, ghb, pbc, pA, pD, part, gws;
+    Buf wf;                                 // prepared weight matrices of the step
+    Buf rfin, rf, stf, logits, rowloss;
+    Buf dr, tmp, dyb, dxz, ddbc, ddtr, dxs, ghb, pbc, pA, pD, pT, part, gws;
 };
 
 void train_ctx_free(void* p) { delete static_cast<TrainCtx*>(p); }
@@ -1077,35 +1455,223 @@ hipError_t gemm(int dt, const float* A, long long sam, long long sak, const floa
     return hipGetLastError();
 }
 
-// Row-major linear maps of X [rows, K] (row stride lx) with W [N, K]:
-hipError_t lin_fwd(int dt, const float* X, int lx, const float* W, int N, int K, float* Y, int ly, long long rows,
-                   int accumulate, float* ws, hipStream_t s) {          // Y (+)= X W^T
-    return gemm(dt, X, lx, 1, W, 1, K, (int)rows, N, K, Y, ly, accumulate, ws, s);
+// Columns of k_trow for a reduction of K: the next size it is built for, or 0.
+int trow_kp(int K) {
+    if (K <= 32) return 32;
+    if (K <= 64) return 64;
+    for (int kp : {128, 256, 512, 1024, 2048})
+        if (K == kp) return kp;
+    return 0;
 }
-hipError_t lin_bwd_x(int dt, const float* dY, int ldy, const float* W, int N, int K, float* dX, int ldx,
-                     long long rows, int accumulate, float* ws, hipStream_t s) {   // dX (+)= dY W
-    return gemm(dt, dY, ldy, 1, W, K, 1, (int)rows, K, N, dX, ldx, accumulate, ws, s);
+template <int DT, int EPI, int KP, int BM, int FN>
+hipError_t trow_launch(const TRow& p, hipStream_t s) {
+    const size_t lds = (size_t)BM * (DT == 0 ? (KP + 4) * 4 : (KP + 8) * 2);
+    auto kern = k_trow<DT, EPI, KP, BM, FN>;
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((p.M + BM - 1) / BM), dim3(256), lds, s, p);
+    return hipGetLastError();
 }
-hipError_t lin_bwd_w(int dt, const float* dY, int ldy, const float* X, int lx, int N, int K, float* dW,
-                     long long rows, float* ws, hipStream_t s) {         // dW = dY^T X
-    return gemm(dt, dY, 1, ldy, X, lx, 1, N, K, rows, dW, K, 0, ws, s);
+template <int DT, int EPI, int KP>
+hipError_t trow_epi_launch(const TRow& p, hipStream_t s) {
+    constexpr int BM = KP <= 256 ? 64 : (KP * (DT == 0 ? 2 : 1) <= 1024 ? 32 : 16);
+    const bool wide = p.N > 192;
+    if constexpr (BM > 16) {
+        if (p.span == 0 && p.M >= 256 * BM)
+            return wide ? trow_launch<DT, EPI, KP, BM, 4>(p, s) : trow_launch<DT, EPI, KP, BM, 1>(p, s);
+    }
+    return wide ? trow_launch<DT, EPI, KP, 16, 4>(p, s) : trow_launch<DT, EPI, KP, 16, 1>(p, s);
+}
+// the epilogues that a reduction of KP occurs with: 2 with K = dt_rank, 3 with
+// K = d_model, 1 with K = d_inner or dt_rank + 32
+template <int DT, int KP>
+hipError_t trow_kp_launch(const TRow& p, hipStream_t s) {
+    if constexpr (KP > 32) {
+        if (p.epi == 0) return trow_epi_launch<DT, 0, KP>(p, s);
+    }
+    if constexpr (KP >= 64 && KP <= 1024) {
+        if (p.epi == 1) return trow_epi_launch<DT, 1, KP>(p, s);
+    }
+    if constexpr (KP == 32) {
+        if (p.epi == 2) return trow_epi_launch<DT, 2, KP>(p, s);
+    }
+    if constexpr (KP >= 64 && KP <= 512) {
+        if (p.epi == 3) return trow_epi_launch<DT, 3, KP>(p, s);
+    }
+    return hipErrorInvalidValue;
+}
+// p.W prepared with trow_kp(p.K) columns
+hipError_t trow(int dt, TRow p, hipStream_t s) {
+    const int S = gemm_splits(p.M, p.N, p.K);
+    // f32 operands are not rounded again, so their sums may be taken in one chain
+    p.span = dt == 1 && S > 1 ? ((p.K + S - 1) / S + TG_BK - 1) / TG_BK : 0;
+#define TROW_K(KPV) case KPV: return dt == 0 ? trow_kp_launch<0, KPV>(p, s) : trow_kp_launch<1, KPV>(p, s);
+    switch (trow_kp(p.K)) {
+        TROW_K(32) TROW_K(64) TROW_K(128) TROW_K(256) TROW_K(512) TROW_K(1024) TROW_K(2048)
+        default: return hipErrorInvalidValue;
+    }
+#undef TROW_K
 }
 
-// out[n] = column sums over rows of X[:, off + n], n < N (fixed row slices)
-hipError_t colsum(const float* X, long long rows, int ld, int off, int N, float* part, float* out, hipStream_t s) {
-    const long long S = row_slices(rows);
-    const long long per = (rows + S - 1) / S;
-    hipLaunchKernelGGL(k_colsum_part, dim3(blocks(N), (unsigned)S), dim3(256), 0, s, X, rows, ld, off, N, per, part);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(N, 64)), dim3(256), 0, s, part, (int)S, (long long)N, (long long)N,
-                       out, 0);
+// Slices of a weight gradient's rows: one workgroup per tile and slice, 256 in
+// all (each of 8 waves with a quarter of a CU's registers per wave), but at
+// least 128 rows per slice.
+struct WCut {
+    int TA, TB, S;
+    long long per;
+};
+WCut wgrad_cut(int N, int K, long long rows) {
+    WCut q;
+    q.TA = N <= 64 ? 64 : 256;
+    q.TB = N > 64 && K <= 64 ? 64 : 256;
+    const long long tiles = (long long)((N + q.TA - 1) / q.TA) * ((K + q.TB - 1) / q.TB);
+    long long S = std::max(1LL, std::min(256 / tiles, (rows + 127) / 128));
+    if (S > 8) S = S / 8 * 8;
+    q.per = ((rows + S - 1) / S + 31) / 32 * 32;
+    q.S = (int)((rows + q.per - 1) / q.per);
+    return q;
+}
+// dW [N][K] = dY^T X over the rows (N, K and both strides multiples of 4)
+hipError_t wgrad(int dt, const float* dY, int ldy, const float* X, int ldx, int N, int K, float* dW, long long rows,
+                 float* ws, hipStream_t s) {
+    const WCut q = wgrad_cut(N, K, rows);
+    const dim3 grid(q.S, ((N + q.TA - 1) / q.TA) * ((K + q.TB - 1) / q.TB));
+    float* out = q.S > 1 ? ws : dW;
+#define TGW(DT, A, B) \
+    hipLaunchKernelGGL((k_tg_w<DT, A, B>), grid, dim3(512), 0, s, dY, (long long)ldy, N, X, (long long)ldx, K, rows, q.per, out)
+    if (dt == 0) {
+        if (q.TA == 64) TGW(0, 64, 256);
+        else if (q.TB == 64) TGW(0, 256, 64);
+        else TGW(0, 256, 256);
+    } else {
+        if (q.TA == 64) TGW(1, 64, 256);
+        else if (q.TB == 64) TGW(1, 256, 64);
+        else TGW(1, 256, 256);
+    }
+#undef TGW
+    if (q.S > 1)
+        hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)N * K, 64)), dim3(256), 0, s, ws, q.S, (long long)N * K,
+                           (long long)N * K, dW, 0);
     return hipGetLastError();
 }
 
-// scratch floats the fixed-order row reductions need
-size_t part_floats(long long rows, int D, int Di, int H) {
+// out[n] = column sums over the rows of X[:, n], n < N (fixed row slices)
+hipError_t colsum(const float* X, long long rows, int ld, int N, float* part, float* out, hipStream_t s) {
     const long long S = row_slices(rows);
-    return (size_t)S * std::max<size_t>({(size_t)VOCAB * D, (size_t)Di * (KCONV + 1), (size_t)2 * Di, 256,
-                                         (size_t)H});
+    const long long per = (rows + S - 1) / S;
+    hipLaunchKernelGGL(k_colsum_part, dim3(blocks(N), (unsigned)S), dim3(256), 0, s, X, rows, ld, N, per, part);
+    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(N, 64)), dim3(256), 0, s, part, (int)S, (long long)N, (long long)N, out,
+                       0);
+    return hipGetLastError();
+}
+void ln_fwd(const float* x, long long rows, int D, const float* w, const float* b, float* out, float* st, hipStream_t s) {
+    const dim3 g(blocks(rows, 4)), t(256);
+    switch (D) {
+        case 64: hipLaunchKernelGGL(k_tr_ln_fwd<1>, g, t, 0, s, x, rows, w, b, out, st); break;
+        case 128: hipLaunchKernelGGL(k_tr_ln_fwd<2>, g, t, 0, s, x, rows, w, b, out, st); break;
+        case 256: hipLaunchKernelGGL(k_tr_ln_fwd<4>, g, t, 0, s, x, rows, w, b, out, st); break;
+        default: hipLaunchKernelGGL(k_tr_ln_fwd<8>, g, t, 0, s, x, rows, w, b, out, st); break;      // 512
+    }
+}
+// dx (+)= the LayerNorm's input gradient; gwb [2][D] = its weight and bias gradients
+void ln_bwd(const float* dy, const float* x, const float* st, long long rows, int D, const float* w, float* dx,
+            int accumulate, float* part, float* gwb, hipStream_t s) {
+    const long long S = row_slices(rows, 1024, 16), per = (rows + S - 1) / S;
+    const dim3 g((unsigned)S), t(256);
+    switch (D) {
+        case 64: hipLaunchKernelGGL(k_tr_ln_bwd<1>, g, t, 0, s, dy, x, st, rows, per, w, dx, accumulate, part); break;
+        case 128: hipLaunchKernelGGL(k_tr_ln_bwd<2>, g, t, 0, s, dy, x, st, rows, per, w, dx, accumulate, part); break;
+        case 256: hipLaunchKernelGGL(k_tr_ln_bwd<4>, g, t, 0, s, dy, x, st, rows, per, w, dx, accumulate, part); break;
+        default: hipLaunchKernelGGL(k_tr_ln_bwd<8>, g, t, 0, s, dy, x, st, rows, per, w, dx, accumulate, part); break;
+    }
+    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(2 * D, 64)), dim3(256), 0, s, part, (int)S, 2LL * D, 2LL * D, gwb, 0);
+}
+
+// scratch floats the fixed-order row reductions need
+size_t part_floats(int B, int Tn, int D, int Di, int H) {
+    const long long rows = (long long)B * Tn, S = row_slices(rows);
+    const size_t conv = (size_t)B * ((Tn + CONV_TS - 1) / CONV_TS) * Di * (KCONV + 1);
+    return std::max<size_t>({(size_t)S * VOCAB * D, (size_t)S * std::max(H, 256), conv,
+                             (size_t)row_slices(rows, 1024, 16) * 2 * D});
+}
+
+// The prepared weight matrices of a training step: per layer in_proj, x_proj,
+// dt_proj, out_proj and their transposes (for the input gradients), with the
+// feed-forward sub-layer W1, W2 and theirs; then the head and its transpose.
+enum { WF_IN, WF_X, WF_DT, WF_OUT, WF_OUT_T, WF_DT_T, WF_X_T, WF_IN_T, WF_W1, WF_W2, WF_W2_T, WF_W1_T };
+struct WMat {
+    const float* w;                   // X(n, k) = w[n sn + k sk]
+    int sn, sk, N, K;
+    size_t at;                        // byte offset of the prepared copy
+    size_t bytes(int dt) const {
+        const int kp = trow_kp(K);
+        return kp ? (size_t)((N + 63) / 64 * 64) * kp * (dt == 0 ? 4 : 2) : 0;
+    }
+};
+// matrices of layer l (l == L: the head and its transpose), placed from *at on
+std::vector<WMat> layer_mats(const Layout& L, const float* w, int l, int dt, size_t* at) {
+    const int D = L.D, Di = L.Di, R = L.R, NO = R + 2 * NSTATE, H = L.H;
+    std::vector<WMat> v;
+    auto add = [&](uint64_t off, int N, int K, bool t) {     // stored [N][K]; t: the transpose
+        WMat m{w + off, t ? 1 : K, t ? K : 1, t ? K : N, t ? N : K, *at};
+        *at += (m.bytes(dt) + 255) / 256 * 256;
+        v.push_back(m);
+    };
+    if (l == L.L) {
+        add(L.head_w, 256, D, false);
+        add(L.head_w, 256, D, true);
+        return v;
+    }
+    const LayerOff& o = L.layer[l];
+    add(o.in_w, 2 * Di, D, false);
+    add(o.xw, NO, Di, false);
+    add(o.dtw, Di, R, false);
+    add(o.out_w, D, Di, false);
+    add(o.out_w, D, Di, true);
+    add(o.dtw, Di, R, true);
+    add(o.xw, NO, Di, true);
+    add(o.in_w, 2 * Di, D, true);
+    if (H) {
+        add(o.ffn_w1, H, D, false);
+        add(o.ffn_w2, D, H, false);
+        add(o.ffn_w2, D, H, true);
+        add(o.ffn_w1, H, D, true);
+    }
+    return v;
+}
+size_t wfrag_bytes(const Layout& L) {                        // FP32 copies are the larger ones
+    size_t at = 0;
+    for (int l = 0; l <= L.L; ++l) (void)layer_mats(L, nullptr, l, 0, &at);
+    return at;
+}
+hipError_t prep_mats(const std::vector<WMat>& v, int dt, uint8_t* base, hipStream_t s) {
+    FragJobs jobs{};
+    int n = 0;
+    for (const WMat& m : v)
+        if (const int kp = trow_kp(m.K))
+            jobs.j[n++] = FragJob{m.w, base + m.at, m.sn, m.sk, m.N, m.K, (m.N + 63) / 64 * 64, kp};
+    if (dt == 0) hipLaunchKernelGGL(k_tr_frags<0>, dim3(128, n), dim3(256), 0, s, jobs);
+    else hipLaunchKernelGGL(k_tr_frags<1>, dim3(128, n), dim3(256), 0, s, jobs);
+    return hipGetLastError();
+}
+// Y = X . W^T for the prepared matrix (epi and its operands as in TRow; a
+// reduction k_trow is not built for, a feed-forward width, goes to k_tg)
+hipError_t lin(int dt, const WMat& m, const uint8_t* base, const float* X, int lx, long long rows, float* Y, int ly,
+               TRow p, float* ws, hipStream_t s) {
+    if (!trow_kp(m.K))
+        return p.epi > 1 ? hipErrorInvalidValue
+                         : gemm(dt, X, lx, 1, m.w, m.sk, m.sn, (int)rows, m.N, m.K, Y, ly, p.epi, ws, s);
+    p.A = X;
+    p.lda = lx;
+    p.M = (int)rows;
+    p.K = m.K;
+    p.N = m.N;
+    p.W = base + m.at;
+    p.C = Y;
+    p.ldc = ly;
+    return trow(dt, p, s);
 }
 
 // ------------------------------------------------------------ selective scan launches
@@ -1166,7 +1732,8 @@ hipError_t scan_y(const float* x, const float* dt, const float* dbc, int NO, int
 // scratch (scan_block_floats floats for ghb and pA, a 16th of it for pD).
 hipError_t scan_grads(const float* x, const float* dt, const float* dbc, int NO, int R, const float* A_log,
                       const float* Dsk, const float* dy, int B, int Tn, int Di, const ScanCut& q, const float* hsub,
-                      float* ghb, float* dx, float* ddt, float* pbc, float* pA, float* pD, hipStream_t s) {
+                      float* ghb, const float* dtr, float* dx, float* ddt, float* pbc, float* pA, float* pD, float* pT,
+                      hipStream_t s) {
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH, w = std::min(4, dblk);
     const bool few = (long long)dblk * B < 256, al = q.NC == 1 || q.Tc % 8 == 0;
 #define GSTATES(NPT, AL) hipLaunchKernelGGL((k_tr_gstates<NPT, AL>), dim3(dblk * (4 / NPT), 1, B), dim3(256), 0, s, dt, \
@@ -1178,7 +1745,7 @@ hipError_t scan_grads(const float* x, const float* dt, const float* dbc, int NO,
 #undef GSTATES
     hipLaunchKernelGGL(k_tr_scan_bwd, dim3((dblk + w - 1) / w, q.NBS, B), dim3(64 * w),
                        (size_t)q.TB * 2 * NSTATE * sizeof(float), s, x, dt, dbc, NO, R, A_log, Dsk, dy, (long long)B * Tn,
-                       Tn, Di, q.Tc, q.NC, q.TB, q.nblk, hsub, q.nsub, ghb, dx, ddt, pbc, pA, pD);
+                       Tn, Di, q.Tc, q.NC, q.TB, q.nblk, hsub, q.nsub, ghb, dtr, dx, ddt, pbc, pA, pD, pT);
     return hipGetLastError();
 }
 }  // namespace
@@ -1193,7 +1760,7 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
     const ScanCut q = scan_cut(B, Tn, Di, Tn);
     c->B = c->T = c->Tc = 0;
-    c->rin.resize(L.L); c->a.resize(L.L); c->st.resize(L.L); c->xz.resize(L.L); c->xc.resize(L.L);
+    c->rin.resize(L.L); c->a.resize(L.L); c->st.resize(L.L); c->xz.resize(L.L); 
     c->xs.resize(L.L); c->dbc.resize(L.L); c->dtr.resize(L.L); c->dt.resize(L.L); c->y.resize(L.L);
     c->g.resize(L.L); c->hs.resize(L.L);
     if (L.H) {
@@ -1207,29 +1774,31 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
     }
     for (int l = 0; l < L.L; ++l) {
         TCHK(c->rin[l].ensure(rows * D * F)); TCHK(c->a[l].ensure(rows * D * F)); TCHK(c->st[l].ensure(rows * 2 * F));
-        TCHK(c->xz[l].ensure(rows * 2 * Di * F)); TCHK(c->xc[l].ensure(rows * Di * F));
+        TCHK(c->xz[l].ensure(rows * 2 * Di * F));
         TCHK(c->xs[l].ensure(rows * Di * F)); TCHK(c->dbc[l].ensure(rows * NO * F));
         TCHK(c->dtr[l].ensure(rows * Di * F)); TCHK(c->dt[l].ensure(rows * Di * F));
         TCHK(c->y[l].ensure(rows * Di * F)); TCHK(c->g[l].ensure(rows * Di * F));
         TCHK(c->hs[l].ensure(scan_hsub_floats(q, B, Di) * F));
     }
-    TCHK(c->rcur.ensure(rows * D * F)); TCHK(c->rfin.ensure(rows * D * F));
+    TCHK(c->wf.ensure(wfrag_bytes(L)));
+    TCHK(c->rfin.ensure(rows * D * F));
     TCHK(c->rf.ensure(rows * D * F)); TCHK(c->stf.ensure(rows * 2 * F)); TCHK(c->logits.ensure(rows * 256 * F));
     TCHK(c->rowloss.ensure(rows * F));
-    TCHK(c->dr.ensure(rows * D * F)); TCHK(c->tmp.ensure(rows * D * F)); TCHK(c->t2.ensure(rows * D * F));
-    TCHK(c->dg.ensure(rows * Di * F)); TCHK(c->dyb.ensure(rows * Di * F)); TCHK(c->dxz.ensure(rows * 2 * Di * F));
-    TCHK(c->ddbc.ensure(rows * NO * F)); TCHK(c->ddt.ensure(rows * Di * F)); TCHK(c->ddtr.ensure(rows * Di * F));
-    TCHK(c->dxs.ensure(rows * Di * F)); TCHK(c->dxc.ensure(rows * Di * F));
+    TCHK(c->dr.ensure(rows * D * F)); TCHK(c->tmp.ensure(rows * D * F));
+    TCHK(c->dyb.ensure(rows * Di * F)); TCHK(c->dxz.ensure(rows * 2 * Di * F));
+    TCHK(c->ddbc.ensure(rows * NO * F)); TCHK(c->ddtr.ensure(rows * Di * F));
+    TCHK(c->dxs.ensure(rows * Di * F));
     TCHK(c->ghb.ensure(scan_block_floats(q, B, Di) * F));
     TCHK(c->pbc.ensure((size_t)dblk * rows * 2 * NSTATE * F));
     TCHK(c->pA.ensure(scan_block_floats(q, B, Di) * F)); TCHK(c->pD.ensure(scan_block_floats(q, B, Di) / NSTATE * F));
-    TCHK(c->part.ensure(part_floats((long long)rows, D, Di, L.H) * F));
+    TCHK(c->pT.ensure(scan_block_floats(q, B, Di) / NSTATE * F));
+    TCHK(c->part.ensure(part_floats(B, Tn, D, Di, L.H) * F));
     // split partials of the weight-gradient GEMMs (the largest of the shapes used)
     size_t ws = 0;
     const long long R = (long long)rows;
     const int Hs = L.H ? L.H : D;
     for (int N : {2 * Di, NO, Di, D, 256, Hs})        // weight gradients [N, K] over the rows
-        for (int K : {D, Di, L.R, Hs}) ws = std::max(ws, gemm_ws_floats(N, K, R));
+        for (int K : {D, Di, L.R, Hs}) ws = std::max(ws, (size_t)wgrad_cut(N, K, R).S * N * K);
     for (int N : {2 * Di, NO, Di, D, 256, L.R, Hs})   // forward and input gradients of few rows
         for (int K : {D, Di, L.R, 2 * Di, NO, 256, Hs}) ws = std::max(ws, gemm_ws_floats((int)R, N, K));
     TCHK(c->gws.ensure(std::max<size_t>(ws, 1) * F));
@@ -1269,8 +1838,8 @@ int scan_bwd(const float* x, const float* dt, const float* A_log, const float* b
     TCHK(pD.alloc(scan_block_floats(q, B, Di) / NSTATE * sizeof(float)));
     TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, q.Tc, q.NC, hsave, hsub.f(), SCAN_SUB, q.nsub, nullptr, 1,
                      s));
-    TCHK(scan_grads(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, dy, B, T, Di, q, hsub.f(), ghb.f(), dx, ddt, pbc.f(), pA.f(),
-                    pD.f(), s));
+    TCHK(scan_grads(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, dy, B, T, Di, q, hsub.f(), ghb.f(), nullptr, dx, ddt, pbc.f(),
+                    pA.f(), pD.f(), nullptr, s));
     hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, pbc.f(), dblk, rows, dbc,
                        2 * NSTATE, 0);
     hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, pA.f(), B * q.NBS,
@@ -1300,42 +1869,53 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
     const size_t F = sizeof(float);
     float* ws = c->gws.f();
     float* part = c->part.f();
+    uint8_t* wf = static_cast<uint8_t*>(c->wf.p);
+    std::vector<std::vector<WMat>> wm;
+    size_t wat = 0;
+    for (int l = 0; l <= L.L; ++l) {
+        wm.push_back(layer_mats(L, Wt, l, dt, &wat));
+        TCHK(prep_mats(wm.back(), dt, wf, s));
+    }
+    const dim3 cblk(std::min(256, Di)), cgrid((Di + 255) / 256, (Tn + CONV_TS - 1) / CONV_TS, B);
+    auto store = [] { return TRow{}; };
+    auto add_to = [](const float* Cin) { TRow p{}; p.epi = 1; p.Cin = Cin; return p; };
     // ---------------- forward
-    hipLaunchKernelGGL(k_tr_embed, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, tok, B, T, Wt + L.embed, D, c->rcur.f());
+    hipLaunchKernelGGL(k_tr_embed, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, tok, B, T, Wt + L.embed, D,
+                       c->rin[0].f());
     for (int l = 0; l < L.L; ++l) {
         const LayerOff& o = L.layer[l];
-        TCHK(hipMemcpyAsync(c->rin[l].p, c->rcur.p, rows * D * F, hipMemcpyDeviceToDevice, s));
-        hipLaunchKernelGGL(k_tr_ln_fwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, c->rin[l].f(), rows, D,
-                           Wt + o.norm_w, Wt + o.norm_b, c->a[l].f(), c->st[l].f());
-        TCHK(lin_fwd(dt, c->a[l].f(), D, Wt + o.in_w, 2 * Di, D, c->xz[l].f(), 2 * Di, rows, 0, ws, s));
-        hipLaunchKernelGGL(k_tr_conv_fwd, dim3(blocks(rows * Di)), dim3(256), 0, s, c->xz[l].f(), rows, Tn, Di,
-                           Wt + o.conv_w, Wt + o.conv_b, c->xc[l].f(), c->xs[l].f());
-        TCHK(lin_fwd(dt, c->xs[l].f(), Di, Wt + o.xw, NO, Di, c->dbc[l].f(), NO, rows, 0, ws, s));
-        TCHK(lin_fwd(dt, c->dbc[l].f(), NO, Wt + o.dtw, Di, R, c->dtr[l].f(), Di, rows, 0, ws, s));
-        hipLaunchKernelGGL(k_tr_bias_softplus, dim3(blocks(rows * Di)), dim3(256), 0, s, c->dtr[l].f(), rows, Di,
-                           Wt + o.dtb, c->dt[l].f());
+        const std::vector<WMat>& w = wm[l];
+        float* rnext = l + 1 < L.L ? c->rin[l + 1].f() : c->rfin.f();
+        ln_fwd(c->rin[l].f(), rows, D, Wt + o.norm_w, Wt + o.norm_b, c->a[l].f(), c->st[l].f(), s);
+        TCHK(lin(dt, w[WF_IN], wf, c->a[l].f(), D, rows, c->xz[l].f(), 2 * Di, store(), ws, s));
+        hipLaunchKernelGGL(k_tr_conv_fwd, cgrid, cblk, 0, s, c->xz[l].f(), Tn, Di, Wt + o.conv_w, Wt + o.conv_b,
+                           c->xs[l].f());
+        TCHK(lin(dt, w[WF_X], wf, c->xs[l].f(), Di, rows, c->dbc[l].f(), NO, store(), ws, s));
+        {
+            TRow p{};
+            p.epi = 2;
+            p.bias = Wt + o.dtb;
+            p.C2 = c->dt[l].f();
+            TCHK(lin(dt, w[WF_DT], wf, c->dbc[l].f(), NO, rows, c->dtr[l].f(), Di, p, ws, s));
+        }
         TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, Tn, 1, nullptr,
                          c->hs[l].f(), SCAN_SUB, cut.nsub, nullptr, 1, s));
         TCHK(scan_y(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->xz[l].f(), B, Tn, Di,
                     c->hs[l].f(), SCAN_SUB, cut.nsub, c->y[l].f(), c->g[l].f(), s));
-        TCHK(lin_fwd(dt, c->g[l].f(), Di, Wt + o.out_w, D, Di, c->rcur.f(), D, rows, 1, ws, s));
+        TCHK(lin(dt, w[WF_OUT], wf, c->g[l].f(), Di, rows, L.H ? c->fr[l].f() : rnext, D, add_to(c->rin[l].f()), ws, s));
         if (L.H) {            // r <- LayerNorm(W2 GELU(W1 r + b1) + b2)
             const int H = L.H;
-            TCHK(hipMemcpyAsync(c->fr[l].p, c->rcur.p, rows * D * F, hipMemcpyDeviceToDevice, s));
-            TCHK(lin_fwd(dt, c->fr[l].f(), D, Wt + o.ffn_w1, H, D, c->fu[l].f(), H, rows, 0, ws, s));
+            TCHK(lin(dt, w[WF_W1], wf, c->fr[l].f(), D, rows, c->fu[l].f(), H, store(), ws, s));
             hipLaunchKernelGGL(k_tr_bias_gelu, dim3(blocks(rows * H)), dim3(256), 0, s, c->fu[l].f(), rows, H,
                                Wt + o.ffn_b1, c->fg[l].f());
-            TCHK(lin_fwd(dt, c->fg[l].f(), H, Wt + o.ffn_w2, D, H, c->ff[l].f(), D, rows, 0, ws, s));
+            TCHK(lin(dt, w[WF_W2], wf, c->fg[l].f(), H, rows, c->ff[l].f(), D, store(), ws, s));
             hipLaunchKernelGGL(k_tr_add_bias, dim3(blocks(rows * D)), dim3(256), 0, s, c->ff[l].f(), rows, D,
                                Wt + o.ffn_b2);
-            hipLaunchKernelGGL(k_tr_ln_fwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, c->ff[l].f(), rows, D,
-                               Wt + o.ffn_nw, Wt + o.ffn_nb, c->rcur.f(), c->fst[l].f());
+            ln_fwd(c->ff[l].f(), rows, D, Wt + o.ffn_nw, Wt + o.ffn_nb, rnext, c->fst[l].f(), s);
         }
     }
-    TCHK(hipMemcpyAsync(c->rfin.p, c->rcur.p, rows * D * F, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(k_tr_ln_fwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, c->rfin.f(), rows, D, Wt + L.norm_f_w,
-                       Wt + L.norm_f_b, c->rf.f(), c->stf.f());
-    TCHK(lin_fwd(dt, c->rf.f(), D, Wt + L.head_w, 256, D, c->logits.f(), 256, rows, 0, ws, s));
+    ln_fwd(c->rfin.f(), rows, D, Wt + L.norm_f_w, Wt + L.norm_f_b, c->rf.f(), c->stf.f(), s);
+    TCHK(lin(dt, wm[L.L][0], wf, c->rf.f(), D, rows, c->logits.f(), 256, store(), ws, s));
     hipLaunchKernelGGL(k_tr_ce, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, c->logits.f(), Wt + L.head_b, tok, B, T,
                        c->rowloss.f(), 1.0f / (float)rows);
     hipLaunchKernelGGL((k_sum_all<float>), dim3(1), dim3(256), 0, s, (const float*)c->rowloss.f(), rows,
@@ -1344,71 +1924,64 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
     float* G = grad;
     float* dr = c->dr.f();
     float* tmp = c->tmp.f();
-    float* t2 = c->t2.f();
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
-    TCHK(lin_bwd_w(dt, c->logits.f(), 256, c->rf.f(), D, 256, D, G + L.head_w, rows, ws, s));
-    TCHK(colsum(c->logits.f(), rows, 256, 0, 256, part, G + L.head_b, s));
-    TCHK(lin_bwd_x(dt, c->logits.f(), 256, Wt + L.head_w, 256, D, tmp, D, rows, 0, ws, s));   // d rf
-    hipLaunchKernelGGL(k_tr_ln_bwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, tmp, c->rfin.f(), c->stf.f(), rows, D,
-                       Wt + L.norm_f_w, dr, 0, t2);
-    TCHK(colsum(t2, rows, D, 0, D, part, G + L.norm_f_w, s));
-    TCHK(colsum(tmp, rows, D, 0, D, part, G + L.norm_f_b, s));
+    TCHK(wgrad(dt, c->logits.f(), 256, c->rf.f(), D, 256, D, G + L.head_w, rows, ws, s));
+    TCHK(colsum(c->logits.f(), rows, 256, 256, part, G + L.head_b, s));
+    TCHK(lin(dt, wm[L.L][1], wf, c->logits.f(), 256, rows, tmp, D, store(), ws, s));          // d rf
+    ln_bwd(tmp, c->rfin.f(), c->stf.f(), rows, D, Wt + L.norm_f_w, dr, 0, part, G + L.norm_f_w, s);
     for (int l = L.L - 1; l >= 0; --l) {
         const LayerOff& o = L.layer[l];
+        const std::vector<WMat>& w = wm[l];
         if (L.H) {            // through LayerNorm(FFN(r)); no residual around it
             const int H = L.H;
-            hipLaunchKernelGGL(k_tr_ln_bwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, dr, c->ff[l].f(),
-                               c->fst[l].f(), rows, D, Wt + o.ffn_nw, tmp, 0, t2);          // tmp = d f
-            TCHK(colsum(t2, rows, D, 0, D, part, G + o.ffn_nw, s));
-            TCHK(colsum(dr, rows, D, 0, D, part, G + o.ffn_nb, s));
-            TCHK(lin_bwd_w(dt, tmp, D, c->fg[l].f(), H, D, H, G + o.ffn_w2, rows, ws, s));
-            TCHK(colsum(tmp, rows, D, 0, D, part, G + o.ffn_b2, s));
-            TCHK(lin_bwd_x(dt, tmp, D, Wt + o.ffn_w2, D, H, c->fdu.f(), H, rows, 0, ws, s));   // d GELU
+            ln_bwd(dr, c->ff[l].f(), c->fst[l].f(), rows, D, Wt + o.ffn_nw, tmp, 0, part, G + o.ffn_nw, s);   // tmp = d f
+            TCHK(wgrad(dt, tmp, D, c->fg[l].f(), H, D, H, G + o.ffn_w2, rows, ws, s));
+            TCHK(colsum(tmp, rows, D, D, part, G + o.ffn_b2, s));
+            TCHK(lin(dt, w[WF_W2_T], wf, tmp, D, rows, c->fdu.f(), H, store(), ws, s));          // d GELU
             hipLaunchKernelGGL(k_tr_gelu_bwd, dim3(blocks(rows * H)), dim3(256), 0, s, c->fdu.f(), c->fu[l].f(),
                                rows * H);
-            TCHK(lin_bwd_w(dt, c->fdu.f(), H, c->fr[l].f(), D, H, D, G + o.ffn_w1, rows, ws, s));
-            TCHK(colsum(c->fdu.f(), rows, H, 0, H, part, G + o.ffn_b1, s));
-            TCHK(lin_bwd_x(dt, c->fdu.f(), H, Wt + o.ffn_w1, H, D, dr, D, rows, 0, ws, s));    // d r
+            TCHK(wgrad(dt, c->fdu.f(), H, c->fr[l].f(), D, H, D, G + o.ffn_w1, rows, ws, s));
+            TCHK(colsum(c->fdu.f(), rows, H, H, part, G + o.ffn_b1, s));
+            TCHK(lin(dt, w[WF_W1_T], wf, c->fdu.f(), H, rows, dr, D, store(), ws, s));           // d r
         }
-        TCHK(lin_bwd_w(dt, dr, D, c->g[l].f(), Di, D, Di, G + o.out_w, rows, ws, s));
-        TCHK(lin_bwd_x(dt, dr, D, Wt + o.out_w, D, Di, c->dg.f(), Di, rows, 0, ws, s));
-        hipLaunchKernelGGL(k_tr_gate_bwd, dim3(blocks(rows * Di)), dim3(256), 0, s, c->dg.f(), c->y[l].f(),
-                           c->xz[l].f(), rows, Di, c->dyb.f(), c->dxz.f());
+        TCHK(wgrad(dt, dr, D, c->g[l].f(), Di, D, Di, G + o.out_w, rows, ws, s));
+        {                     // d gate, straight into dy and dz
+            TRow p{};
+            p.epi = 3;
+            p.y = c->y[l].f();
+            p.z = c->xz[l].f() + Di;
+            p.C2 = c->dxz.f() + Di;
+            p.ldc2 = 2 * Di;
+            TCHK(lin(dt, w[WF_OUT_T], wf, dr, D, rows, c->dyb.f(), Di, p, ws, s));
+        }
         TCHK(scan_grads(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->dyb.f(), B, Tn,
-                        Di, cut, c->hs[l].f(), c->ghb.f(), c->dxs.f(), c->ddt.f(), c->pbc.f(), c->pA.f(), c->pD.f(),
-                        s));
+                        Di, cut, c->hs[l].f(), c->ghb.f(), c->dtr[l].f(), c->dxs.f(), c->ddtr.f(), c->pbc.f(), c->pA.f(),
+                        c->pD.f(), c->pT.f(), s));
         hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, c->pbc.f(), dblk, rows,
                            c->ddbc.f(), NO, R);
         hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, c->pA.f(), B * cut.NBS,
                            (long long)Di * NSTATE, (long long)Di * NSTATE, G + o.A_log, 0);
         hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, c->pD.f(), B * cut.NBS, (long long)Di, (long long)Di,
                            G + o.Dsk, 0);
-        hipLaunchKernelGGL(k_tr_softplus_bwd, dim3(blocks(rows * Di)), dim3(256), 0, s, c->ddt.f(), c->dtr[l].f(),
-                           rows * Di, c->ddtr.f());
-        TCHK(lin_bwd_w(dt, c->ddtr.f(), Di, c->dbc[l].f(), NO, Di, R, G + o.dtw, rows, ws, s));
-        TCHK(colsum(c->ddtr.f(), rows, Di, 0, Di, part, G + o.dtb, s));
-        TCHK(lin_bwd_x(dt, c->ddtr.f(), Di, Wt + o.dtw, Di, R, c->ddbc.f(), NO, rows, 0, ws, s));   // d delta
-        TCHK(lin_bwd_w(dt, c->ddbc.f(), NO, c->xs[l].f(), Di, NO, Di, G + o.xw, rows, ws, s));
-        TCHK(lin_bwd_x(dt, c->ddbc.f(), NO, Wt + o.xw, NO, Di, c->dxs.f(), Di, rows, 1, ws, s));  // dxs += ddbc W_x
-        hipLaunchKernelGGL(k_tr_conv_bwd_x, dim3(blocks(rows * Di)), dim3(256), 0, s, c->dxs.f(), c->xc[l].f(), rows,
-                           Tn, Di, Wt + o.conv_w, c->dxc.f(), c->dxz.f());
+        hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, c->pT.f(), B * cut.NBS, (long long)Di,
+                           (long long)Di, G + o.dtb, 0);
+        TCHK(wgrad(dt, c->ddtr.f(), Di, c->dbc[l].f(), NO, Di, R, G + o.dtw, rows, ws, s));
+        TCHK(lin(dt, w[WF_DT_T], wf, c->ddtr.f(), Di, rows, c->ddbc.f(), NO, store(), ws, s));      // d delta
+        TCHK(wgrad(dt, c->ddbc.f(), NO, c->xs[l].f(), Di, NO, Di, G + o.xw, rows, ws, s));
+        TCHK(lin(dt, w[WF_X_T], wf, c->ddbc.f(), NO, rows, c->dxs.f(), Di, add_to(c->dxs.f()), ws, s));   // dxs += ddbc W_x
         {
-            const long long S = row_slices(rows);
-            const long long per = (rows + S - 1) / S;
+            const int S = (int)(cgrid.y * cgrid.z);
             const long long stride = (long long)Di * (KCONV + 1);
-            hipLaunchKernelGGL(k_tr_conv_bwd_w_part, dim3(blocks(Di), (unsigned)S), dim3(256), 0, s, c->dxc.f(),
-                               c->xz[l].f(), rows, Tn, Di, per, part);
-            hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * KCONV, 64)), dim3(256), 0, s, part, (int)S,
+            hipLaunchKernelGGL(k_tr_conv_bwd, cgrid, cblk, 0, s, c->dxs.f(), c->xz[l].f(), Tn, Di, Wt + o.conv_w,
+                               Wt + o.conv_b, c->dxz.f(), part);
+            hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * KCONV, 64)), dim3(256), 0, s, part, S,
                                (long long)Di * KCONV, stride, G + o.conv_w, 0);
-            hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, part + (long long)Di * KCONV, (int)S,
+            hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, part + (long long)Di * KCONV, S,
                                (long long)Di, stride, G + o.conv_b, 0);
         }
-        TCHK(lin_bwd_w(dt, c->dxz.f(), 2 * Di, c->a[l].f(), D, 2 * Di, D, G + o.in_w, rows, ws, s));
-        TCHK(lin_bwd_x(dt, c->dxz.f(), 2 * Di, Wt + o.in_w, 2 * Di, D, tmp, D, rows, 0, ws, s));   // d a
-        hipLaunchKernelGGL(k_tr_ln_bwd, dim3(blocks(rows, 4)), dim3(64, 4), 0, s, tmp, c->rin[l].f(), c->st[l].f(),
-                           rows, D, Wt + o.norm_w, dr, 1, t2);
-        TCHK(colsum(t2, rows, D, 0, D, part, G + o.norm_w, s));
-        TCHK(colsum(tmp, rows, D, 0, D, part, G + o.norm_b, s));
+        TCHK(wgrad(dt, c->dxz.f(), 2 * Di, c->a[l].f(), D, 2 * Di, D, G + o.in_w, rows, ws, s));
+        TCHK(lin(dt, w[WF_IN_T], wf, c->dxz.f(), 2 * Di, rows, tmp, D, store(), ws, s));            // d a
+        ln_bwd(tmp, c->rin[l].f(), c->st[l].f(), rows, D, Wt + o.norm_w, dr, 1, part, G + o.norm_w, s);
     }
     {
         const long long S = row_slices(rows);
