@@ -177,10 +177,15 @@ hipError_t launch_ln_rows(const float* x, int M, int D, const float* w, const fl
 hipError_t launch_mid(const LayerDev& w, int Di, int R, const float* xz, float* g, int lanes, int T,
                       int lanes_per_wg, const int* row_pos, float* conv_state, float* hstate,
                       hipStream_t s);
-// g_bf16: the gated rows are written as bf16 bits (d_inner <= 512 only)
+// The encoder's mixer over a tile of T rows per lane.  dbc [M][R + 32] is
+// scratch; with few lanes (mixer_few) so are xs, dt [M][Di] and hsub
+// (mixer_hsub_floats), else they may be null.  g_bf16: the gated rows are
+// written as bf16 bits.
+bool mixer_few(int Di, int lanes);
+size_t mixer_hsub_floats(int Di, int lanes, int T);
 hipError_t launch_mid_tiled(const LayerDev& w, int Di, int R, const float* xz, float* xs, float* dbc, float* dt,
-                            float* g, int lanes, int T, const int* row_pos, float* conv_state, float* hstate,
-                            bool g_bf16, hipStream_t s);
+                            float* hsub, float* g, int lanes, int T, const int* row_pos, float* conv_state,
+                            float* hstate, bool g_bf16, hipStream_t s);
 hipError_t launch_quant_sym(const float* logits, int M, const uint8_t* data, const Plan& p,
                             const int* row_chunk, const int* row_pos, uint32_t* cf,
                             float* probs, uint16_t* tables, hipStream_t s);

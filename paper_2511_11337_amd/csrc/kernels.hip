@@ -718,6 +718,7 @@ hipError_t launch_rowgemm(int dtype, int kind, const float* A, int M, int K, con
         if (kind == 3) { RG_K(1, 3, false) }
         if (kind == 4) { RG_K(1, 1, false) }
         if (kind == 5) {
+            if (K == 1024) return rowgemm_launch<1, 2, false, 1024, true>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
             if (K == 512) return rowgemm_launch<1, 2, false, 512, true>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
             if (K == 256) return rowgemm_launch<1, 2, false, 256, true>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
             if (K == 128) return rowgemm_launch<1, 2, false, 128, true>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
@@ -801,7 +802,8 @@ hipError_t launch_ln_rows(const float* x, int M, int D, const float* w, const fl
 // ============================================================== mixer middle
 // Per-element pieces of the Mamba mixer between in_proj and out_proj
 // (Appendix A: selection mechanism and discrete recurrence).  Both the
-// encoder kernels (k_convx + k_scan) and the decoder step kernel (k_mid) call
+// encoder kernels (k_convx and the k_scan kernels) and the decoder step kernel
+// (k_mid) call
 // exactly these functions with the same operands in the same order.
 
 // ---------------------------------------------------------------- decoder step
@@ -936,275 +938,445 @@ hipError_t launch_mid(const LayerDev& w, int Di, int R, const float* xz, float* 
 }
 
 // ---------------------------------------------------------------- encoder
-// k_convx: RB consecutive rows of one lane per workgroup.  Conv + SiLU for
-// every channel (window from earlier rows of the tile, the lane's carried
-// conv state, or zero before the chunk start), then x_proj on the matrix
-// cores: wave f computes column fragments f, f + 4, ... (xproj_fragment).
-template <int Di, int RR>
-__global__ __launch_bounds__(256) void k_convx(LayerDev w, const float* __restrict__ xz, int lanes, int T,
+// The encoder's mixer runs in two kernels over a tile of T rows per lane:
+//   k_convx  conv + SiLU and x_proj, 16 rows of one lane per workgroup;
+//   k_scan   dt_proj, scan and gate, one thread per (lane, channel), rows in
+//            order.
+// Only delta, B and C (NO floats per row) pass through memory between them:
+// k_scan forms the conv output again (nine instructions) instead of reading
+// it.  With few lanes k_scan would leave most of the GPU idle behind one
+// serial chain per channel, so there k_convx also keeps the conv output and
+// Delta, k_scan_states runs the recurrence alone (one thread per channel and
+// state) and k_scan_rows the outputs in blocks of rows side by side.
+//
+// k_convx: phase 1, a thread owns channels tid, tid + 256, ... and walks the 16
+// rows with the window in registers (three rows before the block, or the
+// lane's carried conv state, or zero before a chunk start); phase 2, wave c
+// runs chain c of xproj_fragment's four for every column fragment, so that the
+// four matrix cores share the work evenly and an A operand serves all
+// fragments, and the chains are added through LDS in xproj_fragment's order;
+// KEEP: the conv output and Delta = softplus(dt_proj) of every row are written
+// too.  The first weight fragments are requested before phase 1.  Bound by the
+// f32 MFMA (NF fragments of Di / 4 steps per 16 rows) and the x read.
+// 131072 rows: 121 us at d_inner 512; at 1024 332 us, where one wave per
+// fragment and a window fetched per element took 1008 us.
+template <int Di, int RR, bool KEEP>
+__global__ __launch_bounds__(256) void k_convx(LayerDev w, const float* __restrict__ xz, int T,
                                                const int* __restrict__ row_pos,
                                                const float* __restrict__ conv_state,
-                                               float* __restrict__ xs_out, float* __restrict__ dbc_out) {
+                                               float* __restrict__ dbc_out, float* __restrict__ xs_out,
+                                               float* __restrict__ dt_out) {
     constexpr int RB = 16;
     constexpr int NO = RR + 2 * NSTATE, NF = (NO + 15) / 16;
     constexpr int XSR = Di + 4;                  // row stride in LDS: rows 4 banks apart
-    __shared__ __align__(16) float xs_s[RB * XSR];
+    constexpr int CPT = Di > 256 ? Di / 256 : 1;
+    constexpr int QC = Di / 64, QR = QC < 4 ? QC : 4;         // k-groups of a chain; groups loaded ahead
+    constexpr int XS = RB * XSR, PS = 4 * RB * 16 * NF;       // xs, then the chains' partial outputs
+    static_assert(QC % QR == 0, "whole rings");
+    __shared__ __align__(16) float xs_s[XS > PS ? XS : PS];
+    __shared__ float dl_s[KEEP ? RB * RR : 1];
     const int tid = threadIdx.x;
-    const int lane = blockIdx.y;
-    const int r0 = blockIdx.x * RB;
+    const int lane = blockIdx.x;
+    const int r0 = blockIdx.y * RB;
     const long long base = (long long)lane * T;
     const float* cst = conv_state + (long long)lane * (KCONV - 1) * Di;
+    const int nb = T - r0 < RB ? T - r0 : RB;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), wl = tid & 63;
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    const __attribute__((address_space(1))) f4v* B = (const __attribute__((address_space(1))) f4v*)w.xwF + wl;
+    f4v ring[QR][NF];                            // group q = 4 i + wv of fragment f: element (f * Di / 16 + q) * 64
+#pragma unroll
+    for (int u = 0; u < QR; ++u)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) ring[u][f] = B[(f * (Di / 16) + 4 * u + wv) * 64];
 
-    // phase 1: conv + SiLU
-    for (int it = tid; it < RB * Di; it += 256) {
-        int r = it / Di, d = it % Di;
-        int tr = r0 + r;
-        float v = 0.0f;
-        if (tr < T) {
-            int pos = row_pos[base + tr];
-            if (pos >= 0) {
-                float wv[KCONV];
+    if (tid < Di) {
+        float xv[CPT][RB], win[CPT][KCONV - 1], cw[CPT][KCONV], cb[CPT];
 #pragma unroll
-                for (int j = 0; j < KCONV; ++j) {       // wv[j] = x at offset j - 3
-                    int back = KCONV - 1 - j;
-                    float x = 0.0f;
-                    if (pos - back >= 0) {
-                        int idx = tr - back;
-                        x = idx >= 0 ? xz[(base + idx) * (2 * Di) + d] : cst[(KCONV - 1 + idx) * Di + d];
-                    }
-                    wv[j] = x;
-                }
-                float cw[KCONV];
+        for (int j = 0; j < CPT; ++j) {
+            const int d = tid + 256 * j;
 #pragma unroll
-                for (int k = 0; k < KCONV; ++k) cw[k] = w.convT[k * Di + d];
-                v = conv_silu(cw, w.conv_b[d], wv[0], wv[1], wv[2], wv[3]);
-                xs_out[(base + tr) * Di + d] = v;
+            for (int k = 0; k < KCONV - 1; ++k) {
+                const int idx = r0 - (KCONV - 1) + k;
+                win[j][k] = idx >= 0 ? xz[(base + idx) * (2 * Di) + d] : cst[(KCONV - 1 + idx) * Di + d];
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) xv[j][r] = r < nb ? xz[(base + r0 + r) * (2 * Di) + d] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < KCONV; ++k) cw[j][k] = w.convT[k * Di + d];
+            cb[j] = w.conv_b[d];
+        }
+        // taps before the chunk start are zero
+        const int p0 = row_pos[base + r0];
+#pragma unroll
+        for (int j = 0; j < CPT; ++j)
+#pragma unroll
+            for (int k = 0; k < KCONV - 1; ++k)
+                if (p0 < KCONV - 1 - k) win[j][k] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int pos = r < nb ? row_pos[base + r0 + r] : -1;
+            const bool start = r > 0 && pos == 0;
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) {
+                const int d = tid + 256 * j;
+                if (start) { win[j][0] = 0.0f; win[j][1] = 0.0f; win[j][2] = 0.0f; }
+                const float x = xv[j][r];
+                const float v = pos >= 0 ? conv_silu(cw[j], cb[j], win[j][0], win[j][1], win[j][2], x) : 0.0f;
+                win[j][0] = win[j][1];
+                win[j][1] = win[j][2];
+                win[j][2] = x;
+                xs_s[r * XSR + d] = v;
+                if (KEEP && r < nb) xs_out[(base + r0 + r) * Di + d] = v;
             }
         }
-        xs_s[r * XSR + d] = v;
     }
     __syncthreads();
-    // phase 2: x_proj
-    const int wv = tid >> 6, wl = tid & 63;
-    for (int f = wv; f < NF; f += 4) {
-        v4f acc;
-        xproj_fragment<Di>(xs_s, XSR, RB, w.xwF, f, wl, acc);
+    v4f acc[NF];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int row = 4 * (wl >> 4) + rr, col = 16 * f + (wl & 15);
-            if (r0 + row < T && col < NO) dbc_out[(base + r0 + row) * NO + col] = acc[rr];
+    for (int f = 0; f < NF; ++f) acc[f] = v4f{0.f, 0.f, 0.f, 0.f};
+    {
+        const float* A = xs_s + (wl & 15) * XSR + (wl >> 4);
+#pragma unroll
+        for (int i0 = 0; i0 < QC; i0 += QR)
+#pragma unroll
+            for (int u = 0; u < QR; ++u) {
+                const int q = 4 * (i0 + u) + wv;
+                f4v b[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    b[f] = ring[u][f];
+                    if (i0 + u + QR < QC) ring[u][f] = B[(f * (Di / 16) + q + 4 * QR) * 64];
+                }
+                const float* a = A + 16 * q;
+                const float a0 = a[0], a1 = a[4], a2 = a[8], a3 = a[12];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b[f].x, acc[f], 0, 0, 0);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b[f].y, acc[f], 0, 0, 0);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2, b[f].z, acc[f], 0, 0, 0);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(a3, b[f].w, acc[f], 0, 0, 0);
+            }
+    }
+    __syncthreads();                             // every wave is done with xs
+    // partial outputs [chain][row][column]
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+            xs_s[(wv * RB + 4 * (wl >> 4) + rr) * (16 * NF) + 16 * f + (wl & 15)] = acc[f][rr];
+    __syncthreads();
+    for (int i = tid; i < nb * NO; i += 256) {
+        const int row = i / NO, col = i % NO;
+        const float* c = xs_s + row * (16 * NF) + col;
+        constexpr int CS = RB * 16 * NF;
+        const float v = (c[0] + c[CS]) + (c[2 * CS] + c[3 * CS]);
+        dbc_out[(base + r0) * NO + i] = v;
+        if (KEEP && col < RR) dl_s[row * RR + col] = v;
+    }
+    if (KEEP) {
+        __syncthreads();
+        if (tid < Di) {
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) {
+                const int d = tid + 256 * j;
+                float dtw[RR];
+#pragma unroll
+                for (int k = 0; k < RR; ++k) dtw[k] = w.dtwT[k * Di + d];
+                const float dtb = w.dtb[d];
+                for (int r = 0; r < nb; ++r) dt_out[(base + r0 + r) * Di + d] = dt_of<RR>(dl_s + r * RR, dtw, dtb);
+            }
         }
     }
 }
 
-// k_scan: one thread per (lane, channel) walks the tile's rows in order:
-// dt_proj + softplus, the scan update and the gate.  h stays in registers;
-// the lane's conv state is advanced to the last three inputs of the tile.
-template <int RR>
-__global__ __launch_bounds__(256) void k_scan(LayerDev w, const float* __restrict__ xz,
-                                              const float* __restrict__ xs, const float* __restrict__ dbc,
-                                              int lanes, int T, int Di, const int* __restrict__ row_pos,
-                                              float* __restrict__ conv_state, float* __restrict__ hstate,
-                                              float* __restrict__ g) {
-    constexpr int NO = RR + 2 * NSTATE;
-    const int lane = blockIdx.y;
-    const int d = blockIdx.x * 256 + threadIdx.x;
-    if (d >= Di) return;
+// k_scan: one thread per (lane, channel).  The rows' delta, B and C are the
+// same for a whole wave; each wave keeps those of its RB rows in LDS of its
+// own (no barrier; broadcast reads), loaded one block ahead like x and z.  (The
+// scalar cache would serve them too, but every row is a miss there, and the
+// scalar registers hold only one row.)  Bound by VALU issue, about 130
+// instructions and 23 transcendentals per row and wave.  Blocks of RB rows
+// without a chunk start or an idle row (the common case) run a copy without the
+// per-row checks.  131072 rows on 4096 lanes, d_inner
+// 512: 301 us (scalar-cache form 412 us, one workgroup per lane doing conv,
+// x_proj and scan in phases 623 us); on 256 lanes 335 us (614, 546).
+template <int Di, int RR, bool G16>
+__global__ __launch_bounds__(Di < 256 ? Di : 256) void k_scan(LayerDev w, const float* __restrict__ xz,
+                                                              const float* __restrict__ dbc, int T,
+                                                              const int* __restrict__ row_pos,
+                                                              float* __restrict__ conv_state,
+                                                              float* __restrict__ hstate, float* __restrict__ g) {
+    constexpr int NO = RR + 2 * NSTATE, RB = 8;
+    constexpr int ND = (RB * NO + 63) / 64;      // dbc values per thread and block
+    __shared__ __align__(16) float dbc_s[4][RB * NO];
+    const int wl = threadIdx.x & 63;
+    float* dbw = dbc_s[threadIdx.x >> 6];
+    const int lane = blockIdx.x;
+    const int d = blockIdx.y * blockDim.x + threadIdx.x;
     const long long base = (long long)lane * T;
-    float A2[NSTATE], h[NSTATE], dtw[RR];
+    float cw[KCONV], A2[NSTATE], h[NSTATE], dtw[RR], win[KCONV - 1];
     float* hst = hstate + (long long)lane * NSTATE * Di;
+    float* cst = conv_state + (long long)lane * (KCONV - 1) * Di;
+#pragma unroll
+    for (int k = 0; k < KCONV; ++k) cw[k] = w.convT[k * Di + d];
+#pragma unroll
+    for (int k = 0; k < KCONV - 1; ++k) win[k] = cst[k * Di + d];
 #pragma unroll
     for (int n = 0; n < NSTATE; ++n) { A2[n] = w.A2T[n * Di + d]; h[n] = hst[n * Di + d]; }
 #pragma unroll
     for (int k = 0; k < RR; ++k) dtw[k] = w.dtwT[k * Di + d];
-    const float Dk = w.Dsk[d], dtb = w.dtb[d];
-    bool touched = false;
-    for (int t = 0; t < T; ++t) {
-        const long long row = base + t;
-        const int pos = row_pos[row];
+    const float cb = w.conv_b[d], Dk = w.Dsk[d], dtb = w.dtb[d];
+    const float* xr = xz + base * (2 * Di) + d;
+    float xn[RB], zn[RB], dn[ND];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const bool in = t0 + r < T;
+            xn[r] = in ? xr[(long long)(t0 + r) * (2 * Di)] : 0.0f;
+            zn[r] = in ? xr[(long long)(t0 + r) * (2 * Di) + Di] : 0.0f;
+        }
+        const int left = (T - t0) * NO;
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int e = wl + 64 * i;
+            dn[i] = e < RB * NO && e < left ? dbc[(base + t0) * NO + e] : 0.0f;
+        }
+    };
+    auto row = [&](int t, const float* dr, float x, float z) {
+        const float xs = conv_silu(cw, cb, win[0], win[1], win[2], x);
+        win[0] = win[1];
+        win[1] = win[2];
+        win[2] = x;
+        const float dt = dt_of<RR>(dr, dtw, dtb);
+        const float gv = scan_update(h, dt, xs, dr + RR, dr + RR + NSTATE, A2, Dk, z);
+        if (G16) reinterpret_cast<uint16_t*>(g)[(base + t) * Di + d] = f2bf_bits(gv);
+        else g[(base + t) * Di + d] = gv;
+    };
+    fetch(0);
+    for (int t0 = 0; t0 < T; t0 += RB) {
+        float xv[RB], zv[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) { xv[r] = xn[r]; zv[r] = zn[r]; }
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+            if (wl + 64 * i < RB * NO) dbw[wl + 64 * i] = dn[i];
+        __builtin_amdgcn_wave_barrier();         // the wave's LDS accesses complete in order
+        fetch(t0 + RB);
+        int least = t0 + RB <= T ? 1 : 0;
+        if (least) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const int p = row_pos[base + t0 + r];
+                least = p < least ? p : least;
+            }
+        }
+        if (least > 0) {                             // whole block inside one chunk
+#pragma unroll
+            for (int r = 0; r < RB; ++r) row(t0 + r, dbw + r * NO, xv[r], zv[r]);
+        } else {
+#pragma unroll 1
+            for (int r = 0; r < RB; ++r) {
+                const int pos = t0 + r < T ? row_pos[base + t0 + r] : -1;
+                if (pos < 0) continue;
+                if (pos == 0) {
+#pragma unroll
+                    for (int n = 0; n < NSTATE; ++n) h[n] = 0.0f;
+                    win[0] = 0.0f; win[1] = 0.0f; win[2] = 0.0f;
+                }
+                float x = xv[0], z = zv[0];
+#pragma unroll
+                for (int q = 1; q < RB; ++q)
+                    if (q == r) { x = xv[q]; z = zv[q]; }
+                row(t0 + r, dbw + r * NO, x, z);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int n = 0; n < NSTATE; ++n) hst[n * Di + d] = h[n];
+#pragma unroll
+    for (int k = 0; k < KCONV - 1; ++k) cst[k * Di + d] = win[k];
+}
+
+// k_scan_states (few lanes): the recurrence alone, one thread per (channel,
+// state): wave w of workgroup (channel block, state group) owns state
+// 4 (blockIdx.x % 4) + w.  dt, x and B of 64 rows are staged in LDS while the
+// previous rows are walked; groups of eight rows form their exponentials and
+// inputs first, then the chain of one fused multiply-add per row runs.  The
+// state before every RB-th row goes to hsub.  A chunk start zeroes h; idle rows
+// have dt = x = 0, which leave it as it is.
+constexpr int SCAN_RB = 16;                      // rows between kept states (and per k_scan_rows block)
+template <int Di, int RR>
+__global__ __launch_bounds__(256) void k_scan_states(LayerDev w, const float* __restrict__ xs,
+                                                     const float* __restrict__ dt, const float* __restrict__ dbc, int T,
+                                                     const int* __restrict__ row_pos, float* __restrict__ hstate,
+                                                     float* __restrict__ hsub) {
+    constexpr int NO = RR + 2 * NSTATE, SB = 64;
+    __shared__ float dt_s[SB][64], x_s[SB][64], b_s[SB][4];
+    __shared__ int start_s[SB / 8];              // per group of eight rows: bit r set when row r starts a chunk
+    const int tid = threadIdx.x, wl = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = blockIdx.y, d = (blockIdx.x >> 2) * 64 + wl, n = (blockIdx.x & 3) * 4 + wv;
+    const long long base = (long long)lane * T;
+    const int nslot = (T + SCAN_RB - 1) / SCAN_RB;
+    const float A2 = w.A2T[n * Di + d];
+    float* hp = hstate + ((long long)lane * NSTATE + n) * Di + d;
+    float h = *hp;
+    float rd[SB / 4], rx[SB / 4], rb = 0.0f;
+    int rp = -1;
+    auto fetch = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < SB / 4; ++i) {
+            const int t = s0 + wv + 4 * i;
+            const bool in = t < T && row_pos[base + t] >= 0;
+            rd[i] = in ? dt[(base + t) * Di + d] : 0.0f;
+            rx[i] = in ? xs[(base + t) * Di + d] : 0.0f;
+        }
+        const int t = s0 + (tid >> 2);
+        rb = t < T && row_pos[base + t] >= 0 ? dbc[(base + t) * NO + RR + (blockIdx.x & 3) * 4 + (tid & 3)] : 0.0f;
+        rp = tid < SB && s0 + tid < T ? row_pos[base + s0 + tid] : -1;
+    };
+    fetch(0);
+    for (int s0 = 0; s0 < T; s0 += SB) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SB / 4; ++i) { dt_s[wv + 4 * i][wl] = rd[i]; x_s[wv + 4 * i][wl] = rx[i]; }
+        b_s[tid >> 2][tid & 3] = rb;
+        if (wv == 0) {
+            const unsigned long long m = __ballot(rp == 0);
+            if (wl < SB / 8) start_s[wl] = (int)((m >> (8 * wl)) & 0xFF);
+        }
+        __syncthreads();
+        fetch(s0 + SB);
+#pragma unroll 1
+        for (int t8 = 0; t8 < SB && s0 + t8 < T; t8 += 8) {
+            float a[8], u[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float dtv = dt_s[t8 + j][wl], x = x_s[t8 + j][wl];
+                a[j] = exp2_hw(dtv * A2);
+                u[j] = (dtv * x) * b_s[t8 + j][wv];
+            }
+            if ((s0 + t8) % SCAN_RB == 0)
+                hsub[(((long long)lane * nslot + (s0 + t8) / SCAN_RB) * NSTATE + n) * Di + d] = h;
+            const int starts = __builtin_amdgcn_readfirstlane(start_s[t8 / 8]);
+            if (starts == 0) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) h = fmaf(a[j], h, u[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (starts >> j & 1) h = 0.0f;
+                    h = fmaf(a[j], h, u[j]);
+                }
+            }
+        }
+    }
+    *hp = h;
+}
+
+// k_scan_rows (few lanes): the outputs of SCAN_RB rows from the state before
+// them, one thread per (lane, block of rows, channel).  The last block also
+// advances the lane's conv state.
+template <int Di, int RR, bool G16>
+__global__ __launch_bounds__(Di < 256 ? Di : 256) void k_scan_rows(LayerDev w, const float* __restrict__ xz,
+                                                                   const float* __restrict__ xs,
+                                                                   const float* __restrict__ dt,
+                                                                   const float* __restrict__ dbc, int T,
+                                                                   const int* __restrict__ row_pos,
+                                                                   const float* __restrict__ hsub,
+                                                                   float* __restrict__ conv_state,
+                                                                   float* __restrict__ g) {
+    constexpr int NO = RR + 2 * NSTATE;
+    const int lane = blockIdx.z, blk = blockIdx.y;
+    const int d = blockIdx.x * blockDim.x + threadIdx.x;
+    const long long base = (long long)lane * T;
+    const int t0 = blk * SCAN_RB, t1 = t0 + SCAN_RB < T ? t0 + SCAN_RB : T;
+    float A2[NSTATE], h[NSTATE];
+    const float* hs = hsub + ((long long)lane * gridDim.y + blk) * NSTATE * Di + d;
+#pragma unroll
+    for (int n = 0; n < NSTATE; ++n) { A2[n] = w.A2T[n * Di + d]; h[n] = hs[n * Di]; }
+    const float Dk = w.Dsk[d];
+    float xv[SCAN_RB], dv[SCAN_RB], zv[SCAN_RB];
+#pragma unroll
+    for (int r = 0; r < SCAN_RB; ++r) {
+        const bool in = t0 + r < t1;
+        const long long at = base + t0 + r;
+        xv[r] = in ? xs[at * Di + d] : 0.0f;
+        dv[r] = in ? dt[at * Di + d] : 0.0f;
+        zv[r] = in ? xz[at * (2 * Di) + Di + d] : 0.0f;
+    }
+#pragma unroll
+    for (int r = 0; r < SCAN_RB; ++r) {
+        const int pos = t0 + r < t1 ? row_pos[base + t0 + r] : -1;
         if (pos < 0) continue;
-        touched = true;
         if (pos == 0) {
 #pragma unroll
             for (int n = 0; n < NSTATE; ++n) h[n] = 0.0f;
         }
-        const float* dr = dbc + row * NO;
-        float dl[NO];
-#pragma unroll
-        for (int k = 0; k < NO; ++k) dl[k] = dr[k];
-        const float dt = dt_of<RR>(dl, dtw, dtb);
-        g[row * Di + d] = scan_update(h, dt, xs[row * Di + d], dl + RR, dl + RR + NSTATE, A2, Dk,
-                                      xz[row * (2 * Di) + Di + d]);
+        const float* dr = dbc + (base + t0 + r) * NO;
+        const float gv = scan_update(h, dv[r], xv[r], dr + RR, dr + RR + NSTATE, A2, Dk, zv[r]);
+        if (G16) reinterpret_cast<uint16_t*>(g)[(base + t0 + r) * Di + d] = f2bf_bits(gv);
+        else g[(base + t0 + r) * Di + d] = gv;
     }
-    if (touched) {
+    if (t1 == T) {                               // conv state <- inputs at T - 3, T - 2, T - 1 of this tile
+        float* cst = conv_state + (long long)lane * (KCONV - 1) * Di;
+        float old[KCONV - 1];
 #pragma unroll
-        for (int n = 0; n < NSTATE; ++n) hst[n * Di + d] = h[n];
-    }
-    // conv state <- inputs at offsets T-3, T-2, T-1 of this tile
-    float* cst = conv_state + (long long)lane * (KCONV - 1) * Di;
-    float old[KCONV - 1];
+        for (int k = 0; k < KCONV - 1; ++k) old[k] = cst[k * Di + d];
 #pragma unroll
-    for (int k = 0; k < KCONV - 1; ++k) old[k] = cst[k * Di + d];
-#pragma unroll
-    for (int k = 0; k < KCONV - 1; ++k) {
-        int idx = T - (KCONV - 1) + k;
-        cst[k * Di + d] = idx >= 0 ? xz[(base + idx) * (2 * Di) + d] : old[T + k];
+        for (int k = 0; k < KCONV - 1; ++k) {
+            const int idx = T - (KCONV - 1) + k;
+            // T + k < 3 whenever idx < 0
+            cst[k * Di + d] = idx >= 0 ? xz[(base + idx) * (2 * Di) + d] : (T + k == 1 ? old[1] : old[2]);
+        }
     }
 }
 
-// Encoder mixer in one pass (d_inner <= 512): one workgroup per lane runs the
-// tile's rows of that lane in blocks of 16 -- conv + SiLU, x_proj, dt_proj +
-// softplus, scan and gate -- with everything between the phases in LDS.
-// Thread d owns channel d: its conv window, scan state h and conv / dt / scan
-// weights stay in registers for the whole tile.  x_proj runs on the matrix
-// cores: wave f < NF computes column fragment f of the block's 16 rows
-// (xproj_fragment).  Same per-element functions, operands and orders as
-// the decoder kernels; the window restarts at a chunk start (pos 0) exactly
-// like the zero padding before a chunk.
-template <int Di, int RR, bool G16>
-__global__ __launch_bounds__(512) void k_mixer_enc(LayerDev w, const float* __restrict__ xz, int lanes, int T,
-                                                   const int* __restrict__ row_pos, float* __restrict__ conv_state,
-                                                   float* __restrict__ hstate, float* __restrict__ g) {
-    constexpr int NT = 512, RB = 16;
-    constexpr int NO = RR + 2 * NSTATE, XSR = Di + 4;     // row stride of xs in LDS: rows 4 banks apart
-    constexpr int NF = (NO + 15) / 16;                    // x_proj column fragments
-    static_assert(Di <= NT && NF <= NT / 64 && Di % 16 == 0, "one channel per thread, one fragment per wave");
-    __shared__ __align__(16) float xs_s[RB * XSR];
-    __shared__ float dbc_s[RB * NO];
-    __shared__ int pos_s[RB], start_s;
-    const int tid = threadIdx.x;
-    const int lane = blockIdx.x;
-    if (lane >= lanes) return;
-    const long long base = (long long)lane * T;
-    const bool ch = tid < Di;
-    const int d = tid;
-    float* cst = conv_state + (long long)lane * (KCONV - 1) * Di;
-    float* hst = hstate + (long long)lane * NSTATE * Di;
-
-    float cw[KCONV], cb = 0.0f, dtw[RR], dtb = 0.0f, A2[NSTATE], Dk = 0.0f, h[NSTATE], win[KCONV - 1];
-    if (ch) {
-#pragma unroll
-        for (int k = 0; k < KCONV; ++k) cw[k] = w.convT[k * Di + d];
-        cb = w.conv_b[d];
-#pragma unroll
-        for (int k = 0; k < RR; ++k) dtw[k] = w.dtwT[k * Di + d];
-        dtb = w.dtb[d];
-#pragma unroll
-        for (int n = 0; n < NSTATE; ++n) { A2[n] = w.A2T[n * Di + d]; h[n] = hst[n * Di + d]; }
-        Dk = w.Dsk[d];
-#pragma unroll
-        for (int k = 0; k < KCONV - 1; ++k) win[k] = cst[k * Di + d];
-    }
-    const int wv = tid >> 6, wl = tid & 63, li = wl & 15, lk = wl >> 4;
-
-    for (int t0 = 0; t0 < T; t0 += RB) {
-        const int nb = T - t0 < RB ? T - t0 : RB;
-        float xv[RB], zv[RB];
-        if (ch) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                if (r < nb) {
-                    const float* row = xz + (base + t0 + r) * (2 * Di);
-                    xv[r] = row[d];
-                    zv[r] = row[Di + d];
-                }
-            }
-        }
-        __syncthreads();                       // the previous block's readers are done
-        if (tid < 64) {                        // wave 0: the rows' positions, and whether a chunk starts here
-            const int p = tid < nb && tid < RB ? row_pos[base + t0 + tid] : -1;
-            if (tid < RB) pos_s[tid] = p;
-            const bool any0 = __ballot(p == 0) != 0;
-            if (tid == 0) start_s = any0 ? 1 : 0;
-        }
-        __syncthreads();
-        const int starts = start_s;
-        // conv + SiLU
-        if (ch) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const int pos = pos_s[r];
-                if (pos < 0) continue;
-                if (starts && pos == 0) { win[0] = 0.0f; win[1] = 0.0f; win[2] = 0.0f; }
-                const float x = xv[r];
-                xs_s[r * XSR + d] = conv_silu(cw, cb, win[0], win[1], win[2], x);
-                win[0] = win[1];
-                win[1] = win[2];
-                win[2] = x;
-            }
-        }
-        __syncthreads();
-        // x_proj (rows of idle slots compute stale values and are not used)
-        if (wv < NF) {
-            v4f acc;
-            xproj_fragment<Di>(xs_s, XSR, RB, w.xwF, wv, wl, acc);
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int row = 4 * lk + rr, col = 16 * wv + li;
-                if (row < nb && col < NO) dbc_s[row * NO + col] = acc[rr];
-            }
-        }
-        __syncthreads();
-        // dt_proj + softplus, scan, gate.  A block without a chunk start (the
-        // common case) runs a copy of the loop without the state reset, which
-        // the compiler would otherwise turn into per-row selects.
-        auto scan_rows = [&](auto reset) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const int pos = pos_s[r];
-                if (pos < 0) continue;
-                if (decltype(reset)::value && pos == 0) {
-#pragma unroll
-                    for (int n = 0; n < NSTATE; ++n) h[n] = 0.0f;
-                }
-                const float* db = dbc_s + r * NO;
-                const float dt = dt_of<RR>(db, dtw, dtb);
-                const float xs = xs_s[r * XSR + d];
-                const float gv = scan_update(h, dt, xs, db + RR, db + RR + NSTATE, A2, Dk, zv[r]);
-                if (G16) reinterpret_cast<uint16_t*>(g)[(base + t0 + r) * Di + d] = f2bf_bits(gv);
-                else g[(base + t0 + r) * Di + d] = gv;
-            }
-        };
-        if (ch) {
-            if (__builtin_amdgcn_readfirstlane(starts)) scan_rows(std::true_type{});
-            else scan_rows(std::false_type{});
-        }
-    }
-    if (ch) {
-#pragma unroll
-        for (int n = 0; n < NSTATE; ++n) hst[n * Di + d] = h[n];
-#pragma unroll
-        for (int k = 0; k < KCONV - 1; ++k) cst[k * Di + d] = win[k];
-    }
+// One thread per (lane, channel) fills the GPU with two waves per SIMD from
+// 2048 waves on; below MIXER_FEW waves the blocks of rows run side by side.
+// One 4096-step stream, d_inner 512: k_scan_states 275 us + k_scan_rows 21 us,
+// where a workgroup walking the lane took 3905 us; 256 lanes have enough waves
+// for k_scan, which computes each exponential once.
+constexpr int MIXER_FEW = 1024;
+bool mixer_few(int Di, int lanes) { return (long long)lanes * Di / 64 < MIXER_FEW; }
+size_t mixer_hsub_floats(int Di, int lanes, int T) {
+    return (size_t)lanes * ((T + SCAN_RB - 1) / SCAN_RB) * NSTATE * Di;
 }
 
 hipError_t launch_mid_tiled(const LayerDev& w, int Di, int R, const float* xz, float* xs, float* dbc, float* dt,
-                            float* g, int lanes, int T, const int* row_pos, float* conv_state, float* hstate,
-                            bool g_bf16, hipStream_t s) {
-    (void)dt;
-    dim3 g1((T + 15) / 16, lanes), g2((Di + 255) / 256, lanes);
-#define CX_CASE(DI, RV) \
-    if (Di == DI && R == RV) { \
-        if (g_bf16) return hipErrorInvalidValue; \
-        BOA_LAUNCH((k_convx<DI, RV>), g1, dim3(256), 0, s, w, xz, lanes, T, row_pos, conv_state, xs, dbc); \
-        hipError_t e = hipGetLastError(); \
-        if (e != hipSuccess) return e; \
-        BOA_LAUNCH((k_scan<RV>), g2, dim3(256), 0, s, w, xz, xs, dbc, lanes, T, Di, row_pos, conv_state, \
-                           hstate, g); \
-        return hipGetLastError(); }
-#define MX_CASE(DI, RV) \
-    if (Di == DI && R == RV) { \
-        if (g_bf16) \
-            BOA_LAUNCH((k_mixer_enc<DI, RV, true>), dim3(lanes), dim3(512), 0, s, w, xz, lanes, T, row_pos, \
-                       conv_state, hstate, g); \
-        else \
-            BOA_LAUNCH((k_mixer_enc<DI, RV, false>), dim3(lanes), dim3(512), 0, s, w, xz, lanes, T, row_pos, \
-                       conv_state, hstate, g); \
-        return hipGetLastError(); }
-    MX_CASE(128, 4) MX_CASE(256, 8) MX_CASE(512, 16)
-    CX_CASE(1024, 32)
+                            float* hsub, float* g, int lanes, int T, const int* row_pos, float* conv_state,
+                            float* hstate, bool g_bf16, hipStream_t s) {
+    const dim3 g1(lanes, (T + 15) / 16);
+    const int nt = Di < 256 ? Di : 256;
+#define MX_CASE(DI, RV)                                                                                             \
+    if (Di == DI && R == RV) {                                                                                      \
+        if (mixer_few(Di, lanes)) {                                                                                 \
+            BOA_LAUNCH((k_convx<DI, RV, true>), g1, dim3(256), 0, s, w, xz, T, row_pos, conv_state, dbc, xs, dt);   \
+            BOA_LAUNCH((k_scan_states<DI, RV>), dim3(DI / 64 * 4, lanes), dim3(256), 0, s, w, xs, dt, dbc, T,       \
+                       row_pos, hstate, hsub);                                                                      \
+            const dim3 g3(DI / nt, (T + SCAN_RB - 1) / SCAN_RB, lanes);                                             \
+            if (g_bf16)                                                                                             \
+                BOA_LAUNCH((k_scan_rows<DI, RV, true>), g3, dim3(nt), 0, s, w, xz, xs, dt, dbc, T, row_pos, hsub,   \
+                           conv_state, g);                                                                          \
+            else                                                                                                    \
+                BOA_LAUNCH((k_scan_rows<DI, RV, false>), g3, dim3(nt), 0, s, w, xz, xs, dt, dbc, T, row_pos, hsub,  \
+                           conv_state, g);                                                                          \
+        } else {                                                                                                    \
+            BOA_LAUNCH((k_convx<DI, RV, false>), g1, dim3(256), 0, s, w, xz, T, row_pos, conv_state, dbc,           \
+                       (float*)nullptr, (float*)nullptr);                                                           \
+            if (g_bf16)                                                                                             \
+                BOA_LAUNCH((k_scan<DI, RV, true>), dim3(lanes, DI / nt), dim3(nt), 0, s, w, xz, dbc, T, row_pos,    \
+                           conv_state, hstate, g);                                                                  \
+            else                                                                                                    \
+                BOA_LAUNCH((k_scan<DI, RV, false>), dim3(lanes, DI / nt), dim3(nt), 0, s, w, xz, dbc, T, row_pos,   \
+                           conv_state, hstate, g);                                                                  \
+        }                                                                                                           \
+        return hipGetLastError();                                                                                   \
+    }
+    MX_CASE(128, 4) MX_CASE(256, 8) MX_CASE(512, 16) MX_CASE(1024, 32)
 #undef MX_CASE
-#undef CX_CASE
     return hipErrorInvalidValue;
 }
 

@@ -580,7 +580,7 @@ int upload_plan(const HostPlan& P, const std::vector<long long>& off, const std:
 
 // Per-call activation and state buffers for `lanes` lanes and tiles of T rows.
 struct Work {
-    DevBuf r, xz, g, logits, cf, row_chunk, row_pos, conv, h, coder, step, xs, dbc, dt;
+    DevBuf r, xz, g, logits, cf, row_chunk, row_pos, conv, h, coder, step, xs, dbc, dt, hsub;
     DevBuf fh, ff;     // feed-forward hidden [M, H] and output [M, D]
     int lanes = 0, T = 0;
     Arena own_arena;
@@ -594,9 +594,13 @@ struct Work {
         r.carve(A, M * L.D * 4);
         xz.carve(A, M * 2 * L.Di * 4);
         g.carve(A, M * L.Di * 4);
-        if (T > 1 && L.Di > 512) {             // the two-kernel mixer's intermediates
-            xs.carve(A, M * L.Di * 4);
+        if (T > 1) {                           // the mixer's intermediates
             dbc.carve(A, M * (L.R + 2 * L.N) * 4);
+            if (mixer_few(L.Di, lanes)) {
+                xs.carve(A, M * L.Di * 4);
+                dt.carve(A, M * L.Di * 4);
+                hsub.carve(A, mixer_hsub_floats(L.Di, lanes, T) * 4);
+            }
         }
         logits.carve(A, M * 256 * 4);
         cf.carve(A, M * 2 * 4);
@@ -651,9 +655,9 @@ int forward_tile(const boa_model* m, Work& W, int dtype, const uint8_t* bytes, c
     auto frag = [&](const float* f32, const uint16_t* h16, const uint8_t* f8) {
         return dtype == BOA_DTYPE_FP8 ? (const void*)f8 : dtype == BOA_DTYPE_BF16 ? (const void*)h16 : (const void*)f32;
     };
-    // BF16 encoder tiles: the one-pass mixer writes the gated rows as the bf16
-    // bits the out_proj stages anyway (half the bytes both ways)
-    const bool g16 = dtype == BOA_DTYPE_BF16 && rows_big && W.T > 1 && L.Di <= 512;
+    // BF16 encoder tiles: the mixer writes the gated rows as the bf16 bits the
+    // out_proj stages anyway (half the bytes both ways)
+    const bool g16 = dtype == BOA_DTYPE_BF16 && rows_big && W.T > 1;
     for (int l = 0; l < L.L; ++l) {
         const LayerDev& w = m->ld[l];
         // the mixer reads the x_proj / dt_proj weights of the dtype's numerics
@@ -674,8 +678,8 @@ int forward_tile(const boa_model* m, Work& W, int dtype, const uint8_t* bytes, c
             ProfScope ps(BOA_K_MIXER, s);
             if (W.T > 1)
                 HIPCHK(launch_mid_tiled(wm, L.Di, L.R, W.xz.as<float>(), W.xs.as<float>(), W.dbc.as<float>(),
-                                        W.dt.as<float>(), W.g.as<float>(), W.lanes, W.T, W.row_pos.as<int>(), conv,
-                                        h, g16, s));
+                                        W.dt.as<float>(), W.hsub.as<float>(), W.g.as<float>(), W.lanes, W.T,
+                                        W.row_pos.as<int>(), conv, h, g16, s));
             else
                 HIPCHK(launch_mid(wm, L.Di, L.R, W.xz.as<float>(), W.g.as<float>(), W.lanes, W.T, lpw,
                                   W.row_pos.as<int>(), conv, h, s));
