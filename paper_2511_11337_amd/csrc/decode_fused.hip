@@ -275,9 +275,10 @@ struct FGemm {
             for (int j = 0; j < FPW; ++j) ring[u][j] = ld(r, f0, u, j, wl);
     }
     // the pass over fragments f0, f0 + 8, ... whose first ring is in flight
+    // (f1 >= 0: the ring goes on with the first loads of the pass at f1)
     template <class Epi>
     DEVI void pass(const float* __restrict__ A, int as, const void* __restrict__ Wf, const unsigned* amax_rows,
-                   int ew, int wl, int f0, Epi& epi) {
+                   int ew, int wl, int f0, int f1, Epi& epi) {
         const int li = wl & 15, lk = wl >> 4;
         const bool arow = li < G;
         const __amdgpu_buffer_rsrc_t rs = rsrc(Wf);
@@ -297,6 +298,9 @@ struct FGemm {
                 if (st + P < SK) {
 #pragma unroll
                     for (int j = 0; j < FPW; ++j) ring[u][j] = ld(rs, f0, st + P, j, wl);
+                } else if (f1 >= 0) {
+#pragma unroll
+                    for (int j = 0; j < FPW; ++j) ring[u][j] = ld(rs, f1, u, j, wl);
                 }
                 if (DT == 0) {
                     float av[4];
@@ -367,16 +371,13 @@ struct FGemm {
     DEVI void run(const float* __restrict__ A, int as, const void* __restrict__ Wf, int wl, int wv,
                   const unsigned* amax_rows, const int* ewp, Epi&& epi) {
         const int ew = DT == 2 ? *ewp : 0;
-        pass(A, as, Wf, amax_rows, ew, wl, wv, epi);
 #pragma unroll 1
-        for (int f = FPW; f < FALL; f += FPW) {
-            issue(Wf, wv + FNW * f, wl);
-            pass(A, as, Wf, amax_rows, ew, wl, wv + FNW * f, epi);
-        }
+        for (int f = 0; f < FALL; f += FPW)
+            pass(A, as, Wf, amax_rows, ew, wl, wv + FNW * f, f + FPW < FALL ? wv + FNW * (f + FPW) : -1, epi);
     }
 };
 
-// f(j, rr, row, n, v) for every output of a pass that this lane holds
+// f(row, n, v) for every output of a pass that this lane holds
 template <int FPW, int G, int NF, class F>
 DEVI void for_outputs(const v4f (&acc)[FPW], int f0, int wl, F&& f) {
     const int li = wl & 15, lk = wl >> 4;
@@ -387,73 +388,213 @@ DEVI void for_outputs(const v4f (&acc)[FPW], int f0, int wl, F&& f) {
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
             const int row = 4 * lk + rr;
-            if (row < G) f(j, rr, row, 16 * nf + li, acc[j][rr]);
+            if (row < G) f(row, 16 * nf + li, acc[j][rr]);
         }
     }
 }
 
-// LayerNorm of the G residual rows into a_s.  Element i = tid + 512 m is
-// normalised by its thread; the 64 elements of a wave lie in one row (D is a
-// multiple of 64), and the wave takes that row's statistics itself
-// (ln_stats_v: every wave that reads a row gets the same values), so no
-// barrier separates statistics from normalisation.  With G * D <= 512 the
-// caller loads each thread's LayerNorm weight and bias early (LnPre).
-template <int D, int G>
+// LayerNorm of the G residual rows into a_s.  With G >= 8 a wave takes whole
+// rows (w, w + 8); with fewer rows the waves share them, wave w normalising the
+// 64 elements 64 w % D .. of row 64 w / D (512 elements a pass) after taking
+// that row's statistics itself: every wave that reads a row gets the same
+// values (ln_stats_v), so no barrier separates statistics from normalisation.
+// Either way a thread's elements lie in the same columns of every row (D
+// divides 512), so it loads their weights and biases once, ahead of the phase.
+template <int D, int G, bool F8>
 struct LnPre {
-    static constexpr bool ONE = G * D <= FNT;
-    float w = 0.0f, b = 0.0f;
-    DEVI void load(const float* lw, const float* lb, int tid) {
-        if (ONE && tid < G * D) { w = gld(lw + tid % D); b = gld(lb + tid % D); }
+    static constexpr int NV = D / 64;
+    static constexpr int NE = G >= FNW || F8 ? NV : 1;   // fp8: every wave needs the whole row's maximum
+    float w[NE], b[NE];
+    DEVI void load(const float* lw, const float* lb, int wl, int wv) {
+        if (G < FNW && 64 * wv >= G * D) return;
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            const int k = NE == 1 ? (64 * wv) % D + wl : 64 * j + wl;
+            w[j] = gld(lw + k);
+            b[j] = gld(lb + k);
+        }
     }
 };
-// With amax_s (fp8), the first wave of each row also takes the row's largest
-// normalised magnitude (the same ln_apply values as the normalisation).
 // B16: the normalised rows are stored rounded to bf16 (the GEMM's A operand
 // in bf16 mode), row stride 2 * ds halves.
-// F8: every wave takes the row's largest normalised magnitude itself and
-// stores its elements as E4M3 bytes scaled by 2^-ea (row stride 4 * ds bytes),
-// the A operand of the fp8 GEMM.
+// F8: the row's largest normalised magnitude goes to amax_s and the elements
+// are stored as E4M3 bytes scaled by 2^-ea (row stride 4 * ds bytes), the A
+// operand of the fp8 GEMM.
 template <int D, int G, bool B16 = false, bool F8 = false>
-DEVI void fused_ln(const float* __restrict__ r_s, float* __restrict__ a_s, int ds, const float* __restrict__ lw,
-                   const float* __restrict__ lb, const LnPre<D, G>& pre, int wl, int wv, unsigned* amax_s = nullptr) {
+DEVI void fused_ln(const float* __restrict__ r_s, float* __restrict__ a_s, int ds, const LnPre<D, G, F8>& pre, int wl,
+                   int wv, unsigned* amax_s = nullptr) {
     constexpr int NV = D / 64;
-    static_assert(D % 64 == 0, "rows of whole waves");
-#pragma unroll 1
-    for (int i0 = 64 * wv; i0 < G * D; i0 += FNT) {      // wave-uniform
-        const int row = i0 / D, kw = i0 % D;
-        float v[NV];
-#pragma unroll
-        for (int j = 0; j < NV; ++j) v[j] = r_s[row * D + wl + 64 * j];
-        float mu, rs;
-        ln_stats_v<NV>(v, D, mu, rs);
-        float am = 0.0f;
-        if (amax_s && (F8 || kw == 0)) {
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-                am = fmaxf(am, fabsf(ln_apply(v[j], mu, rs, gld(lw + wl + 64 * j), gld(lb + wl + 64 * j))));
-            am = wave_max(am);
-            if (kw == 0 && wl == 0) amax_s[row] = __float_as_uint(am);
-        }
-        const int k = kw + wl;
-        float x = 0.0f;
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-            if (64 * j == kw) x = v[j];
-        const float g = LnPre<D, G>::ONE ? pre.w : gld(lw + k);
-        const float bb = LnPre<D, G>::ONE ? pre.b : gld(lb + k);
-        const float y = ln_apply(x, mu, rs, g, bb);
+    static_assert(D % 64 == 0 && FNT % D == 0, "rows of whole waves, fixed columns per thread");
+    auto put = [&](int row, int k, float y, float am) {
         if (F8) reinterpret_cast<uint8_t*>(a_s)[row * 4 * ds + k] = fp8_byte(ldexpf(y, -fp8_exp(am)));
         else if (B16) reinterpret_cast<uint16_t*>(a_s)[row * 2 * ds + k] = f2bf_bits(y);
         else a_s[row * ds + k] = y;
+    };
+    if constexpr (G >= FNW) {
+        float v[G / FNW][NV];
+#pragma unroll
+        for (int q = 0; q < G / FNW; ++q)
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[q][j] = r_s[(wv + FNW * q) * D + wl + 64 * j];
+#pragma unroll
+        for (int q = 0; q < G / FNW; ++q) {
+            const int row = wv + FNW * q;
+            float mu, rs, am = 0.0f;
+            ln_stats_v<NV>(v[q], D, mu, rs);
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                v[q][j] = ln_apply(v[q][j], mu, rs, pre.w[j], pre.b[j]);
+                if (F8) am = fmaxf(am, fabsf(v[q][j]));
+            }
+            if (F8) {
+                am = wave_max(am);
+                if (wl == 0) amax_s[row] = __float_as_uint(am);
+            }
+#pragma unroll
+            for (int j = 0; j < NV; ++j) put(row, 64 * j + wl, v[q][j], am);
+        }
+    } else {
+#pragma unroll
+        for (int i1 = 0; i1 < G * D; i1 += FNT) {
+            const int i0 = i1 + 64 * wv;                     // wave-uniform
+            if (i0 >= G * D) break;
+            const int row = i0 / D, kw = (64 * wv) % D;
+            float v[NV];
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[j] = r_s[row * D + wl + 64 * j];
+            float mu, rs, am = 0.0f;
+            ln_stats_v<NV>(v, D, mu, rs);
+            if (F8) {
+#pragma unroll
+                for (int j = 0; j < NV; ++j) am = fmaxf(am, fabsf(ln_apply(v[j], mu, rs, pre.w[F8 ? j : 0], pre.b[F8 ? j : 0])));
+                am = wave_max(am);
+                if (kw == 0 && wl == 0) amax_s[row] = __float_as_uint(am);
+            }
+            float x = 0.0f, g = pre.w[0], bb = pre.b[0];
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                if (64 * j == kw) {
+                    x = v[j];
+                    if (F8) { g = pre.w[F8 ? j : 0]; bb = pre.b[F8 ? j : 0]; }
+                }
+            put(row, kw + wl, ln_apply(x, mu, rs, g, bb), am);
+        }
     }
     __syncthreads();
 }
+
+// x_proj of the G rows of xs_s into dbc_s, the four chains per output of
+// xproj_fragment.  Left to one wave per column fragment, as the step kernels
+// have it, it was half of a step (48k of 97k cycles at one lane of d_model 256:
+// 128 dependent MFMAs behind a ring of four loads); both forms below start
+// their weight loads before the conv phase and use more of the waves.
+//
+// One or two rows: on the vector ALU.  The f32 16x16x4 MFMA adds its four
+// products one after another, each with a single rounding, exactly as fmaf in
+// increasing k does, so lane (c = lane / 16, lane % 16) of wave f + 4 r runs
+// chain c of output 16 f + lane % 16 of row r and the chains meet by lane
+// exchanges.  A matrix instruction spends the same time on 1 row
+// as on 16.  One lane of d_model 256: 6.8k cycles a step.
+template <int Di, int NFX, int NO, int G>
+struct XRows {
+    static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : 4;
+    static_assert(G <= 2 && NFX <= 4 && FNW == 8, "a wave per (fragment, row)");
+    f32x4 ring[PG][4];
+    DEVI static bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
+    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int lk) {
+        const int q = 4 * i + (wl >> 4);
+        return ((const __attribute__((address_space(1))) f32x4*)Wf)[((wv & 3) * SQ + q) * 64 + 16 * lk + (wl & 15)];
+    }
+    DEVI void issue(const float* Wf, int wv, int wl) {
+        if (!mine(wv)) return;
+#pragma unroll
+        for (int i = 0; i < PG; ++i)
+#pragma unroll
+            for (int lk = 0; lk < 4; ++lk) ring[i][lk] = ld(Wf, wv, wl, i, lk);
+    }
+    DEVI void run(const float* xs, int xsr, const float* Wf, int wv, int wl, float* dbc) {
+        if (!mine(wv)) return;
+        float acc = 0.0f;
+        const float* xrow = xs + (wv >> 2) * xsr + 16 * (wl >> 4);
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            f32x4 w[4];
+#pragma unroll
+            for (int lk = 0; lk < 4; ++lk) w[lk] = ring[i % PG][lk];
+            if (i + PG < NG) {
+#pragma unroll
+                for (int lk = 0; lk < 4; ++lk) ring[i % PG][lk] = ld(Wf, wv, wl, i + PG, lk);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 xv = *reinterpret_cast<const f32x4*>(xrow + 64 * i + 4 * j);
+#pragma unroll
+                for (int lk = 0; lk < 4; ++lk) acc = fmaf(xv[lk], w[lk][j], acc);
+            }
+        }
+        const int n = 16 * (wv & 3) + (wl & 15);
+        float v = acc + __shfl_xor(acc, 16);                 // chains 0 + 1, 2 + 3
+        v = v + __shfl_xor(v, 32);
+        if (wl < 16 && n < NO) dbc[(wv >> 2) * NO + n] = v;
+    }
+};
+// More rows: on the matrix cores, wave f + 4 h chains 2 h and 2 h + 1 of
+// column fragment f; the halves are added through part [2][G][16 NFX].  16
+// lanes of d_model 256: 45k cycles a step before, 20k so.
+template <int Di, int NFX, int NO, int G>
+struct XTile {
+    static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : 4, PN = 16 * NFX;
+    f32x4 ring[PG][2];
+    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {
+        return ((const __attribute__((address_space(1))) f32x4*)Wf)[((wv & 3) * SQ + 4 * i + 2 * (wv >> 2) + c) * 64 + wl];
+    }
+    DEVI void issue(const float* Wf, int wv, int wl) {
+        if ((wv & 3) >= NFX) return;
+#pragma unroll
+        for (int i = 0; i < PG; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) ring[i][c] = ld(Wf, wv, wl, i, c);
+    }
+    DEVI void run(const float* xs, int xsr, const float* Wf, int wv, int wl, int tid, float* part, float* dbc) {
+        if ((wv & 3) < NFX) {
+            const int li = wl & 15, lk = wl >> 4;
+            const float* x = xs + (li < G ? li : 0) * xsr + 32 * (wv >> 2) + lk;
+            v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                f32x4 w[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) w[c] = ring[i % PG][c];
+                if (i + PG < NG) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) ring[i % PG][c] = ld(Wf, wv, wl, i + PG, c);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)      // rows from G on: a copy of row 0, not stored
+                        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[64 * i + 16 * c + 4 * j], w[c][j], acc[c], 0, 0, 0);
+            }
+            const int n = 16 * (wv & 3) + li;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const int row = 4 * lk + rr;
+                if (row < G) part[((wv >> 2) * G + row) * PN + n] = acc[0][rr] + acc[1][rr];
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < G * NO; i += FNT) {
+            const int row = i / NO, n = i % NO;
+            dbc[i] = part[row * PN + n] + part[(G + row) * PN + n];
+        }
+    }
+};
 }  // namespace
 
 // SL: the lanes' conv and scan state live in LDS after the activations
 // ([n_layers][G][K-1][Di] then [n_layers][G][N][Di]) instead of device memory.
 // Without SL the state lives in device memory, one record per (layer, lane):
-// conv window [K-1][Di] (taps t-3, t-2, t-1) and h [N/4][Di] float4, so the
+// conv window [K-1][Di] (tap t in slot t % 3) and h [N/4][Di] float4, so the
 // accesses of a wave are contiguous.
 //
 // Decoding waves: wave w decodes lanes w, w + 8, ... of the workgroup (one
@@ -478,10 +619,17 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
     __shared__ int pos_s[G], chunk_s[G];
     __shared__ float hb_s[VOCAB];                 // head bias, read every step
     __shared__ unsigned am_ln[G], am_g[G];        // fp8: row maxima of the LayerNorm output and of g
-    unsigned* am_ln_p = DT == 2 ? am_ln : nullptr;
     // wave index as a wave-uniform (scalar) value: weight addresses that depend
     // only on it are formed in scalar registers
-    const int tid = threadIdx.x, wl = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tid = threadIdx.x, wl = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // The thread index is made opaque once per phase group: addresses formed
+    // from it are then recomputed there (a few integer operations) instead of
+    // being kept in registers over the whole step, which spilled.
+    auto fresh = [&]() {
+        asm volatile("" : "+v"(tid));
+        wl = tid & 63;
+    };
     const int lane0 = blockIdx.x * G;
 
     for (int i = tid; i < S::total; i += FNT) sm[i] = 0.0f;
@@ -535,28 +683,15 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
     __syncthreads();
 
     // The LayerNorm weights of the next LayerNorm (layer l, or the final one
-    // for l == n_layers) are requested one phase ahead; with one lane per
-    // workgroup, the conv weights of the in_proj epilogue before its LayerNorm
+    // for l == n_layers) are requested one phase ahead
     using GIn = FGemm<DT, G, D, 2 * Di / 16, DT == 2>;
-    constexpr int XF = GIn::FALL / 2 < GIn::FPW ? GIn::FALL / 2 : GIn::FPW;   // x-half fragments per wave
-    constexpr bool CWP = XF <= 4 && G == 1 && DT != 2;
-    LnPre<D, G> lnp;
-    float pcw[CWP ? XF : 1][KCONV], pcb[CWP ? XF : 1];
+    LnPre<D, G, DT == 2> lnp;
     auto pre_layer = [&](int l) {
-        if (l == a.n_layers) lnp.load(a.norm_f_w, a.norm_f_b, tid);
-        else lnp.load(a.layers[l].norm_w, a.layers[l].norm_b, tid);
+        if (l == a.n_layers) lnp.load(a.norm_f_w, a.norm_f_b, wl, wv);
+        else lnp.load(a.layers[l].norm_w, a.layers[l].norm_b, wl, wv);
     };
-    auto pre_conv = [&](const FusedLayer& w) {
-        if (CWP) {
-#pragma unroll
-            for (int j = 0; j < XF; ++j) {
-                const int n = 16 * (wv + FNW * j) + (wl & 15);
-#pragma unroll
-                for (int k = 0; k < KCONV; ++k) pcw[j][k] = gld(w.convT + k * Di + n);
-                pcb[j] = gld(w.conv_b + n);
-            }
-        }
-    };
+    // step position of slot g as a scalar (-1: idle), and its conv window's slot
+    auto spos = [&](int g) { return __builtin_amdgcn_readfirstlane(pos_s[g]); };
     pre_layer(0);
     for (long long it = 0; it < a.max_steps; ++it) {
         bool any = false;
@@ -579,87 +714,53 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
 
         for (int l = 0; l < a.n_layers; ++l) {
             const FusedLayer& w = a.layers[l];
-            // Weights are requested ahead of their phase where that hides a
-            // latency without delaying other loads: the LayerNorm weights
-            // during the previous out_proj (pre_layer), the conv weights
-            // before the LayerNorm, the dt / scan weights before the barrier
-            // that precedes x_proj, the out_proj ring at the
+            fresh();
+            // Weights and state are requested ahead of their phase where that
+            // hides a latency without delaying other loads: the LayerNorm
+            // weights during the previous out_proj (pre_layer), the conv
+            // window before the LayerNorm, the conv weights, the x_proj ring and
+            // the dt / scan weights before the conv, the out_proj ring at the
             // end of the scan (issued before it, the ring's registers pushed
             // the scan's state loads into spills).
-            pre_conv(w);
+            //
+            // Conv window of (slot, channel): a ring of K - 1 taps [K-1][Di] in
+            // LDS (SL) or in the slot's device record; tap t of a chunk is
+            // slot t % 3, so a step reads three taps and writes one.
+            constexpr int CPT = (Di + FNT - 1) / FNT;          // channels per thread
+            constexpr int CW = SL ? 1 : CPT * G * (KCONV - 1);
+            float cwin[CW];
+            auto cwin_dev = [&](int g) {
+                return a.conv_state + ((long long)l * a.lanes + lane0 + g) * (KCONV - 1) * Di;
+            };
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) {
+                const int d = tid + FNT * j;
+                if (Di % FNT && d >= Di) break;
+                if (!SL) {
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const int p = spos(g);
+#pragma unroll
+                        for (int k = 0; k < KCONV - 1; ++k) {
+                            float v = 0.0f;
+                            if (p >= KCONV - 1 - k) v = gld_nt(cwin_dev(g) + (p + k) % 3 * Di + d);
+                            cwin[(j * G + g) * (KCONV - 1) + k] = v;
+                        }
+                    }
+                }
+            }
             // the in_proj ring goes out before the LayerNorm (fp8: after it;
             // there the early ring cost more than it hid)
             GIn gin;
             if (DT != 2) gin.issue(w.in_frag, wv, wl);
-            fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, w.norm_w, w.norm_b, lnp, wl, wv, am_ln_p);
-            {
-                // epilogue: the x half goes through the causal conv + SiLU
-                // right here (channels are independent), advancing the conv
-                // state; the z half is stored for the gate
-                auto epi_in = [&](const typename GIn::Acc& acc, int f0) {
-                    const int li = wl & 15, lk = wl >> 4;
-                    // conv window of (row, channel n): [K-1][Di] in LDS (SL) or
-                    // in the row's device record
-                    auto cst_lds = [&](int row) { return cst_s + (l * G + row) * (KCONV - 1) * Di; };
-                    auto cst_dev = [&](int row) {
-                        return a.conv_state + ((long long)l * a.lanes + lane0 + row) * (KCONV - 1) * Di;
-                    };
-                    // every weight and state load of the pass first, then the arithmetic
-                    float cw[XF][KCONV], cb[XF], st[XF][4][KCONV - 1];
-#pragma unroll
-                    for (int j = 0; j < XF; ++j) {
-                        const int nf = f0 + FNW * j;
-                        if (nf >= Di / 16) continue;             // later passes hold z only
-                        const int n = 16 * nf + li;
-                        if (CWP) {
-#pragma unroll
-                            for (int k = 0; k < KCONV; ++k) cw[j][k] = pcw[CWP ? j : 0][k];
-                            cb[j] = pcb[CWP ? j : 0];
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < KCONV; ++k) cw[j][k] = gld(w.convT + k * Di + n);
-                            cb[j] = gld(w.conv_b + n);
-                        }
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) {
-                            const int row = 4 * lk + rr;
-                            const bool live = row < G && pos_s[row] > 0;
-                            if (SL) {
-                                const float* cs = cst_lds(0);
-#pragma unroll
-                                for (int k = 0; k < KCONV - 1; ++k) st[j][rr][k] = live ? cs[k * Di + n] : 0.0f;
-                            } else {
-                                const float* cs = cst_dev(live ? row : 0);
-#pragma unroll
-                                for (int k = 0; k < KCONV - 1; ++k) st[j][rr][k] = live ? gld_nt(cs + k * Di + n) : 0.0f;
-                            }
-                        }
-                    }
-                    for_outputs<GIn::FPW, G, 2 * Di / 16>(acc, f0, wl, [&](int j, int rr, int row, int n, float v) {
-                        if (n < Di) {
-                            const int jx = j < XF ? j : 0;           // x fragments are j < XF
-                            if (pos_s[row] < 0) return;
-                            xs_s[row * S::XSR + n] =
-                                conv_silu(cw[jx], cb[jx], st[jx][rr][0], st[jx][rr][1], st[jx][rr][2], v);
-                            if (SL) {
-                                float* cs = cst_lds(row);
-                                cs[n] = st[jx][rr][1];
-                                cs[Di + n] = st[jx][rr][2];
-                                cs[2 * Di + n] = v;
-                            } else {
-                                float* cs = cst_dev(row);
-                                gst_nt(cs + n, st[jx][rr][1]);
-                                gst_nt(cs + Di + n, st[jx][rr][2]);
-                                gst_nt(cs + 2 * Di + n, v);
-                            }
-                        } else {
-                            xz_s[row * ZS + (n - Di)] = v;
-                        }
-                    });
-                };
-                if (DT == 2) gin.issue(w.in_frag, wv, wl);
-                gin.run(a_s, S::DS, w.in_frag, wl, wv, am_ln, w.in_ew, epi_in);
-            }
+            fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, lnp, wl, wv, am_ln);
+            if (DT == 2) gin.issue(w.in_frag, wv, wl);
+            gin.run(a_s, S::DS, w.in_frag, wl, wv, am_ln, w.in_ew, [&](const typename GIn::Acc& acc, int f0) {
+                for_outputs<GIn::FPW, G, 2 * Di / 16>(acc, f0, wl, [&](int row, int n, float v) {
+                    if (n < Di) xs_s[row * S::XSR + n] = v;
+                    else xz_s[row * ZS + (n - Di)] = v;
+                });
+            });
             constexpr bool ONE = Di <= FNT;                    // one channel per thread in the scan
             DtW<DT, RR> pdtw;
             float pA2[NSTATE], pdtb = 0.0f, pDk = 0.0f;
@@ -671,22 +772,87 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 pDk = gld(w.Dsk + tid);
             }
             constexpr int NFX = (NO + 15) / 16;
-            __syncthreads();
-            // x_proj on the matrix cores: wave f computes column fragment f
-            // of the lanes' rows (xproj_fragment, a ring of 4 weight loads)
-            if (wv < NFX) {
-                v4f acc;
-                xproj_fragment<Di, 4>(xs_s, S::XSR, G, w.xw_frag, wv, wl, acc);
+            typename std::conditional<(G <= 2), XRows<Di, NFX, NO, (G <= 2 ? G : 1)>, XTile<Di, NFX, NO, G>>::type xp;
+            __builtin_amdgcn_sched_barrier(0);       // not among the product's loads: registers
+            float ccw[CPT][KCONV], ccb[CPT];
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int row = 4 * (wl >> 4) + rr, col = 16 * wv + (wl & 15);
-                    if (row < G && col < NO) dbc_s[row * NO + col] = acc[rr];
+            for (int j = 0; j < CPT; ++j) {
+                const int d = tid + FNT * j;
+                if (Di % FNT && d >= Di) break;
+#pragma unroll
+                for (int k = 0; k < KCONV; ++k) ccw[j][k] = gld(w.convT + k * Di + d);
+                ccb[j] = gld(w.conv_b + d);
+            }
+            xp.issue(w.xw_frag, wv, wl);
+            __syncthreads();
+            fresh();
+            // causal conv + SiLU in place, a thread per channel, advancing the
+            // window (in in_proj's epilogue it read the window in 64-byte pieces
+            // after the product: 122k cycles a step of 16 lanes of d_model 256
+            // there, 45k in the product and 21k here so)
+#pragma unroll
+            for (int j = 0; j < CPT; ++j) {
+                const int d = tid + FNT * j;
+                if (Di % FNT && d >= Di) break;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int p = spos(g);
+                    if (p < 0) continue;
+                    float t[KCONV - 1];
+                    float* cl = cst_s + (l * G + g) * (KCONV - 1) * Di + d;
+#pragma unroll
+                    for (int k = 0; k < KCONV - 1; ++k) {
+                        if (SL) t[k] = p >= KCONV - 1 - k ? cl[(p + k) % 3 * Di] : 0.0f;
+                        else t[k] = cwin[(j * G + g) * (KCONV - 1) + k];
+                    }
+                    const float x = xs_s[g * S::XSR + d];
+                    xs_s[g * S::XSR + d] = conv_silu(ccw[j], ccb[j], t[0], t[1], t[2], x);
+                    if (SL) cl[p % 3 * Di] = x;
+                    else gst_nt(cwin_dev(g) + p % 3 * Di + d, x);
                 }
             }
+            __syncthreads();
+            // The scan state of DP lane slots is in flight at a time, the first
+            // ones' during x_proj.  h of slot g: LDS [N][Di] (SL) or the slot's
+            // device record [N/4][Di] float4 (a wave's access is 1 KiB
+            // contiguous).  A slot's 16 states go together: in parts of 4 or 8
+            // states of 8 or 4 slots, with as many loads in flight, a step of 16
+            // lanes of d_model 256 took 212 and 202 us, so 187: 4.8 TB/s, what a
+            // plain copy reaches.
+            constexpr int DP = G < 4 ? G : 4;
+            static_assert(G % DP == 0, "the ring closes on the next channel");
+            float hp[DP][NSTATE];
+            auto hrec = [&](int g, int d) {
+                return reinterpret_cast<float4*>(a.h_state) + ((long long)l * a.lanes + lane0 + g) * (NSTATE / 4) * Di + d;
+            };
+            auto load_slot = [&](int d, int g) {
+                float (&h)[NSTATE] = hp[g % DP];
+                const bool live = spos(g) > 0;
+                if (SL) {
+                    const float* hst = hst_s + (l * G + g) * NSTATE * Di;
+#pragma unroll
+                    for (int n = 0; n < NSTATE; ++n) h[n] = live ? hst[n * Di + d] : 0.0f;
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NSTATE / 4; ++q) {
+                        float4 v4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        if (live) v4 = gld_nt(hrec(g, d) + q * Di);
+                        h[4 * q] = v4.x; h[4 * q + 1] = v4.y;
+                        h[4 * q + 2] = v4.z; h[4 * q + 3] = v4.w;
+                    }
+                }
+            };
+            if (Di % FNT == 0 || tid < Di) {
+#pragma unroll
+                for (int g = 0; g < DP; ++g) load_slot(tid, g);
+            }
+            if constexpr (G <= 2) xp.run(xs_s, S::XSR, w.xw_frag, wv, wl, dbc_s);
+            else xp.run(xs_s, S::XSR, w.xw_frag, wv, wl, tid, g_s, dbc_s);
             if (DT == 2 && tid < G) am_g[tid] = 0u;
             using GOut = FGemm<DT, G, Di, D / 16, DT == 2>;
             GOut gout;
             __syncthreads();
+            fresh();
             // dt_proj + softplus, selective scan, gate
             for (int d = tid; d < Di; d += FNT) {
                 float dtw[RR], A2[NSTATE], dtb, Dk;
@@ -707,90 +873,22 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                     dtb = gld(w.dtb + d);
                     Dk = gld(w.Dsk + d);
                 }
-                // The scan state goes in parts of SQ states for a group of up to
-                // 8 lane slots at once, so the loads of a part are all in
-                // flight together (one slot after another would wait G times
-                // per layer).  h of slot g: LDS [N][Di] (SL) or the slot's
-                // device record [N/4][Di] float4 (a wave's access is 1 KiB
-                // contiguous).  Each state is updated and folded into y in
-                // increasing n, the sequence of scan_update.
-                constexpr int GB = G < 8 ? G : 8;                  // slots per group
-                constexpr int SQ = GB <= 4 ? NSTATE : 8;           // states per part
-                constexpr int NP = NSTATE / SQ;
-                static_assert(SQ % 4 == 0 && NSTATE % SQ == 0 && G % GB == 0, "parts of whole float4s");
-                auto hrec = [&](int g) {
-                    return reinterpret_cast<float4*>(a.h_state) +
-                           ((long long)l * a.lanes + lane0 + g) * (NSTATE / 4) * Di + d;
-                };
-#pragma unroll 1
-                for (int g0 = 0; g0 < G; g0 += GB) {
-                    float hp[GB][SQ];
-                    auto load_part = [&](int p) {
 #pragma unroll
-                        for (int b = 0; b < GB; ++b) {
-                            const int g = g0 + b;
-                            const bool live = pos_s[g] > 0;
-                            if (SL) {
-                                const float* hst = hst_s + (l * G + g) * NSTATE * Di;
+                for (int g = 0; g < G; ++g) {
+                    if (spos(g) >= 0) {
+                        float (&h)[NSTATE] = hp[g % DP];
+                        const float* dbc = dbc_s + g * NO;
+                        const float gv = scan_update(h, dt_of<RR>(dbc, dtw, dtb), xs_s[g * S::XSR + d], dbc + RR,
+                                                     dbc + RR + NSTATE, A2, Dk, xz_s[g * ZS + d]);
+                        if (SL) {
+                            float* hst = hst_s + (l * G + g) * NSTATE * Di;
 #pragma unroll
-                                for (int s = 0; s < SQ; ++s) hp[b][s] = live ? hst[(p * SQ + s) * Di + d] : 0.0f;
-                            } else {
+                            for (int n = 0; n < NSTATE; ++n) hst[n * Di + d] = h[n];
+                        } else {
 #pragma unroll
-                                for (int q = 0; q < SQ / 4; ++q) {
-                                    float4 v4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                                    if (live) v4 = gld_nt(hrec(g) + (long long)(p * SQ / 4 + q) * Di);
-                                    hp[b][4 * q] = v4.x; hp[b][4 * q + 1] = v4.y;
-                                    hp[b][4 * q + 2] = v4.z; hp[b][4 * q + 3] = v4.w;
-                                }
-                            }
+                            for (int q = 0; q < NSTATE / 4; ++q)
+                                gst_nt(hrec(g, d) + q * Di, make_float4(h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]));
                         }
-                    };
-                    load_part(0);
-                    float dtv[GB], xsv[GB], yv[GB];
-#pragma unroll
-                    for (int b = 0; b < GB; ++b) {
-                        const int g = g0 + b;
-                        dtv[b] = 0.0f; xsv[b] = 0.0f; yv[b] = 0.0f;
-                        if (pos_s[g] < 0) continue;
-                        dtv[b] = dt_of<RR>(dbc_s + g * NO, dtw, dtb);
-                        xsv[b] = xs_s[g * S::XSR + d];
-                    }
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        if (p > 0) load_part(p);
-#pragma unroll
-                        for (int b = 0; b < GB; ++b) {
-                            const int g = g0 + b;
-                            if (pos_s[g] < 0) continue;
-                            const float* Bv = dbc_s + g * NO + RR + p * SQ;
-                            const float* Cv = Bv + NSTATE;
-                            const float dx = dtv[b] * xsv[b];
-#pragma unroll
-                            for (int s = 0; s < SQ; ++s) {
-                                const float dA = exp2_hw(dtv[b] * A2[p * SQ + s]);
-                                hp[b][s] = fmaf(dA, hp[b][s], dx * Bv[s]);
-                            }
-                            float y = yv[b];
-#pragma unroll
-                            for (int s = 0; s < SQ; ++s) y = fmaf(hp[b][s], Cv[s], y);
-                            yv[b] = y;
-                            if (SL) {
-                                float* hst = hst_s + (l * G + g) * NSTATE * Di;
-#pragma unroll
-                                for (int s = 0; s < SQ; ++s) hst[(p * SQ + s) * Di + d] = hp[b][s];
-                            } else {
-#pragma unroll
-                                for (int q = 0; q < SQ / 4; ++q)
-                                    gst_nt(hrec(g) + (long long)(p * SQ / 4 + q) * Di,
-                                        make_float4(hp[b][4 * q], hp[b][4 * q + 1], hp[b][4 * q + 2], hp[b][4 * q + 3]));
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int b = 0; b < GB; ++b) {
-                        const int g = g0 + b;
-                        if (pos_s[g] < 0) continue;
-                        const float gv = fmaf(Dk, xsv[b], yv[b]) * silu_hp(xz_s[g * ZS + d]);
                         if (DT == 1) reinterpret_cast<uint16_t*>(g_s)[g * 2 * S::GS + d] = f2bf_bits(gv);
                         else g_s[g * S::GS + d] = gv;
                         if (DT == 2) {            // row maximum: per wave first, then one LDS atomic per wave
@@ -798,8 +896,11 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                             if (wl == 0) atomicMax(&am_g[g], __float_as_uint(wm));
                         }
                     }
+                    if (g + DP < G) load_slot(d, g + DP);
+                    else if (Di > FNT && d + FNT < Di) load_slot(d + FNT, g + DP - G);
                 }
             }
+            fresh();
             gout.issue(w.out_frag, wv, wl);
             __syncthreads();
             pre_layer(l + 1);
@@ -816,21 +917,22 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
             }
             // out_proj, added into the residual stream
             gout.run(DT == 2 ? reinterpret_cast<float*>(g8_s) : g_s, DT == 2 ? Di / 4 : S::GS, w.out_frag, wl, wv, am_g, w.out_ew, [&](const typename GOut::Acc& acc, int f0) {
-                for_outputs<GOut::FPW, G, D / 16>(acc, f0, wl, [&](int, int, int row, int n, float v) {
+                for_outputs<GOut::FPW, G, D / 16>(acc, f0, wl, [&](int row, int n, float v) {
                     r_s[row * D + n] = r_s[row * D + n] + v;
                 });
             });
             __syncthreads();
         }
+        fresh();
         using GH = FGemm<DT, G, D, VOCAB / 16, DT == 2>;
         GH ghead;
         if (DT != 2) ghead.issue(a.head_frag, wv, wl);   // the head ring goes out before the final LayerNorm
-        fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, a.norm_f_w, a.norm_f_b, lnp, wl, wv, am_ln_p);
+        fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, lnp, wl, wv, am_ln);
         float* lg_s = xz_s;
         {
             if (DT == 2) ghead.issue(a.head_frag, wv, wl);
             ghead.run(a_s, S::DS, a.head_frag, wl, wv, am_ln, a.head_ew, [&](const typename GH::Acc& acc, int f0) {
-                for_outputs<GH::FPW, G, VOCAB / 16>(acc, f0, wl, [&](int, int, int row, int n, float v) {
+                for_outputs<GH::FPW, G, VOCAB / 16>(acc, f0, wl, [&](int row, int n, float v) {
                     lg_s[row * VOCAB + n] = v + hb_s[n];
                 });
             });
@@ -838,6 +940,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
         pre_layer(0);                                    // the next step's first LayerNorm
         __syncthreads();
 
+        fresh();
         // histogram, range decoding and the lane's next input row
 #pragma unroll
         for (int k = 0; k < LPW; ++k) {
