@@ -888,13 +888,21 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
 
 // =================================================================== decode
 namespace {
-// Lanes per workgroup of the fused decoder: the largest of 16, 8, 4, 2 that
-// fits LDS and still leaves at least 256 workgroups (one per CU), else 1.
+// Lanes per workgroup of the fused decoder.  A CU holds one workgroup (its
+// registers), and a workgroup beyond the 256th starts when another has decoded
+// all its lanes, so the fewest lanes whose workgroups are all resident at once
+// win: a step costs 33 / 54 / 72 / 103 / 187 us at 1 / 2 / 4 / 8 / 16 lanes
+// (bf16, d_model 256), 130 / 162 / 207 / 279 at 1 / 2 / 4 / 8 (fp8, 512), always
+// less than two rounds of half as many.  (384 lanes of the latter, 1022 steps:
+// 261 ms at one lane a workgroup, 164 at two.)  With more lanes than fit, the most that LDS holds.
 int pick_fused_lanes(int D, int lanes, int n_layers) {
-    for (int g : {16, 8, 4, 2})
-        if (g * D <= 16 * 256 && fused_lds_bytes(D, g, n_layers, false) + 2048 <= get_max_lds() && lanes / g >= 256)
-            return g;
-    return 1;
+    int best = 1;
+    for (int g : {1, 2, 4, 8, 16}) {
+        if (g * D > 16 * 256 || fused_lds_bytes(D, g, n_layers, false) + 2048 > get_max_lds()) break;
+        best = g;
+        if ((lanes + g - 1) / g <= 256) break;
+    }
+    return best;
 }
 
 // Schedule and launch shape of the fused decoder for these chunks.
