@@ -231,10 +231,8 @@ template <> struct BLoad<2> { using T = uint4; static constexpr int KPL = 64; };
 // The NF fragments of W are dealt to the waves (wave w owns w, w + 8, ...),
 // at most 8 per pass.  issue() requests the first ring of B loads of the
 // wave's first pass; it can be called a phase early so the loads arrive while
-// other work runs.  run() completes the product and hands each pass's
-// accumulators to the caller's epilogue, epi(acc, f0): lane l holds rows
-// 4 (l >> 4) + rr (rr < 4) of column l & 15 of fragments f0 + 8 j (fp8:
-// already rescaled by the row and weight scales).
+// other work runs.  run() completes the product and calls f(row, n, v) for
+// every output (fp8: rescaled by the row and weight scales).
 // A8 (fp8 only): the A rows are already E4M3 bytes (row stride 4 * as bytes,
 // scaled by 2^-ea of their row) instead of floats quantised here per k step.
 template <int DT, int G, int K, int NF, bool A8 = false>
@@ -246,7 +244,6 @@ struct FGemm {
     static constexpr int PW = 16 / FPW > 0 ? 16 / FPW : 1;
     static constexpr int P = PW < SK ? PW : SK;            // load steps in flight (power of 2, divides SK)
     static_assert(SK % P == 0, "ring period");
-    using Acc = v4f[FPW];
     BT ring[P][FPW];
 
     // Weight loads are raw buffer loads: the fragment offset (wave-uniform,
@@ -276,9 +273,9 @@ struct FGemm {
     }
     // the pass over fragments f0, f0 + 8, ... whose first ring is in flight
     // (f1 >= 0: the ring goes on with the first loads of the pass at f1)
-    template <class Epi>
+    template <class F>
     DEVI void pass(const float* __restrict__ A, int as, const void* __restrict__ Wf, const unsigned* amax_rows,
-                   int ew, int wl, int f0, int f1, Epi& epi) {
+                   int ew, int wl, int f0, int f1, F& f) {
         const int li = wl & 15, lk = wl >> 4;
         const bool arow = li < G;
         const __amdgpu_buffer_rsrc_t rs = rsrc(Wf);
@@ -362,36 +359,119 @@ struct FGemm {
                     if (row < G) acc[j][rr] = ldexpf(acc[j][rr], fp8_exp(__uint_as_float(amax_rows[row])) + ew);
                 }
         }
-        epi(acc, f0);
+#pragma unroll
+        for (int j = 0; j < FPW; ++j) {
+            const int nf = f0 + FNW * j;
+            if (nf >= NF) continue;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+                if (4 * lk + rr < G) f(4 * lk + rr, 16 * nf + li, acc[j][rr]);
+        }
     }
     // every pass of wave wv; the first pass's ring must have been issued
     // (fp8: amax_rows are the A rows' largest magnitudes as float bits, ew
     // W's scale exponent)
-    template <class Epi>
+    template <class F>
     DEVI void run(const float* __restrict__ A, int as, const void* __restrict__ Wf, int wl, int wv,
-                  const unsigned* amax_rows, const int* ewp, Epi&& epi) {
+                  const unsigned* amax_rows, const int* ewp, F&& f) {
         const int ew = DT == 2 ? *ewp : 0;
 #pragma unroll 1
-        for (int f = 0; f < FALL; f += FPW)
-            pass(A, as, Wf, amax_rows, ew, wl, wv + FNW * f, f + FPW < FALL ? wv + FNW * (f + FPW) : -1, epi);
+        for (int p = 0; p < FALL; p += FPW)
+            pass(A, as, Wf, amax_rows, ew, wl, wv + FNW * p, p + FPW < FALL ? wv + FNW * (p + FPW) : -1, f);
     }
 };
 
-// f(row, n, v) for every output of a pass that this lane holds
-template <int FPW, int G, int NF, class F>
-DEVI void for_outputs(const v4f (&acc)[FPW], int f0, int wl, F&& f) {
-    const int li = wl & 15, lk = wl >> 4;
+// The same product in f32 for one or two rows, on the vector ALU: the MFMA adds
+// its four products one after another, each with a single rounding, exactly as
+// fmaf in increasing k does, and takes the same time for 1 row as for 16 -- 164k
+// cycles of a step of d_model 256, where 5 MB of weights arrive in 85k and a
+// row's fmaf take 20k.  Each lane owns one column of four fragments' 64 (column
+// lane % 16 of fragment lane / 16) and reads the fragment order's k = 4 j + lk
+// values as four float4; sets of four fragments are dealt to the waves.  A step
+// of one lane took 101 us with the MFMA and takes 60 so (two lanes: 123 and
+// 101; four: 135 and 148).
+template <int G, int K, int NF>
+struct RGemm {
+    static constexpr int NS = NF / 4, SPW = NS > FNW ? NS / FNW : 1;   // sets; per wave
+    static constexpr int SP = SPW < 2 ? SPW : 2;                       // per pass
+    static constexpr int SK = K / 16, PW = 4 / SP, P = PW < SK ? PW : SK;
+    static_assert(NF % 4 == 0 && (NS <= FNW || NS % FNW == 0) && SPW % SP == 0 && SK % P == 0, "whole sets and rings");
+    f32x4 ring[P][SP][4];
+    DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, 16 * NF * K * 4, 0x00020000);
+    }
+    DEVI static f32x4 ld(__amdgpu_buffer_rsrc_t r, int set, int q, int lk, int voff) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, ((4 * set * SK + q) * 64 + 16 * lk) * 16, 0);
+        f32x4 o;
+        __builtin_memcpy(&o, &v, sizeof o);
+        return o;
+    }
+    DEVI static int voff(int wl) { return ((wl >> 4) * SK * 64 + (wl & 15)) * 16; }
+    // (waves without a set load past the buffer's range, which reads as zero:
+    // a branch here would keep the ring's registers alive around it)
+    DEVI void issue(const void* Wf, int wv, int wl) {
+        const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
+        const int vo = voff(wl);
 #pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-        const int nf = f0 + FNW * j;
-        if (nf >= NF) continue;
+        for (int u = 0; u < P; ++u)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int row = 4 * lk + rr;
-            if (row < G) f(row, 16 * nf + li, acc[j][rr]);
+            for (int s = 0; s < SP; ++s)
+#pragma unroll
+                for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv + FNW * s, u, lk, vo);
+    }
+    template <class F>
+    DEVI void run(const float* __restrict__ A, int as, const void* __restrict__ Wf, int wl, int wv, const unsigned*,
+                  const int*, F&& f) {
+        if (wv >= NS) return;
+        const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
+        const int vo = voff(wl);
+#pragma unroll 1
+        for (int p = 0; p < SPW; p += SP) {
+            float acc[SP][G];
+#pragma unroll
+            for (int s = 0; s < SP; ++s)
+#pragma unroll
+                for (int g = 0; g < G; ++g) acc[s][g] = 0.0f;
+            // one ring of k groups from q0, refilled with those of pass pn from qn
+            auto period = [&](int q0, int pn, int qn, bool refill) {
+#pragma unroll
+                for (int u = 0; u < P; ++u) {
+                    f32x4 w[SP][4];
+#pragma unroll
+                    for (int s = 0; s < SP; ++s)
+#pragma unroll
+                        for (int lk = 0; lk < 4; ++lk) w[s][lk] = ring[u][s][lk];
+                    if (refill) {
+#pragma unroll
+                        for (int s = 0; s < SP; ++s)
+#pragma unroll
+                            for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv + FNW * (pn + s), qn + u, lk, vo);
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const f32x4 x = *reinterpret_cast<const f32x4*>(A + g * as + 16 * (q0 + u) + 4 * j);
+#pragma unroll
+                            for (int lk = 0; lk < 4; ++lk)
+#pragma unroll
+                                for (int s = 0; s < SP; ++s) acc[s][g] = fmaf(x[lk], w[s][lk][j], acc[s][g]);
+                        }
+                }
+            };
+#pragma unroll 1
+            for (int q0 = 0; q0 + P < SK; q0 += P) period(q0, p, q0 + P, true);
+            if (p + SP < SPW) period(SK - P, p + SP, 0, true);
+            else period(SK - P, 0, 0, false);
+#pragma unroll
+            for (int s = 0; s < SP; ++s)
+#pragma unroll
+                for (int g = 0; g < G; ++g) f(g, 16 * (4 * (wv + FNW * (p + s)) + (wl >> 4)) + (wl & 15), acc[s][g]);
         }
     }
-}
+};
+template <int DT, int G, int K, int NF>
+using Gemm = typename std::conditional<DT == 0 && G <= 2, RGemm<(G <= 2 ? G : 1), K, NF>, FGemm<DT, G, K, NF, DT == 2>>::type;
 
 // LayerNorm of the G residual rows into a_s.  With G >= 8 a wave takes whole
 // rows (w, w + 8); with fewer rows the waves share them, wave w normalising the
@@ -502,11 +582,16 @@ struct XRows {
     f32x4 ring[PG][4];
     DEVI static bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
     DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int lk) {
-        const int q = 4 * i + (wl >> 4);
-        return ((const __attribute__((address_space(1))) f32x4*)Wf)[((wv & 3) * SQ + q) * 64 + 16 * lk + (wl & 15)];
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, 16 * NFX * Di * 4, 0x00020000);
+        const int f = mine(wv) ? wv & 3 : NFX;               // past the range: reads as zero
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, ((wl >> 4) * 64 + (wl & 15)) * 16,
+                                                              ((f * SQ + 4 * i) * 64 + 16 * lk) * 16, 0);
+        f32x4 o;
+        __builtin_memcpy(&o, &v, sizeof o);
+        return o;
     }
     DEVI void issue(const float* Wf, int wv, int wl) {
-        if (!mine(wv)) return;
 #pragma unroll
         for (int i = 0; i < PG; ++i)
 #pragma unroll
@@ -545,11 +630,16 @@ template <int Di, int NFX, int NO, int G>
 struct XTile {
     static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : 4, PN = 16 * NFX;
     f32x4 ring[PG][2];
-    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {
-        return ((const __attribute__((address_space(1))) f32x4*)Wf)[((wv & 3) * SQ + 4 * i + 2 * (wv >> 2) + c) * 64 + wl];
+    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {   // fragments past NFX read as zero
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, 16 * NFX * Di * 4, 0x00020000);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, wl * 16,
+                                                              ((wv & 3) * SQ + 4 * i + 2 * (wv >> 2) + c) * 1024, 0);
+        f32x4 o;
+        __builtin_memcpy(&o, &v, sizeof o);
+        return o;
     }
     DEVI void issue(const float* Wf, int wv, int wl) {
-        if ((wv & 3) >= NFX) return;
 #pragma unroll
         for (int i = 0; i < PG; ++i)
 #pragma unroll
@@ -684,7 +774,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
 
     // The LayerNorm weights of the next LayerNorm (layer l, or the final one
     // for l == n_layers) are requested one phase ahead
-    using GIn = FGemm<DT, G, D, 2 * Di / 16, DT == 2>;
+    using GIn = Gemm<DT, G, D, 2 * Di / 16>;
     LnPre<D, G, DT == 2> lnp;
     auto pre_layer = [&](int l) {
         if (l == a.n_layers) lnp.load(a.norm_f_w, a.norm_f_b, wl, wv);
@@ -755,11 +845,9 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
             if (DT != 2) gin.issue(w.in_frag, wv, wl);
             fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, lnp, wl, wv, am_ln);
             if (DT == 2) gin.issue(w.in_frag, wv, wl);
-            gin.run(a_s, S::DS, w.in_frag, wl, wv, am_ln, w.in_ew, [&](const typename GIn::Acc& acc, int f0) {
-                for_outputs<GIn::FPW, G, 2 * Di / 16>(acc, f0, wl, [&](int row, int n, float v) {
-                    if (n < Di) xs_s[row * S::XSR + n] = v;
-                    else xz_s[row * ZS + (n - Di)] = v;
-                });
+            gin.run(a_s, S::DS, w.in_frag, wl, wv, am_ln, w.in_ew, [&](int row, int n, float v) {
+                if (n < Di) xs_s[row * S::XSR + n] = v;
+                else xz_s[row * ZS + (n - Di)] = v;
             });
             constexpr bool ONE = Di <= FNT;                    // one channel per thread in the scan
             DtW<DT, RR> pdtw;
@@ -849,7 +937,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
             if constexpr (G <= 2) xp.run(xs_s, S::XSR, w.xw_frag, wv, wl, dbc_s);
             else xp.run(xs_s, S::XSR, w.xw_frag, wv, wl, tid, g_s, dbc_s);
             if (DT == 2 && tid < G) am_g[tid] = 0u;
-            using GOut = FGemm<DT, G, Di, D / 16, DT == 2>;
+            using GOut = Gemm<DT, G, Di, D / 16>;
             GOut gout;
             __syncthreads();
             fresh();
@@ -916,25 +1004,21 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 __syncthreads();
             }
             // out_proj, added into the residual stream
-            gout.run(DT == 2 ? reinterpret_cast<float*>(g8_s) : g_s, DT == 2 ? Di / 4 : S::GS, w.out_frag, wl, wv, am_g, w.out_ew, [&](const typename GOut::Acc& acc, int f0) {
-                for_outputs<GOut::FPW, G, D / 16>(acc, f0, wl, [&](int row, int n, float v) {
-                    r_s[row * D + n] = r_s[row * D + n] + v;
-                });
+            gout.run(DT == 2 ? reinterpret_cast<float*>(g8_s) : g_s, DT == 2 ? Di / 4 : S::GS, w.out_frag, wl, wv, am_g, w.out_ew, [&](int row, int n, float v) {
+                r_s[row * D + n] = r_s[row * D + n] + v;
             });
             __syncthreads();
         }
         fresh();
-        using GH = FGemm<DT, G, D, VOCAB / 16, DT == 2>;
+        using GH = Gemm<DT, G, D, VOCAB / 16>;
         GH ghead;
         if (DT != 2) ghead.issue(a.head_frag, wv, wl);   // the head ring goes out before the final LayerNorm
         fused_ln<D, G, DT == 1, DT == 2>(r_s, a_s, S::DS, lnp, wl, wv, am_ln);
         float* lg_s = xz_s;
         {
             if (DT == 2) ghead.issue(a.head_frag, wv, wl);
-            ghead.run(a_s, S::DS, a.head_frag, wl, wv, am_ln, a.head_ew, [&](const typename GH::Acc& acc, int f0) {
-                for_outputs<GH::FPW, G, VOCAB / 16>(acc, f0, wl, [&](int row, int n, float v) {
-                    lg_s[row * VOCAB + n] = v + hb_s[n];
-                });
+            ghead.run(a_s, S::DS, a.head_frag, wl, wv, am_ln, a.head_ew, [&](int row, int n, float v) {
+                lg_s[row * VOCAB + n] = v + hb_s[n];
             });
         }
         pre_layer(0);                                    // the next step's first LayerNorm
