@@ -1033,11 +1033,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
             if (gl >= G || q.pos < 0) continue;
             const int lane = lane0 + gl;
             QRow qr = quant_row(lg_s + gl * VOCAB, wl);
-            const uint32_t x = dec_target(q.dc);
-            int hit = -1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((uint32_t)qr.cx[i] <= x && x < (uint32_t)(qr.cx[i] + qr.f[i])) hit = 4 * wl + i;
+            const int hit = dec_hit(q.dc, qr.cx, qr.f, wl);
             const unsigned long long bal = __ballot(hit >= 0);
             const int src = bal ? (__ffsll((long long)bal) - 1) : 0;
             int sym = __builtin_amdgcn_readlane(hit, src);  // wave-uniform lane indices: lane reads

@@ -233,93 +233,134 @@ DEVI QRow quant_row(const float* __restrict__ lg, int lane) {
 
 
 // ---------------------------------------------------------------- range coder
+// State: the interval [L, L + D] of 32-bit values (D = R - 1 of the paper's
+// width R, which lies in [2^16, 2^32] between symbols).  A symbol of (cl, f)
+// narrows it to L + floor(R cl / 2^16), R = floor(R f / 2^16); the bytes on
+// which both ends agree leave, and an interval that straddles them with
+// R < 2^16 is cut to R = 2^16 - (L mod 2^16), whose ends agree on two bytes or
+// more.  Shifting a byte out brings 00 into L and FF into L + D, so the bytes
+// to shift are the leading equal ones of the two ends, known at once, before
+// and after the cut, and no second cut can follow: no loop per byte.
+// rc_step: narrows, returns the number of bytes shifted out (0 .. 8; they are
+// the leading bytes of the narrowed L, then zeros) and that L in top.
+DEVI int rc_lead(uint32_t L, uint32_t D) {      // leading equal bytes of L and L + D
+    const uint32_t x = L ^ (L + D);
+    return x ? __builtin_clz(x) >> 3 : 4;
+}
+DEVI uint64_t rc_mul(uint32_t D, uint32_t c) { return (uint64_t)D * c + c; }   // R c, c <= 2^16
+DEVI void rc_shift(uint32_t& L, uint32_t& D, int n) {
+    L = (uint32_t)((uint64_t)L << (8 * n));
+    D = (uint32_t)(((uint64_t)D << (8 * n)) | ((1ULL << (8 * n)) - 1));
+}
+DEVI int rc_step(uint32_t& L, uint32_t& D, uint32_t cl, uint32_t f, uint32_t& top) {
+    L += (uint32_t)(rc_mul(D, cl) >> 16);
+    D = (uint32_t)(rc_mul(D, f) >> 16) - 1;
+    top = L;
+    int n = rc_lead(L, D);
+    rc_shift(L, D, n);
+    if (__builtin_expect(D < 65535u, 0)) {
+        D = 65535u - (L & 65535u);
+        const int m = rc_lead(L, D);
+        rc_shift(L, D, m);
+        n += m;
+    }
+    return n;
+}
+
+// Encoder: cnt (0 .. 3) bytes wait in the top of acc, cur are written.
 struct Enc {
-    uint64_t L, R;
-    uint32_t cur;
+    uint32_t L, D;
+    uint32_t cur, cnt;
+    uint64_t acc;
 };
-DEVI void enc_reset(Enc& e) { e.L = 0; e.R = 1ULL << 32; e.cur = 0; }
-DEVI void enc_emit(Enc& e, uint8_t* out, uint32_t cap, uint32_t b) {
-    if (e.cur < cap) out[e.cur] = (uint8_t)b;
-    e.cur++;
+DEVI void enc_reset(Enc& e) { e.L = 0; e.D = 0xFFFFFFFFu; e.cur = 0; e.cnt = 0; e.acc = 0; }
+DEVI void enc_bytes(Enc& e, uint8_t* out, uint32_t cap) {   // the waiting bytes, one by one
+    for (; e.cnt; --e.cnt) {
+        if (e.cur < cap) out[e.cur] = (uint8_t)(e.acc >> 56);
+        e.acc <<= 8;
+        e.cur++;
+    }
+}
+// n <= 4 bytes, the top ones of w, join the waiting ones; four leave as a word
+DEVI void enc_emit(Enc& e, uint8_t* out, uint32_t cap, uint32_t w, int n) {
+    const uint64_t keep = ~(~0ULL >> (8 * n)) & ((uint64_t)w << 32);
+    e.acc |= keep >> (8 * e.cnt);
+    e.cnt += n;
+    if (e.cnt >= 4) {
+        const uint32_t v = __builtin_bswap32((uint32_t)(e.acc >> 32));
+        if (e.cur + 4 <= cap) {
+            __builtin_memcpy(out + e.cur, &v, 4);
+        } else {
+            for (uint32_t i = 0; i < 4; ++i)
+                if (e.cur + i < cap) out[e.cur + i] = (uint8_t)(v >> (8 * i));
+        }
+        e.cur += 4;
+        e.cnt -= 4;
+        e.acc <<= 32;
+    }
 }
 DEVI void enc_put(Enc& e, uint32_t cl, uint32_t f, uint8_t* out, uint32_t cap) {
-    uint64_t L = e.L + ((e.R * cl) >> 16);
-    uint64_t R = (e.R * f) >> 16;
-    for (;;) {
-        if ((L >> 24) == ((L + R - 1) >> 24)) {
-            enc_emit(e, out, cap, (uint32_t)(L >> 24));
-            L = (L << 8) & 0xFFFFFFFFULL;
-            R <<= 8;
-        } else if (R < 65536ULL) {
-            R = 65536ULL - (L & 0xFFFFULL);
-        } else {
-            break;
-        }
+    uint32_t top;
+    const int n = rc_step(e.L, e.D, cl, f, top);
+    if (n) {
+        enc_emit(e, out, cap, top, n < 4 ? n : 4);
+        if (n > 4) enc_emit(e, out, cap, 0, n - 4);
     }
-    e.L = L;
-    e.R = R;
 }
 DEVI void enc_flush(Enc& e, uint8_t* out, uint32_t cap) {
     for (int k = 0; k < 3; ++k) {
         int sh = 32 - 8 * k;
-        uint64_t V = ((e.L + (1ULL << sh) - 1) >> sh) << sh;
-        if (V <= e.L + e.R - 1) {
-            for (int i = 0; i < k; ++i) enc_emit(e, out, cap, (uint32_t)((V >> (24 - 8 * i)) & 0xFF));
-            return;
+        uint64_t V = (((uint64_t)e.L + (1ULL << sh) - 1) >> sh) << sh;
+        if (V <= (uint64_t)e.L + e.D) {
+            enc_emit(e, out, cap, (uint32_t)V, k);
+            break;
         }
     }
+    enc_bytes(e, out, cap);
 }
 
 struct Dec {
-    uint64_t L, R, X;
+    uint32_t L, D, X;
     uint32_t cur;
 };
 DEVI uint32_t dec_byte(const uint8_t* in, uint32_t len, uint32_t i) { return i < len ? in[i] : 0u; }
 DEVI void dec_reset(Dec& d, const uint8_t* in, uint32_t len) {
     d.L = 0;
-    d.R = 1ULL << 32;
+    d.D = 0xFFFFFFFFu;
     d.X = 0;
     for (uint32_t i = 0; i < 4; ++i) d.X = (d.X << 8) | dec_byte(in, len, i);
     d.cur = 4;
 }
-// floor(v / r) for v < 2^53 and 1 <= r <= 2^32: the correctly rounded double
-// quotient is within 2^-5 of v / r, so its truncation is the floor or one
-// above it, which the integer check corrects (no 64-bit integer division)
-DEVI uint64_t udiv_small(uint64_t v, uint64_t r) {
-    uint64_t q = (uint64_t)((double)v / (double)r);
-    if (q * r > v) --q;
-    return q;
-}
-DEVI uint32_t dec_target(const Dec& d) {   // x = floor(((X - L + 1) M - 1) / R)
-    uint64_t v = ((d.X - d.L + 1) << 16) - 1;
-    uint64_t x = udiv_small(v, d.R);
-    return x > 65535ULL ? 65535u : (uint32_t)x;   // clamp only matters for corrupt input
+// The symbol is the one with cx <= x < cx + f for the paper's target
+// x = floor(v / R), v = (X - L + 1) 2^16 - 1: cx R <= v < (cx + f) R, products
+// instead of a division.  x past the tables' total (a corrupt payload, X < L
+// included: v wraps to a huge value) means the last symbol.
+DEVI uint64_t dec_v(const Dec& d) { return (((uint64_t)d.X - d.L + 1) << 16) - 1; }
+DEVI bool dec_from(uint64_t v, uint32_t D, uint32_t c) { return rc_mul(D, c) <= v; }
+DEVI bool dec_upto(uint64_t v, uint32_t D, uint32_t end) { return end >= 65536u || v < rc_mul(D, end); }
+// the symbol among this wave lane's four (4 wl .. 4 wl + 3), or -1
+DEVI int dec_hit(const Dec& d, const int (&cx)[4], const int (&f)[4], int wl) {
+    const uint64_t v = dec_v(d);
+    int hit = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (dec_from(v, d.D, (uint32_t)cx[i]) && dec_upto(v, d.D, (uint32_t)(cx[i] + f[i]))) hit = 4 * wl + i;
+    return hit;
 }
 // pf: the next 8 payload bytes from d.cur, read ahead of time, byte i in bits
 // 8i..8i+7 (has_pf = false: read each byte when needed)
 DEVI void dec_update(Dec& d, uint32_t cl, uint32_t f, const uint8_t* in, uint32_t len,
                      uint64_t pf = 0, bool has_pf = false) {
-    uint64_t L = d.L + ((d.R * cl) >> 16);
-    uint64_t R = (d.R * f) >> 16;
-    uint64_t X = d.X;
-    uint32_t used = 0;
-    for (;;) {
-        if ((L >> 24) == ((L + R - 1) >> 24)) {
-            L = (L << 8) & 0xFFFFFFFFULL;
-            R <<= 8;
-            uint32_t b = (has_pf && used < 8) ? (uint32_t)((pf >> (8 * used)) & 0xFF) : dec_byte(in, len, d.cur);
-            X = ((X << 8) & 0xFFFFFFFFULL) | b;
-            d.cur++;
-            used++;
-        } else if (R < 65536ULL) {
-            R = 65536ULL - (L & 0xFFFFULL);
-        } else {
-            break;
-        }
+    uint32_t top;
+    const int n = rc_step(d.L, d.D, cl, f, top);
+    if (has_pf) {
+        const uint64_t b = __builtin_bswap64(pf);
+        d.X = n <= 4 ? (uint32_t)(((((uint64_t)d.X << 32) | (b >> 32)) << (8 * n)) >> 32)
+                     : (uint32_t)((b << (8 * (n - 4))) >> 32);
+    } else {
+        for (int i = 0; i < n; ++i) d.X = (d.X << 8) | dec_byte(in, len, d.cur + i);
     }
-    d.L = L;
-    d.R = R;
-    d.X = X;
+    d.cur += n;
 }
 
 

@@ -239,7 +239,9 @@ struct QShared {
     int f[256], cx[256];
     ll red[4];
     int redi[4];
-    int sym, x;
+    int sym;
+    uint32_t D;
+    uint64_t v;
     ll t16[16], lnc[17];         // the exponential's and logarithm's tables, read with divergent indexes
 };
 
@@ -417,9 +419,9 @@ __global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
             __syncthreads();
             if (t == 0) boa::enc_put(enc, (uint32_t)sh.cx[y], (uint32_t)sh.f[y], pay_out, cap);
         } else {
-            if (t == 0) sh.x = (int)boa::dec_target(dec);
+            if (t == 0) { sh.v = boa::dec_v(dec); sh.D = dec.D; }
             __syncthreads();
-            if (cx <= sh.x && sh.x < cx + f) sh.sym = t;
+            if (boa::dec_from(sh.v, sh.D, (uint32_t)cx) && boa::dec_upto(sh.v, sh.D, (uint32_t)(cx + f))) sh.sym = t;
             __syncthreads();
             y = sh.sym;
             if (t == 0) {

@@ -1483,73 +1483,132 @@ hipError_t launch_diag(const float* logits, int M, const uint8_t* data, const Pl
 // byte cursor.  Paper, Range coding: encoder update, renormalisation while the
 // top byte of L and E = L + R - 1 agree; readings: R is not reduced mod 2^32,
 // straddle fix R <- 2^16 - (L mod 2^16), flush with at most 2 bytes.
-// Encoder lanes: one thread per lane walks its rows of the tile in order.
-// cst per lane: [L, R_lo, R_hi, cur] (uint32).
-__global__ void k_encode(const uint32_t* __restrict__ cf, int lanes, int T, const int* __restrict__ row_chunk,
-                         const int* __restrict__ row_pos, Plan p, uint32_t* __restrict__ cst,
-                         uint8_t* __restrict__ payload, const long long* __restrict__ pay_off,
-                         const long long* __restrict__ pay_cap, uint32_t* __restrict__ pay_len,
-                         double* __restrict__ ideal) {
-    constexpr int RB = 16;                       // rows fetched per batch (independent loads, one latency)
-    int lane = blockIdx.x * blockDim.x + threadIdx.x;
-    if (lane >= lanes) return;
-    Enc e;
-    e.L = cst[4 * lane];
-    e.R = (uint64_t)cst[4 * lane + 1] | ((uint64_t)cst[4 * lane + 2] << 32);
-    e.cur = cst[4 * lane + 3];
+// Encoder lanes: one thread per lane walks its rows of the tile in order.  A
+// serial chain per lane, so nothing else is left to it: the wave loads 32
+// or 64 rows of its per_wave lanes together into LDS, with what marks a row that
+// starts or ends a chunk or is idle, while the rows before are coded, and the
+// lanes are spread over the chip.  With every row loaded by its lane's thread
+// (64 cache lines a load), a loop iteration per byte and byte stores, a symbol
+// took 380 ns on one lane and 780 on 256, 200 and 290 so.
+// cst per lane: [L, D, 0, cur] (uint32).
+// ONE (a lane per wave, up to 511 lanes): every thread of the wave holds the
+// lane's values, so the chain runs in scalar registers with scalar branches.
+constexpr int ENC_LANES = 16;                    // lanes per wave at most
+template <bool ONE>
+__global__ __launch_bounds__(64) void k_encode(const uint32_t* __restrict__ cf, int lanes, int per_wave, int T,
+                                               const int* __restrict__ row_chunk, const int* __restrict__ row_pos,
+                                               Plan p, uint32_t* __restrict__ cst, uint8_t* __restrict__ payload,
+                                               const long long* __restrict__ pay_off,
+                                               const long long* __restrict__ pay_cap,
+                                               uint32_t* __restrict__ pay_len, double* __restrict__ ideal) {
+    constexpr int RB = ONE ? 64 : 32, NL = ONE ? 1 : ENC_LANES;   // rows per batch; lanes
+    constexpr int RS = RB + 1;                   // row stride of a lane: other banks for its neighbours
+    constexpr int NE = RB * NL / 64;             // rows per thread and batch
+    constexpr int IDLE = -2, PLAIN = -1;         // mark: idle row; inside a chunk; else the row's chunk
+    __shared__ uint2 cf_s[NL * RS];
+    __shared__ int mark_s[NL * RS], pos_s[NL * RS];
+    const int tid = threadIdx.x, lane0 = blockIdx.x * per_wave;
+    const int me = ONE ? 0 : tid, lane = lane0 + me;
+    const bool mine = me < per_wave && lane < lanes;
+    auto uni = [](uint32_t v) { return ONE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)v) : v; };
+    uint2 fc[NE];
+    int fp[NE], fk[NE];
+    auto fetch = [&](int t0) {                   // row t0 + i % RB of lane i / RB
+#pragma unroll
+        for (int u = 0; u < NE; ++u) {
+            const int i = tid + 64 * u, l = i / RB, t = t0 + i % RB;
+            fp[u] = -1;
+            fk[u] = IDLE;
+            if (l >= per_wave || lane0 + l >= lanes || t >= T) continue;
+            const long long row = (long long)(lane0 + l) * T + t;
+            fp[u] = row_pos[row];
+            if (fp[u] < 0) continue;
+            fc[u] = reinterpret_cast<const uint2*>(cf)[row];
+            const int c = row_chunk[row];
+            fk[u] = t == 0 || fp[u] == 0 || fp[u] == p.chunk_steps[c] - 1 ? c : PLAIN;
+        }
+    };
+    Enc e{};
+    if (mine) {
+        e.L = uni(cst[4 * lane]);
+        e.D = uni(cst[4 * lane + 1]);
+        e.cur = uni(cst[4 * lane + 3]);
+    }
     double ib = 0.0;
     int cur_chunk = -1;
     uint8_t* out = nullptr;
     uint32_t cap = 0;
-    long long last = -1;                         // last position of the current chunk
+    fetch(0);
     for (int t0 = 0; t0 < T; t0 += RB) {
-        int pos_b[RB], chk_b[RB];
-        uint32_t cl_b[RB], f_b[RB];
+        __syncthreads();
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const long long row = (long long)lane * T + t0 + r;
-            const bool in = t0 + r < T;
-            pos_b[r] = in ? row_pos[row] : -1;
-            chk_b[r] = in ? row_chunk[row] : -1;
-            cl_b[r] = in ? cf[2 * row] : 0u;
-            f_b[r] = in ? cf[2 * row + 1] : 0u;
+        for (int u = 0; u < NE; ++u) {
+            const int i = tid + 64 * u, at = i / RB * RS + i % RB;
+            cf_s[at] = fc[u];
+            mark_s[at] = fk[u];
+            pos_s[at] = fp[u];
         }
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int pos = pos_b[r];
-            if (pos < 0) continue;
-            const int c = chk_b[r];
-            if (c != cur_chunk) {
-                if (cur_chunk >= 0 && ideal) ideal[cur_chunk] = ib;
-                out = payload + pay_off[c];
-                cap = (uint32_t)pay_cap[c];
-                last = p.chunk_steps[c] - 1;
-                ib = (pos > 0 && ideal) ? ideal[c] : 0.0;
-                cur_chunk = c;
-            }
-            if (pos == 0) { enc_reset(e); ib = 0.0; }
-            const uint32_t f = f_b[r];
-            // ideal cost -log2(f / 2^16) = 16 - log2 f: hardware log2 in FP32
-            // (about 1 ulp), summed in FP64
-            if (ideal) ib += (double)(16.0f - __builtin_amdgcn_logf((float)f));
-            enc_put(e, cl_b[r], f, out, cap);
-            if (pos == last) {
-                enc_flush(e, out, cap);
-                pay_len[c] = e.cur <= cap ? e.cur : 0xFFFFFFFFu;
+        __syncthreads();
+        fetch(t0 + RB);
+        if (!mine) continue;
+        const int n = T - t0 < RB ? T - t0 : RB;
+        // ideal cost -log2(f / 2^16) = 16 - log2 f: hardware log2 in FP32
+        // (about 1 ulp), summed in FP64
+        auto code = [&](uint2 q) {
+            if (ideal) ib += (double)(16.0f - __builtin_amdgcn_logf((float)q.y));
+            enc_put(e, q.x, q.y, out, cap);
+        };
+        int next_c = mark_s[me * RS];
+        uint2 next_q = cf_s[me * RS];
+        for (int r = 0; r < n; ++r) {
+            const int at = me * RS + r, c = (int)uni((uint32_t)next_c);
+            const uint2 q = make_uint2(uni(next_q.x), uni(next_q.y));
+            next_c = mark_s[at + 1];             // (after the batch's last row: not used)
+            next_q = cf_s[at + 1];
+            if (c == PLAIN) {
+                code(q);
+            } else if (c != IDLE) {
+                const int pos = (int)uni((uint32_t)pos_s[at]);
+                if (c != cur_chunk) {            // (the previous chunk's bytes left with its flush)
+                    if (cur_chunk >= 0 && ideal) ideal[cur_chunk] = ib;
+                    const long long po = pay_off[c];
+                    out = payload + (long long)((uint64_t)uni((uint32_t)po) |
+                                                (uint64_t)uni((uint32_t)((uint64_t)po >> 32)) << 32);
+                    cap = uni((uint32_t)pay_cap[c]);
+                    ib = (pos > 0 && ideal) ? ideal[c] : 0.0;
+                    cur_chunk = c;
+                    // used here, so that no later use waits for these loads (and
+                    // with them for every byte store since)
+                    if (!ONE) asm volatile("" : "+v"(cap), "+v"(out), "+v"(ib));
+                    else asm volatile("" : "+s"(cap), "+s"(out), "+v"(ib));
+                }
+                if (pos == 0) { enc_reset(e); ib = 0.0; }
+                code(q);
+                if (pos == (int)uni((uint32_t)p.chunk_steps[c]) - 1) {
+                    enc_flush(e, out, cap);
+                    pay_len[c] = e.cur <= cap ? e.cur : 0xFFFFFFFFu;
+                }
             }
         }
     }
+    if (!mine) return;
     if (cur_chunk >= 0 && ideal) ideal[cur_chunk] = ib;
-    cst[4 * lane] = (uint32_t)e.L;
-    cst[4 * lane + 1] = (uint32_t)(e.R & 0xFFFFFFFFULL);
-    cst[4 * lane + 2] = (uint32_t)(e.R >> 32);
+    enc_bytes(e, out, cap);
+    cst[4 * lane] = e.L;
+    cst[4 * lane + 1] = e.D;
     cst[4 * lane + 3] = e.cur;
 }
 hipError_t launch_encode(const uint32_t* cf, int lanes, int T, const int* row_chunk, const int* row_pos,
                          const Plan& p, uint32_t* cst, uint8_t* payload, const long long* pay_off,
                          const long long* pay_cap, uint32_t* pay_len, double* ideal, hipStream_t s) {
-    BOA_LAUNCH(k_encode, dim3((lanes + 63) / 64), dim3(64), 0, s, cf, lanes, T, row_chunk, row_pos, p,
-                       cst, payload, pay_off, pay_cap, pay_len, ideal);
+    const int w = lanes / 256, per_wave = w < 1 ? 1 : (w < ENC_LANES ? w : ENC_LANES);
+    const dim3 grid((lanes + per_wave - 1) / per_wave);
+    if (per_wave == 1)
+        BOA_LAUNCH(k_encode<true>, grid, dim3(64), 0, s, cf, lanes, per_wave, T, row_chunk, row_pos, p, cst, payload,
+                   pay_off, pay_cap, pay_len, ideal);
+    else
+        BOA_LAUNCH(k_encode<false>, grid, dim3(64), 0, s, cf, lanes, per_wave, T, row_chunk, row_pos, p, cst, payload,
+                   pay_off, pay_cap, pay_len, ideal);
     return hipGetLastError();
 }
 
@@ -1557,7 +1616,7 @@ hipError_t launch_encode(const uint32_t* cf, int lanes, int T, const int* row_ch
 // symbol whose CDF interval holds the target, updates the coder, writes the
 // byte, and prepares the lane's next step: its (chunk, pos) and the embedding
 // row r = E[next input byte] (the decoded byte, or the stored first byte of
-// the lane's next chunk).  dst per lane: [L, R_lo, R_hi, X, cur, step_lo, step_hi, 0].
+// the lane's next chunk).  dst per lane: [L, D, 0, X, cur, step_lo, step_hi, 0].
 __global__ void k_decode(const float* __restrict__ logits, int lanes, int* __restrict__ row_chunk,
                          int* __restrict__ row_pos, Plan p, uint32_t* __restrict__ dst,
                          const uint8_t* __restrict__ payload, const long long* __restrict__ pay_off,
@@ -1570,7 +1629,7 @@ __global__ void k_decode(const float* __restrict__ logits, int lanes, int* __res
     if (pos < 0) return;
     const int c = row_chunk[lane_id];
     uint32_t* st = dst + 8 * lane_id;
-    const uint32_t s0 = st[0], s1 = st[1], s2 = st[2], s3 = st[3], s4 = st[4], s5 = st[5], s6 = st[6];
+    const uint32_t s0 = st[0], s1 = st[1], s3 = st[3], s4 = st[4], s5 = st[5], s6 = st[6];
     const long long poff = pay_off[c];
     const uint32_t len = (uint32_t)pay_len[c];
     const uint8_t* in = payload + poff;
@@ -1580,18 +1639,14 @@ __global__ void k_decode(const float* __restrict__ logits, int lanes, int* __res
         dec_reset(d, in, len);
     } else {
         d.L = s0;
-        d.R = (uint64_t)s1 | ((uint64_t)s2 << 32);
+        d.D = s1;
         d.X = s3;
         d.cur = s4;
     }
     uint64_t pf = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) pf |= (uint64_t)dec_byte(in, len, d.cur + i) << (8 * i);
-    uint32_t x = dec_target(d);
-    int hit = -1;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if ((uint32_t)q.cx[i] <= x && x < (uint32_t)(q.cx[i] + q.f[i])) hit = 4 * wl + i;
+    const int hit = dec_hit(d, q.cx, q.f, wl);
     unsigned long long bal = __ballot(hit >= 0);
     int src = bal ? (__ffsll((long long)bal) - 1) : 0;
     int sym = __builtin_amdgcn_readlane(hit, src);   // wave-uniform lane indices
@@ -1616,10 +1671,9 @@ __global__ void k_decode(const float* __restrict__ logits, int lanes, int* __res
     }
     if (wl == 0) {
         dec_update(d, (uint32_t)cl, (uint32_t)fs, in, len, pf, true);
-        st[0] = (uint32_t)d.L;
-        st[1] = (uint32_t)(d.R & 0xFFFFFFFFULL);
-        st[2] = (uint32_t)(d.R >> 32);
-        st[3] = (uint32_t)d.X;
+        st[0] = d.L;
+        st[1] = d.D;
+        st[3] = d.X;
         st[4] = d.cur;
         st[5] = (uint32_t)((uint64_t)(lstep + 1) & 0xFFFFFFFFULL);
         st[6] = (uint32_t)((uint64_t)(lstep + 1) >> 32);
@@ -1724,10 +1778,10 @@ __global__ void k_decode_tables(const uint8_t* __restrict__ payload, const long 
         int loc = ((fl[0] + fl[1]) + fl[2]) + fl[3];
         int incl = wave_incl_scan_i(loc, wl);
         int c = incl - loc;
-        uint32_t x = dec_target(d);
+        const uint64_t v = dec_v(d);
         int hit = -1, hc = 0, hf = 0;
         for (int i = 0; i < 4; ++i) {
-            if ((uint32_t)c <= x && x < (uint32_t)(c + fl[i])) { hit = 4 * wl + i; hc = c; hf = fl[i]; }
+            if (fl[i] && dec_from(v, d.D, (uint32_t)c) && dec_upto(v, d.D, (uint32_t)(c + fl[i]))) { hit = 4 * wl + i; hc = c; hf = fl[i]; }
             c += fl[i];
         }
         unsigned long long bal = __ballot(hit >= 0);
@@ -1742,7 +1796,7 @@ __global__ void k_decode_tables(const uint8_t* __restrict__ payload, const long 
         }
         // broadcast the updated state from wave lane 0
         d.L = __shfl(d.L, 0, 64);
-        d.R = __shfl(d.R, 0, 64);
+        d.D = __shfl(d.D, 0, 64);
         d.X = __shfl(d.X, 0, 64);
         d.cur = __shfl(d.cur, 0, 64);
     }
@@ -1756,23 +1810,82 @@ hipError_t launch_decode_tables(const uint8_t* payload, const long long* pay_off
 }
 
 // ============================================================== CRC32 per chunk
-// Reflected CRC-32 (polynomial 0xEDB88320), bitwise, one thread per chunk.
-__global__ void k_crc32(const uint8_t* __restrict__ data, const long long* __restrict__ off,
-                        const long long* __restrict__ len, int n, uint32_t* __restrict__ crc) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint32_t c = 0xFFFFFFFFu;
-    const uint8_t* p = data + off[i];
-    for (long long j = 0; j < len[i]; ++j) {
-        c ^= p[j];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) c = (c >> 1) ^ (0xEDB88320u & (0u - (c & 1u)));
+// Reflected CRC-32 (polynomial 0xEDB88320): the register holds a polynomial
+// over GF(2), bit 31 - i the coefficient of x^i, and is linear in message and
+// start value, so a wave splits its chunk into 64 pieces of S bytes that end
+// with the chunk (the first ones short or empty), each lane runs its piece
+// from 0 -- the one with the chunk's first byte from all ones -- and the pieces
+// meet pairwise: left x^(8 S 2^k) + right at level k.  Within a piece four
+// bytes go through four tables at a time.  One thread per chunk, bit by bit,
+// took 0.41 ms for a chunk of 4 KiB and 2.1 ms for 256 of 16 KiB, 12 and 20 us
+// so.
+constexpr uint32_t CRC_POLY = 0xEDB88320u, CRC_ONE = 0x80000000u;
+// a b mod P
+__host__ __device__ constexpr uint32_t crc_mul(uint32_t a, uint32_t b) {
+    uint32_t r = 0;
+    for (int i = 0; i < 32; ++i) {                       // b = b x^i
+        r ^= b & (0u - (a >> 31));
+        a <<= 1;
+        b = (b >> 1) ^ (CRC_POLY & (0u - (b & 1u)));
     }
-    crc[i] = ~c;
+    return r;
+}
+struct CrcPowers {
+    uint32_t v[64];                                      // x^(8 2^k)
+    constexpr CrcPowers() : v() {
+        v[0] = CRC_ONE >> 8;
+        for (int k = 1; k < 64; ++k) v[k] = crc_mul(v[k - 1], v[k - 1]);
+    }
+};
+__constant__ CrcPowers kCrcPow = CrcPowers();
+__global__ __launch_bounds__(256) void k_crc32(const uint8_t* __restrict__ data, const long long* __restrict__ off,
+                                               const long long* __restrict__ len, int n, uint32_t* __restrict__ crc) {
+    __shared__ uint32_t tab[4][256];                     // [j]: one byte, then j zero bytes
+    {
+        uint32_t c = threadIdx.x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) c = (c >> 1) ^ (CRC_POLY & (0u - (c & 1u)));
+            tab[j][threadIdx.x] = c;
+        }
+    }
+    __syncthreads();
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), wl = threadIdx.x & 63;
+    if (i >= n) return;
+    const long long ln = len[i];
+    const long long S = ((ln + 63) / 64 + 3) & ~3LL;     // bytes per piece
+    long long b0 = ln - (64 - wl) * S, b1 = b0 + S;
+    uint32_t c = b0 <= 0 && b1 > 0 ? 0xFFFFFFFFu : 0u;
+    b0 = b0 < 0 ? 0 : b0;
+    const uint8_t* p = data + off[i];
+    constexpr int U = 8;                                 // words in flight
+    for (; b0 + 4 * U <= b1; b0 += 4 * U) {
+        uint32_t w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) __builtin_memcpy(&w[u], p + b0 + 4 * u, 4);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c ^= w[u];
+            c = tab[3][c & 255] ^ tab[2][(c >> 8) & 255] ^ tab[1][(c >> 16) & 255] ^ tab[0][c >> 24];
+        }
+    }
+    for (; b0 < b1; ++b0) c = (c >> 8) ^ tab[0][(c ^ p[b0]) & 255];
+    // x^(8 S): the product of the powers of S's bits
+    uint32_t xs = (S >> wl) & 1 ? kCrcPow.v[wl] : CRC_ONE;
+#pragma unroll 1
+    for (int o = 1; o < 64; o <<= 1) xs = crc_mul(xs, __shfl_xor(xs, o));
+#pragma unroll 1
+    for (int o = 1; o < 64; o <<= 1) {                   // lanes with the wave's low bits set hold a right piece
+        const uint32_t left = __shfl_up(c, o);
+        if ((wl & (2 * o - 1)) == 2 * o - 1) c ^= crc_mul(left, xs);
+        xs = crc_mul(xs, xs);
+    }
+    if (wl == 63) crc[i] = ln > 0 ? ~c : 0u;
 }
 hipError_t launch_crc32(const uint8_t* data, const long long* off, const long long* len, int n, uint32_t* crc,
                         hipStream_t s) {
-    hipLaunchKernelGGL(k_crc32, dim3((n + 63) / 64), dim3(64), 0, s, data, off, len, n, crc);
+    hipLaunchKernelGGL(k_crc32, dim3((n + 3) / 4), dim3(256), 0, s, data, off, len, n, crc);
     return hipGetLastError();
 }
 
@@ -1883,10 +1996,7 @@ __global__ void k_order2_decode(const uint8_t* __restrict__ payload, const long 
         uint16_t* row = cnt + ((long long)(p2 * 256 + p1)) * 256;
         int f[4], cx[4], total;
         o2_table(row, wl, f, cx, total);
-        uint32_t xt = dec_target(d);
-        int hit = -1;
-        for (int i = 0; i < 4; ++i)
-            if ((uint32_t)cx[i] <= xt && xt < (uint32_t)(cx[i] + f[i])) hit = 4 * wl + i;
+        const int hit = dec_hit(d, cx, f, wl);
         unsigned long long bal = __ballot(hit >= 0);
         int src = bal ? (__ffsll((long long)bal) - 1) : 0;
         int s = __shfl(hit, src, 64);
@@ -1897,7 +2007,7 @@ __global__ void k_order2_decode(const uint8_t* __restrict__ payload, const long 
             x[t] = (uint8_t)s;
         }
         d.L = __shfl(d.L, 0, 64);
-        d.R = __shfl(d.R, 0, 64);
+        d.D = __shfl(d.D, 0, 64);
         d.X = __shfl(d.X, 0, 64);
         d.cur = __shfl(d.cur, 0, 64);
         o2_update(row, wl, s, total);
