@@ -471,8 +471,12 @@ hipError_t mgemm_launch(const float* A, int M, int K, const float* W32, const ui
 // fragment copy with per-tensor exponent *ew; the accumulator is rescaled
 // exactly by 2^(ea + ew) before the epilogue.  MFMA 16x16x32 fp8 in k steps of
 // 32 from zero.
+// Three workgroups a CU for the added-to products of up to 32 rows: left to
+// itself the compiler takes registers for two (131072 x 512 -> 256 in bf16: 109
+// us, 102 with three, 130 with four, 140 when the values to add to were read in
+// the epilogue; 84 us of memory time).
 template <int DT, int EPI, bool LNA, int K, int BM, bool A16 = false>
-__global__ __launch_bounds__(256) void k_rowgemm(const float* __restrict__ A, int M, const void* __restrict__ Wf,
+__global__ __launch_bounds__(256, EPI == 2 && BM <= 32 ? 3 : 1) void k_rowgemm(const float* __restrict__ A, int M, const void* __restrict__ Wf,
                                                  int N, float* __restrict__ C, const float* __restrict__ ln_w,
                                                  const float* __restrict__ ln_b, const float* __restrict__ bias,
                                                  const int* __restrict__ ew) {
@@ -568,6 +572,20 @@ __global__ __launch_bounds__(256) void k_rowgemm(const float* __restrict__ A, in
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        // EPI 2: the values to add to are requested before the product (read
+        // one by one between the stores, each waited for the last)
+        float old[EPI == 2 ? FM : 1][FN][4];
+        if (EPI == 2) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int row = m0 + i * 16 + 4 * lk + rr;
+                        old[EPI == 2 ? i : 0][j][rr] = C[(long long)(row < M ? row : M - 1) * N + (nf0 + j) * 16 + li];
+                    }
+        }
         if (DT == 0) {
             constexpr int Q = K / 16;
             const float4* W4 = reinterpret_cast<const float4*>(Wf) + (long long)nf0 * Q * 64 + lane;
@@ -665,12 +683,26 @@ __global__ __launch_bounds__(256) void k_rowgemm(const float* __restrict__ A, in
                         float v = acc[i][j][rr];
                         if (DT == 2) v = ldexpf(v, ea_s[i * 16 + 4 * lk + rr] + ew0);
                         if (EPI == 1) v = v + bias[n];
-                        if (EPI == 2) v = *dst + v;
+                        if (EPI == 2) v = old[EPI == 2 ? i : 0][j][rr] + v;
                         if (EPI == 3) v = gelu_f(v + bias[n]);
                         *dst = v;
                     }
                 }
     }
+}
+
+template <int DT, int EPI, bool LNA, int K, int BM, bool A16>
+hipError_t rowgemm_rows(const float* A, int M, const void* Wf, int N, float* C, const float* ln_w, const float* ln_b,
+                        const float* bias, const int* ew, hipStream_t s) {
+    constexpr int AS = DT == 0 ? K + 4 : (DT == 1 ? K + 8 : K + 16);
+    const size_t lds = (size_t)BM * AS * (DT == 0 ? 4 : (DT == 1 ? 2 : 1));
+    auto kern = k_rowgemm<DT, EPI, LNA, K, BM, A16>;
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    BOA_LAUNCH(kern, dim3((M + BM - 1) / BM), dim3(256), lds, s, A, M, Wf, N, C, ln_w, ln_b, bias, ew);
+    return hipGetLastError();
 }
 
 template <int DT, int EPI, bool LNA, int K, bool A16 = false>
@@ -684,16 +716,12 @@ hipError_t rowgemm_launch(const float* A, int M, const void* Wf, int N, float* C
     // than 64; the BF16 head, 256 columns: 32 rows 21 % faster than 64, where
     // the in_proj's 1024 columns want 64)
     constexpr bool HEAD16 = DT == 1 && EPI == 1 && LNA && K <= 256;
-    constexpr int BM = A16 ? 32 : K <= 256 ? (HEAD16 ? 32 : 64) : (K == 512 ? (DT == 1 ? 16 : 32) : 16);
-    constexpr int AS = DT == 0 ? K + 4 : (DT == 1 ? K + 8 : K + 16);
-    const size_t lds = (size_t)BM * AS * (DT == 0 ? 4 : (DT == 1 ? 2 : 1));
-    auto kern = k_rowgemm<DT, EPI, LNA, K, BM, A16>;
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    BOA_LAUNCH(kern, dim3((M + BM - 1) / BM), dim3(256), lds, s, A, M, Wf, N, C, ln_w, ln_b, bias, ew);
-    return hipGetLastError();
+    constexpr int BMX = A16 ? 32 : K <= 256 ? (HEAD16 ? 32 : 64) : (K == 512 ? (DT == 1 ? 16 : 32) : 16);
+    // too few rows for a workgroup per CU: 16 at a time (4096 f32
+    // rows: in_proj of d_model 256 87 -> 42 us, out_proj 30 -> 25)
+    if (BMX > 16 && (M + BMX - 1) / BMX < 256)
+        return rowgemm_rows<DT, EPI, LNA, K, 16, A16>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
+    return rowgemm_rows<DT, EPI, LNA, K, BMX, A16>(A, M, Wf, N, C, ln_w, ln_b, bias, ew, s);
 }
 
 hipError_t launch_rowgemm(int dtype, int kind, const float* A, int M, int K, const void* Wf, int N, float* C,
