@@ -1232,9 +1232,11 @@ __global__ __launch_bounds__(Di < 256 ? Di : 256) void k_scan(LayerDev w, const 
 // state): wave w of workgroup (channel block, state group) owns state
 // 4 (blockIdx.x % 4) + w.  dt, x and B of 64 rows are staged in LDS while the
 // previous rows are walked; groups of eight rows form their exponentials and
-// inputs first, then the chain of one fused multiply-add per row runs.  The
-// state before every RB-th row goes to hsub.  A chunk start zeroes h; idle rows
-// have dt = x = 0, which leave it as it is.
+// inputs first (the next group's operands are read meanwhile), then the chain
+// of one fused multiply-add per row runs.  The state before every RB-th row goes
+// to hsub.  A chunk start zeroes h; idle rows leave it as it is.  With a branch
+// per staged row and each group's operands waited for, 4096 rows of one lane
+// took 274 us, 188 so.
 constexpr int SCAN_RB = 16;                      // rows between kept states (and per k_scan_rows block)
 template <int Di, int RR>
 __global__ __launch_bounds__(256) void k_scan_states(LayerDev w, const float* __restrict__ xs,
@@ -1242,8 +1244,8 @@ __global__ __launch_bounds__(256) void k_scan_states(LayerDev w, const float* __
                                                      const int* __restrict__ row_pos, float* __restrict__ hstate,
                                                      float* __restrict__ hsub) {
     constexpr int NO = RR + 2 * NSTATE, SB = 64;
-    __shared__ float dt_s[SB][64], x_s[SB][64], b_s[SB][4];
-    __shared__ int start_s[SB / 8];              // per group of eight rows: bit r set when row r starts a chunk
+    __shared__ __align__(16) float dt_s[SB][64], x_s[SB][64], b_s[4][SB];
+    __shared__ int start_s[SB / 8], live_s[SB / 8];   // per group of eight rows: bit r for row r
     const int tid = threadIdx.x, wl = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = blockIdx.y, d = (blockIdx.x >> 2) * 64 + wl, n = (blockIdx.x & 3) * 4 + wv;
     const long long base = (long long)lane * T;
@@ -1251,50 +1253,67 @@ __global__ __launch_bounds__(256) void k_scan_states(LayerDev w, const float* __
     const float A2 = w.A2T[n * Di + d];
     float* hp = hstate + ((long long)lane * NSTATE + n) * Di + d;
     float h = *hp;
-    float rd[SB / 4], rx[SB / 4], rb = 0.0f;
-    int rp = -1;
-    auto fetch = [&](int s0) {
+    float rd[SB / 4], rx[SB / 4], rb;
+    int rp;
+    auto fetch = [&](int s0) {                   // rows past the tile: its last row, marked idle
 #pragma unroll
         for (int i = 0; i < SB / 4; ++i) {
-            const int t = s0 + wv + 4 * i;
-            const bool in = t < T && row_pos[base + t] >= 0;
-            rd[i] = in ? dt[(base + t) * Di + d] : 0.0f;
-            rx[i] = in ? xs[(base + t) * Di + d] : 0.0f;
+            const int t = s0 + wv + 4 * i, tc = t < T ? t : T - 1;
+            rd[i] = dt[(base + tc) * Di + d];
+            rx[i] = xs[(base + tc) * Di + d];
         }
-        const int t = s0 + (tid >> 2);
-        rb = t < T && row_pos[base + t] >= 0 ? dbc[(base + t) * NO + RR + (blockIdx.x & 3) * 4 + (tid & 3)] : 0.0f;
-        rp = tid < SB && s0 + tid < T ? row_pos[base + s0 + tid] : -1;
+        const int tb = s0 + (tid & 63), tc = tb < T ? tb : T - 1;
+        rb = dbc[(base + tc) * NO + RR + n];   // thread (wave, row): B of the wave's state
+        rp = tb < T ? row_pos[base + tb] : -1;
     };
     fetch(0);
     for (int s0 = 0; s0 < T; s0 += SB) {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < SB / 4; ++i) { dt_s[wv + 4 * i][wl] = rd[i]; x_s[wv + 4 * i][wl] = rx[i]; }
-        b_s[tid >> 2][tid & 3] = rb;
+        b_s[wv][wl] = rb;
         if (wv == 0) {
-            const unsigned long long m = __ballot(rp == 0);
-            if (wl < SB / 8) start_s[wl] = (int)((m >> (8 * wl)) & 0xFF);
+            const unsigned long long m = __ballot(rp == 0), lv = __ballot(rp >= 0);
+            if (wl < SB / 8) {
+                start_s[wl] = (int)((m >> (8 * wl)) & 0xFF);
+                live_s[wl] = (int)((lv >> (8 * wl)) & 0xFF);
+            }
         }
         __syncthreads();
         fetch(s0 + SB);
+        const int ng = T - s0 < SB ? (T - s0 + 7) / 8 : SB / 8;
+        float dn[8], xn[8], bn[8];
+        int sn, ln;
+        auto operands = [&](int q) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                dn[j] = dt_s[8 * q + j][wl];
+                xn[j] = x_s[8 * q + j][wl];
+                bn[j] = b_s[wv][8 * q + j];
+            }
+            sn = start_s[q];
+            ln = live_s[q];
+        };
+        operands(0);
 #pragma unroll 1
-        for (int t8 = 0; t8 < SB && s0 + t8 < T; t8 += 8) {
+        for (int q = 0; q < ng; ++q) {
             float a[8], u[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float dtv = dt_s[t8 + j][wl], x = x_s[t8 + j][wl];
-                a[j] = exp2_hw(dtv * A2);
-                u[j] = (dtv * x) * b_s[t8 + j][wv];
+                a[j] = exp2_hw(dn[j] * A2);
+                u[j] = (dn[j] * xn[j]) * bn[j];
             }
-            if ((s0 + t8) % SCAN_RB == 0)
-                hsub[(((long long)lane * nslot + (s0 + t8) / SCAN_RB) * NSTATE + n) * Di + d] = h;
-            const int starts = __builtin_amdgcn_readfirstlane(start_s[t8 / 8]);
-            if (starts == 0) {
+            const int starts = __builtin_amdgcn_readfirstlane(sn), live = __builtin_amdgcn_readfirstlane(ln);
+            operands(q + 1 < SB / 8 ? q + 1 : q);
+            if ((s0 + 8 * q) % SCAN_RB == 0)
+                hsub[(((long long)lane * nslot + (s0 + 8 * q) / SCAN_RB) * NSTATE + n) * Di + d] = h;
+            if (starts == 0 && live == 0xFF) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) h = fmaf(a[j], h, u[j]);
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
+                    if (!(live >> j & 1)) continue;
                     if (starts >> j & 1) h = 0.0f;
                     h = fmaf(a[j], h, u[j]);
                 }
@@ -1364,7 +1383,7 @@ __global__ __launch_bounds__(Di < 256 ? Di : 256) void k_scan_rows(LayerDev w, c
 
 // One thread per (lane, channel) fills the GPU with two waves per SIMD from
 // 2048 waves on; below MIXER_FEW waves the blocks of rows run side by side.
-// One 4096-step stream, d_inner 512: k_scan_states 275 us + k_scan_rows 21 us,
+// One 4096-step stream, d_inner 512: k_scan_states 188 us + k_scan_rows 21 us,
 // where a workgroup walking the lane took 3905 us; 256 lanes have enough waves
 // for k_scan, which computes each exponential once.
 constexpr int MIXER_FEW = 1024;
