@@ -68,6 +68,15 @@ __device__ inline ll fdiv(ll a, ll b) {
     while ((q + 1) * b <= a) ++q;
     return q;
 }
+// floor(a / b) for numerators exact in double, 0 <= a, 0 < b < 2^32 and a
+// quotient below 2^31: the truncated double quotient is the answer or one off,
+// which one remainder tells (a - q b lies within (-b, 2 b)); the loops of fdiv,
+// a 64-bit product each, were a ninth of a step
+__device__ inline unsigned fdiv32(ll a, unsigned b) {
+    const unsigned q = (unsigned)((double)a / (double)b);
+    const ll r = a - (ll)((unsigned long long)q * b);
+    return r < 0 ? q - 1 : (r >= (ll)b ? q + 1 : q);
+}
 // 2^30 2^(g / 2^30) for 0 <= g < 2^30: 2^(k/16) from the table times a
 // degree-4 Taylor polynomial of 2^u on [0, 1/16), Horner in Q30
 __host__ __device__ inline ll exp2_frac(ll g, ll tk) {
@@ -79,21 +88,77 @@ __host__ __device__ inline ll exp2_frac(ll g, ll tk) {
     q = (1LL << 30) + rsh(mulu32(q, u), 30);
     return rsh(mulu32(tk, q), 30);
 }
-// exp(x / 2^24) in Q30 for x <= 0 (0 below 2^-46)
-__device__ inline ll exp_neg(ll x, const ll* T16) {
-    if (x < -(64LL << 24)) x = -(64LL << 24);     // -2^30 <= x <= 0
-    const ll y = rsh(mul32(x, LOG2E), 24);
-    const ll n = y >> 30;
-    const ll g = y - (n << 30);
-    const ll p = exp2_frac(g, T16[g >> 26]);
-    const ll sh = -n;                             // >= 0: a right shift, rounded half up, without branches
-    return sh >= 62 ? 0 : (p + ((1LL << sh) >> 1)) >> sh;
+// exp(x / 2^24) in Q30 for -2^30 <= x <= 0 (0 below 2^-46), in 32-bit words: each
+// product is one 32 x 32 + 64 multiply-add whose rounding is its addend and
+// whose shift is the choice of its upper word (u is kept times 4, so that
+// >> 30 becomes >> 32) or one funnel shift.  The intermediate ranges are those
+// of exp2_frac; p < 2^31, so shifts by 32 and more round to 0.  The pipeline is
+// bound by the issue of this integer arithmetic (half of a step's cycles here):
+// 1024 chunks of 128 to 384 bytes, d_model 256, encoded and decoded took 118 ms
+// with 64-bit values throughout, 87 with these forms, q8 and fdiv32.
+// (written as the instruction: from the C expression the compiler widens an
+// operand and spends two more multiplies)
+__host__ __device__ inline ll mad_i(int a, int b, ll c) {
+#ifdef __HIP_DEVICE_COMPILE__
+    ll r;
+    asm("v_mad_i64_i32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c) : "vcc");
+    return r;
+#else
+    return (ll)a * b + c;
+#endif
 }
-__device__ inline ll sigmoid_q30(ll u, const ll* T16) {          // u Q12
+__host__ __device__ inline unsigned long long mad_u(unsigned a, unsigned b, unsigned long long c) {
+#ifdef __HIP_DEVICE_COMPILE__
+    unsigned long long r;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c) : "vcc");
+    return r;
+#else
+    return (unsigned long long)a * b + c;
+#endif
+}
+__host__ __device__ inline unsigned hi32(unsigned long long v) { return (unsigned)(v >> 32); }
+__host__ __device__ inline unsigned funnel(unsigned long long v, int s) { return (unsigned)(v >> s); }
+__host__ __device__ inline unsigned exp_neg32(int x, const unsigned* T16) {
+    const ll y = mad_i(x, (int)LOG2E, 1LL << 23);                   // y >> 24 = n 2^30 + g
+    const unsigned g = funnel((unsigned long long)y, 24) & ((1u << 30) - 1);
+    const unsigned sh = (unsigned)-((int)hi32((unsigned long long)y) >> 22);
+    const unsigned u4 = g << 2 & ((1u << 28) - 1);
+    constexpr unsigned long long HALF = 1ULL << 31;
+    unsigned q = (unsigned)C4;
+    q = (unsigned)C3 + hi32(mad_u(q, u4, HALF));
+    q = (unsigned)C2 + hi32(mad_u(q, u4, HALF));
+    q = (unsigned)C1 + hi32(mad_u(q, u4, HALF));
+    q = (1u << 30) + hi32(mad_u(q, u4, HALF));
+    const unsigned p = funnel(mad_u(T16[g >> 26], q, 1ULL << 29), 30);
+    const unsigned r = (p + ((1u << (sh & 31)) >> 1)) >> (sh & 31);
+    return sh > 31 ? 0 : r;
+}
+__device__ inline ll exp_neg(ll x, const unsigned* T16) {
+    return exp_neg32(x < -(64LL << 24) ? -(64 << 24) : (int)x, T16);
+}
+// exp of the rounded product (dl A) / 2^8 for 0 <= dl <= 2^30, -2^24 <= A <= 0
+__host__ __device__ inline unsigned exp_prod(int dl, int A, const unsigned* T16) {
+    const ll v = mad_i(dl, A, 128);
+    const int hi = (int)hi32((unsigned long long)v);
+    return exp_neg32(hi < -64 ? -(1 << 30) : (int)funnel((unsigned long long)v, 8), T16);
+}
+// clamp to +-(2^31 - 1)
+__host__ __device__ inline int sat31(ll v) {
+    const int lo = (int)v, hi = (int)(v >> 32);
+    const int r = hi == lo >> 31 ? lo : (hi < 0 ? -2147483647 : 2147483647);
+    return r < -2147483647 ? -2147483647 : r;
+}
+// h' = clamp(round(dA h / 2^30) + round(dx B / 2^8)) for dA <= 2^30, |h| < 2^31,
+// |dx| <= 2^33, |B| < 2^23; dx = 2^8 dh + d8, so the second rounding needs d8 B only
+__host__ __device__ inline int state_next(unsigned dA, int h, int dh, int d8, int B) {
+    const int a = (int)funnel((unsigned long long)mad_i((int)dA, h, 1LL << 29), 30);
+    return sat31(mad_i(dh, B, (ll)((d8 * B + 128) >> 8)) + a);
+}
+__device__ inline ll sigmoid_q30(ll u, const unsigned* T16) {          // u Q12
     const ll e = exp_neg(-(u < 0 ? -u : u) << 12, T16);
-    return u >= 0 ? fdiv(1LL << 60, (1LL << 30) + e) : fdiv(e << 30, (1LL << 30) + e);
+    return fdiv32(u >= 0 ? 1LL << 60 : e << 30, (1u << 30) + (unsigned)e);
 }
-__device__ inline ll silu_q12(ll u, const ll* T16) {
+__device__ inline ll silu_q12(ll u, const unsigned* T16) {
     return clampll(rsh(mul32(u, sigmoid_q30(u, T16)), 30), -SAT23, SAT23);
 }
 // ln(1 + w / 2^30) in Q30 for 0 <= w <= 2^30: ln(1 + k/16) from the table plus
@@ -101,7 +166,7 @@ __device__ inline ll silu_q12(ll u, const ll* T16) {
 __device__ inline ll log1p_q30(ll w, const ll* LNC) {
     const ll k = w >> 26;
     const ll c = (1LL << 30) + (k << 26);
-    const ll r = fdiv(((1LL << 30) + w - c) << 30, c);
+    const ll r = fdiv32(((1LL << 30) + w - c) << 30, (unsigned)c);
     ll h = H5;                                    // 0 < h <= 2^30, 0 <= r < 2^26
     h = (1LL << 28) - rsh(mulu32(h, r), 30);
     h = H3 - rsh(mulu32(h, r), 30);
@@ -109,15 +174,14 @@ __device__ inline ll log1p_q30(ll w, const ll* LNC) {
     h = (1LL << 30) - rsh(mulu32(h, r), 30);
     return LNC[k] + rsh(mulu32(h, r), 30);
 }
-__device__ inline ll softplus_q20(ll v, const ll* T16, const ll* LNC) {         // v Q12 -> Delta Q20
+__device__ inline ll softplus_q20(ll v, const unsigned* T16, const ll* LNC) {         // v Q12 -> Delta Q20
     const ll w = exp_neg(-(v < 0 ? -v : v) << 12, T16);
     return clampll(((v > 0 ? v : 0) << 8) + rsh(log1p_q30(w, LNC), 10), 0, 1LL << 30);
 }
-__device__ inline ll isqrt64(ll v) {              // floor(sqrt(v)), v >= 0
-    ll r = (ll)sqrt((double)v);
-    while (r > 0 && r * r > v) --r;
-    while ((r + 1) * (r + 1) <= v) ++r;
-    return r;
+__device__ inline ll isqrt64(ll v) {              // floor(sqrt(v)), 0 <= v < 2^53
+    ll r = (ll)sqrt((double)v);                   // the root or one above
+    if (mulu32(r, r) > v) --r;
+    return mulu32(r + 1, r + 1) <= v ? r + 1 : r;
 }
 __device__ inline int bitlen(unsigned m) { return m ? 32 - __clz(m) : 0; }
 
@@ -190,51 +254,121 @@ __device__ inline int blk_argmax(ll v, int idx, ll* red, int* redi) {
     return bi;
 }
 
-// LayerNorm of D Q12 values (src) into dst
-__device__ void int_ln(const int* src, int* dst, const int* g, const int* b, int D, ll* red) {
+// the largest of non-negative values
+__device__ inline int blk_max_i(int v, int* red) {
+    for (int o = 32; o > 0; o >>= 1) {
+        const int w = __shfl_xor(v, o);
+        v = w > v ? w : v;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int m = red[0];
+    for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
+    return m;
+}
+// LayerNorm of D Q12 values (src) into dst; D is a power of two, so the means
+// are shifts, and |src - mu| <= sqrt(D) sd bounds the normalised value below
+// 2^18, so K = 2^20 makes the numerator of its floor non-negative
+template <int D>
+__device__ void int_ln(const int* src, int* dst, const int* g, const int* b, ll* red) {
+    constexpr int LD = D == 64 ? 6 : D == 128 ? 7 : D == 256 ? 8 : 9;
+    static_assert(1 << LD == D, "d_model");
     const int t = threadIdx.x;
     ll s = 0;
     for (int d = t; d < D; d += NT) s += src[d];
     s = blk_sum(s, red);
-    const ll mu = fdiv(s, D);
+    const ll mu = s >> LD;
     ll v = 0;
     for (int d = t; d < D; d += NT) { ll dd = src[d] - mu; v += mul32(dd, dd); }   // |dd| < 2^24
     v = blk_sum(v, red);
-    const ll sd = isqrt64(fdiv(v, D) + EPS_Q24);
+    const ll sd = isqrt64((v >> LD) + EPS_Q24);
+    constexpr ll K = 1 << 20;
     for (int d = t; d < D; d += NT) {
         const ll dd = src[d] - mu;
-        const ll nn = fdiv(2 * (dd << 12) + sd, 2 * sd);
-        dst[d] = (int)clampll(rsh(nn * g[d], 12) + b[d], -SAT23, SAT23);
+        const ll nn = (ll)fdiv32(2 * (dd << 12) + sd + K * 2 * sd, (unsigned)(2 * sd)) - K;
+        dst[d] = (int)clampll(rsh(mul32(nn, g[d]), 12) + b[d], -SAT23, SAT23);
     }
     __syncthreads();
 }
+// round(v / 2^e) half up, clamped to +-127, |v| < 2^23
+__device__ inline unsigned q8(int v, int e) {
+    const int q = e > 0 ? (v + (1 << (e - 1))) >> e : v;
+    return (unsigned)(q < -127 ? -127 : (q > 127 ? 127 : q)) & 0xFFu;
+}
 // dynamic INT8 input of a projection: packs n values of src (n % 4 == 0) into
 // words and returns the shift e
-__device__ int int_q8(const int* src, int n, int* words, ll* red) {
+__device__ int int_q8(const int* src, int n, int* words, int* red) {
     const int t = threadIdx.x;
-    ll m = 0;
-    for (int i = t; i < n; i += NT) { ll a = src[i] < 0 ? -(ll)src[i] : src[i]; m = a > m ? a : m; }
-    m = blk_max(m, red);
+    int m = 0;
+    for (int i = t; i < n; i += NT) { const int a = src[i] < 0 ? -src[i] : src[i]; m = a > m ? a : m; }
+    m = blk_max_i(m, red);
     const int bl = bitlen((unsigned)m);
     const int e = bl > 7 ? bl - 7 : 0;
     for (int w = t; w < n / 4; w += NT) {
-        unsigned pk = 0;
-        for (int b = 0; b < 4; ++b) {
-            ll q = clampll(rsh(src[4 * w + b], e), -127, 127);
-            pk |= ((unsigned)q & 0xFFu) << (8 * b);
-        }
-        words[w] = (int)pk;
+        const int4 x = reinterpret_cast<const int4*>(src)[w];
+        words[w] = (int)(q8(x.x, e) | q8(x.y, e) << 8 | q8(x.z, e) << 16 | q8(x.w, e) << 24);
     }
     __syncthreads();
     return e;
 }
 
+__device__ inline int dot16(int4 a, int4 b, int acc) {
+    acc = __builtin_amdgcn_sdot4(a.x, b.x, acc, false);
+    acc = __builtin_amdgcn_sdot4(a.y, b.y, acc, false);
+    acc = __builtin_amdgcn_sdot4(a.z, b.z, acc, false);
+    return __builtin_amdgcn_sdot4(a.w, b.w, acc, false);
+}
+// Sums over k words of inputs a8 with words w [K4][N]: V adjacent outputs from o
+// on, input words k0 .. k0 + K4 - 1 (V words a load).
+template <int V, int N, int K4>
+__device__ inline void dot_cols(const int* a8, const int* w, int o, int k0, int (&acc)[V]) {
+    typedef int vec __attribute__((ext_vector_type(V)));
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[v] = 0;
+    constexpr int U = K4 < 32 / V ? K4 : 32 / V;        // loads in flight
+#pragma unroll 1
+    for (int k = 0; k < K4; k += U) {
+        int b[U][V];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int* src = w + (k0 + k + u) * N + o;
+            if constexpr (V == 1) {
+                b[u][0] = *src;
+            } else {
+                const vec x = *reinterpret_cast<const vec*>(src);
+#pragma unroll
+                for (int v = 0; v < V; ++v) b[u][v] = x[v];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] = __builtin_amdgcn_sdot4(a8[k0 + k + u], b[u][v], acc[v], false);
+    }
+}
+// The N sums of K4 words: wave w takes a quarter of the inputs for all outputs
+// (64 lanes x V of them a pass) and the quarters meet in part [4][N].
+template <int N, int K4>
+__device__ inline void dot_split(const int* a8, const int* w, int* part) {
+    constexpr int V = N / 64 < 4 ? N / 64 : 4;
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+    for (int o = V * ln; o < N; o += 64 * V) {
+        int acc[V];
+        dot_cols<V, N, K4 / 4>(a8, w, o, wv * (K4 / 4), acc);
+#pragma unroll
+        for (int v = 0; v < V; ++v) part[wv * N + o + v] = acc[v];
+    }
+    __syncthreads();
+}
+
 struct QShared {
-    int r[512], nrm[512];
-    int a8[256];
-    int xz[2048];
-    int xs[1024];
-    int gate[1024];
+    alignas(16) int r[512];                      // (16-byte aligned: read four at a time)
+    alignas(16) int nrm[512];
+    alignas(16) int a8[256];
+    alignas(16) int xz[2048];
+    alignas(16) int xs[1024];
+    alignas(16) int gate[1024];
     int dbc[64];
     int f[256], cx[256];
     ll red[4];
@@ -242,12 +376,13 @@ struct QShared {
     int sym;
     uint32_t D;
     uint64_t v;
-    ll t16[16], lnc[17];         // the exponential's and logarithm's tables, read with divergent indexes
+    unsigned t16[16];
+    ll lnc[17];         // the exponential's and logarithm's tables, read with divergent indexes
 };
 
 // DM = d_model: every loop bound below is a compile-time constant
 template <int DM>
-__global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
+__global__ __launch_bounds__(NT, 4) void k_int_chunk(QArgs a, QJob j, int mode) {
     __shared__ QShared sh;
     const int t = threadIdx.x;
     const ll c = blockIdx.x;
@@ -259,7 +394,7 @@ __global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
     }
     int* st = j.state + c * j.state_words;
     for (ll i = t; i < j.state_words; i += NT) st[i] = 0;
-    if (t < 16) sh.t16[t] = kT16[t];
+    if (t < 16) sh.t16[t] = (unsigned)kT16[t];
     if (t < 17) sh.lnc[t] = kLNC[t];
     const ll off = j.chunk_off[c];
     int y = mode == MODE_DECODE ? j.first[c] : j.in[off];
@@ -287,52 +422,80 @@ __global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
             const QLayer& L = a.L[l];
             int* win = st + (ll)l * 3 * Di;
             int* hst = st + (ll)a.n_layers * 3 * Di + (ll)l * QN * Di;
-            // LayerNorm, in_proj
-            int_ln(sh.r, sh.nrm, L.ln_g, L.ln_b, D, sh.red);
-            int e = int_q8(sh.nrm, D, sh.a8, sh.red);
-            for (int o = t; o < 2 * Di; o += NT) {
-                int acc = 0;
-#pragma unroll 16
-                for (int k = 0; k < D / 4; ++k) acc = __builtin_amdgcn_sdot4(sh.a8[k], L.in_w[k * 2 * Di + o], acc, false);
-                sh.xz[o] = (int)clampll(rsh(acc, L.in_p[o] - e), -SAT23, SAT23);
+            // LayerNorm, in_proj; the conv's window and weights are requested first
+            constexpr int CPT = (Di + NT - 1) / NT;      // channels of a thread
+            int cwin[CPT][3], ccw[CPT][5];
+#pragma unroll
+            for (int q = 0; q < CPT; ++q) {
+                const int d = t + NT * q;
+                if (Di % NT && d >= Di) break;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) cwin[q][k] = win[k * Di + d];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) ccw[q][k] = L.cw[k * Di + d];
+                ccw[q][4] = L.cb[d];
+            }
+            int_ln<D>(sh.r, sh.nrm, L.ln_g, L.ln_b, sh.red);
+            int e = int_q8(sh.nrm, D, sh.a8, sh.redi);
+            constexpr int VI = 2 * Di / NT < 4 ? 2 * Di / NT : 4;   // adjacent outputs of a thread
+            for (int o = VI * t; o < 2 * Di; o += VI * NT) {
+                int acc[VI];
+                dot_cols<VI, 2 * Di, D / 4>(sh.a8, L.in_w, o, 0, acc);
+#pragma unroll
+                for (int v = 0; v < VI; ++v) sh.xz[o + v] = (int)clampll(rsh(acc[v], L.in_p[o + v] - e), -SAT23, SAT23);
             }
             __syncthreads();
             // causal conv over x_{t-3} .. x_t, SiLU
-            for (int d = t; d < Di; d += NT) {
+#pragma unroll
+            for (int q = 0; q < CPT; ++q) {
+                const int d = t + NT * q;
+                if (Di % NT && d >= Di) break;
                 const ll x = sh.xz[d];
-                const ll w0 = win[d], w1 = win[Di + d], w2 = win[2 * Di + d];
-                const ll u = clampll(rsh((ll)L.cw[d] * w0 + (ll)L.cw[Di + d] * w1 + (ll)L.cw[2 * Di + d] * w2 +
-                                             (ll)L.cw[3 * Di + d] * x, 14) + L.cb[d], -SAT23, SAT23);
-                win[d] = (int)w1;
-                win[Di + d] = (int)w2;
+                const ll u = clampll(rsh(mul32(ccw[q][0], cwin[q][0]) + mul32(ccw[q][1], cwin[q][1]) +
+                                             mul32(ccw[q][2], cwin[q][2]) + mul32(ccw[q][3], x), 14) + ccw[q][4], -SAT23, SAT23);
+                win[d] = cwin[q][1];
+                win[Di + d] = cwin[q][2];
                 win[2 * Di + d] = (int)x;
                 sh.xs[d] = (int)silu_q12(u, sh.t16);
             }
+            // the scan's states and A of the thread's first channel, needed after x_proj
+            int hv[QN], Av[QN];
+            auto load_state = [&](int n, int d) {
+                Av[n] = L.A[n * Di + d];
+                hv[n] = hst[n * Di + d];
+            };
+            if (Di % NT == 0 || t < Di) {
+#pragma unroll
+                for (int n = 0; n < QN; ++n) load_state(n, t);
+            }
             __syncthreads();
-            // x_proj: one wave per output, the lanes split the inputs
-            e = int_q8(sh.xs, Di, sh.a8, sh.red);
-            {
-                const int wv = t >> 6, ln = t & 63;
-                for (int o = wv; o < NO; o += NT / 64) {
-                    int acc = 0;
-                    for (int k = ln; k < Di / 4; k += 64) acc = __builtin_amdgcn_sdot4(sh.a8[k], L.x_w[o * (Di / 4) + k], acc, false);
-                    for (int m = 32; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
-                    if (ln == 0) sh.dbc[o] = (int)clampll(rsh(acc, L.x_p[o] - e), -SAT23, SAT23);
-                }
+            // x_proj: four threads per output, each a quarter of the inputs, 16 at
+            // a time (a wave per output and a shuffle tree took 22k cycles a
+            // layer of four chunks a CU, 7k so)
+            e = int_q8(sh.xs, Di, sh.a8, sh.redi);
+            if (t < 4 * NO) {
+                const int o = t >> 2, part = t & 3;
+                const int4* wp = reinterpret_cast<const int4*>(L.x_w) + o * (Di / 16) + part;
+                const int4* ap = reinterpret_cast<const int4*>(sh.a8) + part;
+                int acc = 0;
+#pragma unroll
+                for (int k = 0; k < Di / 64; ++k) acc = dot16(ap[4 * k], wp[4 * k], acc);
+                acc += __shfl_xor(acc, 1);
+                acc += __shfl_xor(acc, 2);
+                if (part == 0) sh.dbc[o] = (int)clampll(rsh(acc, L.x_p[o] - e), -SAT23, SAT23);
             }
             __syncthreads();
             // dt_proj (its R inputs quantised by every thread alike), softplus,
             // the scan and the gate, one channel per thread
             {
-                ll m = 0;
-                for (int k = 0; k < R; ++k) { ll v = sh.dbc[k] < 0 ? -(ll)sh.dbc[k] : sh.dbc[k]; m = v > m ? v : m; }
+                int m = 0;
+                for (int k = 0; k < R; ++k) { const int v = sh.dbc[k] < 0 ? -sh.dbc[k] : sh.dbc[k]; m = v > m ? v : m; }
                 const int bl = bitlen((unsigned)m);
                 const int e3 = bl > 7 ? bl - 7 : 0;
                 int dq[8];
                 for (int k4 = 0; k4 < R / 4; ++k4) {
                     unsigned pk = 0;
-                    for (int b = 0; b < 4; ++b)
-                        pk |= ((unsigned)clampll(rsh(sh.dbc[4 * k4 + b], e3), -127, 127) & 0xFFu) << (8 * b);
+                    for (int b = 0; b < 4; ++b) pk |= q8(sh.dbc[4 * k4 + b], e3) << (8 * b);
                     dq[k4] = (int)pk;
                 }
                 for (int d = t; d < Di; d += NT) {
@@ -342,26 +505,15 @@ __global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
                     const ll dl = softplus_q20(v, sh.t16, sh.lnc);
                     const ll xs = sh.xs[d];
                     const ll dx = rsh(mul32(dl, xs), 20);           // dl <= 2^30, |xs| < 2^23
+                    const int dh = (int)(dx >> 8), d8 = (int)(dx & 255);
                     ll ys = 0;
-                    // four states at a time: their A and h loads go out together (h is
-                    // written back in the same pass, so the compiler would not move the
-                    // next loads above those stores by itself)
-                    for (int n0 = 0; n0 < QN; n0 += 4) {
-                        int Av[4], hv[4];
+                    // (each state's registers take the next channel's as they become free)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            Av[i] = L.A[(n0 + i) * Di + d];
-                            hv[i] = hst[(n0 + i) * Di + d];
-                        }
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int n = n0 + i;
-                            // dl <= 2^30, |A| <= 2^24, dA <= 2^30, |h| < 2^31: 32-bit operands
-                            const ll dA = exp_neg(rsh(mul32(dl, Av[i]), 8), sh.t16);
-                            const ll hn = clampll(rsh(mul32(dA, hv[i]), 30) + rsh(dx * (ll)sh.dbc[R + n], 8), -SAT31, SAT31);
-                            hst[n * Di + d] = (int)hn;
-                            ys += mul32(sh.dbc[R + QN + n], hn);
-                        }
+                    for (int n = 0; n < QN; ++n) {
+                        const int hn = state_next(exp_prod((int)dl, Av[n], sh.t16), hv[n], dh, d8, sh.dbc[R + n]);
+                        hst[n * Di + d] = hn;
+                        ys = mad_i(sh.dbc[R + QN + n], hn, ys);
+                        if (Di > NT && d + NT < Di) load_state(n, d + NT);
                     }
                     const ll yv = clampll(rsh(ys, 16) + rsh(mul32(L.Dq[d], xs), 12), -SAT23, SAT23);
                     sh.gate[d] = (int)clampll(rsh(mul32(yv, silu_q12(sh.xz[Di + d], sh.t16)), 12), -SAT23, SAT23);
@@ -369,22 +521,20 @@ __global__ __launch_bounds__(NT) void k_int_chunk(QArgs a, QJob j, int mode) {
             }
             __syncthreads();
             // out_proj and the residual
-            e = int_q8(sh.gate, Di, sh.a8, sh.red);
+            e = int_q8(sh.gate, Di, sh.a8, sh.redi);
+            dot_split<D, Di / 4>(sh.a8, L.out_w, sh.xz);
             for (int o = t; o < D; o += NT) {
-                int acc = 0;
-#pragma unroll 16
-                for (int k = 0; k < Di / 4; ++k) acc = __builtin_amdgcn_sdot4(sh.a8[k], L.out_w[k * D + o], acc, false);
+                const int acc = (sh.xz[o] + sh.xz[D + o]) + (sh.xz[2 * D + o] + sh.xz[3 * D + o]);
                 const ll pr = clampll(rsh(acc, L.out_p[o] - e), -SAT23, SAT23);
                 sh.r[o] = (int)clampll(sh.r[o] + pr, -SAT23, SAT23);
             }
             __syncthreads();
         }
         // final LayerNorm, head: thread t owns symbol t
-        int_ln(sh.r, sh.nrm, a.nf_g, a.nf_b, D, sh.red);
-        const int e = int_q8(sh.nrm, D, sh.a8, sh.red);
-        int acc = 0;
-#pragma unroll 16
-        for (int k = 0; k < D / 4; ++k) acc = __builtin_amdgcn_sdot4(sh.a8[k], a.head_w[k * 256 + t], acc, false);
+        int_ln<D>(sh.r, sh.nrm, a.nf_g, a.nf_b, sh.red);
+        const int e = int_q8(sh.nrm, D, sh.a8, sh.redi);
+        dot_split<256, D / 4>(sh.a8, a.head_w, sh.xz);
+        const int acc = (sh.xz[t] + sh.xz[256 + t]) + (sh.xz[512 + t] + sh.xz[768 + t]);
         const ll lg = clampll(rsh(acc, a.head_p[t] - e) + a.head_b[t], -SAT23, SAT23);
         // integer softmax and histogram
         const ll mx = blk_max(lg, sh.red);
