@@ -780,13 +780,16 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
         if (l == a.n_layers) lnp.load(a.norm_f_w, a.norm_f_b, wl, wv);
         else lnp.load(a.layers[l].norm_w, a.layers[l].norm_b, wl, wv);
     };
-    // step position of slot g as a scalar (-1: idle), and its conv window's slot
-    auto spos = [&](int g) { return __builtin_amdgcn_readfirstlane(pos_s[g]); };
     pre_layer(0);
     for (long long it = 0; it < a.max_steps; ++it) {
+        // step position of every slot (-1: idle) as scalars, for the whole step
+        int spos[G];
         bool any = false;
 #pragma unroll
-        for (int g = 0; g < G; ++g) any = any || pos_s[g] >= 0;
+        for (int g = 0; g < G; ++g) {
+            spos[g] = __builtin_amdgcn_readfirstlane(pos_s[g]);
+            any = any || spos[g] >= 0;
+        }
         if (!any) break;                                 // uniform: read after a barrier
         // the decoding wave requests its next 8 payload bytes now, one per
         // lane (lane i: byte cur + i, zero past the payload); nothing waits
@@ -829,7 +832,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 if (!SL) {
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
-                        const int p = spos(g);
+                        const int p = spos[g];
 #pragma unroll
                         for (int k = 0; k < KCONV - 1; ++k) {
                             float v = 0.0f;
@@ -884,7 +887,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 if (Di % FNT && d >= Di) break;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    const int p = spos(g);
+                    const int p = spos[g];
                     if (p < 0) continue;
                     float t[KCONV - 1];
                     float* cl = cst_s + (l * G + g) * (KCONV - 1) * Di + d;
@@ -915,7 +918,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
             };
             auto load_slot = [&](int d, int g) {
                 float (&h)[NSTATE] = hp[g % DP];
-                const bool live = spos(g) > 0;
+                const bool live = spos[g] > 0;
                 if (SL) {
                     const float* hst = hst_s + (l * G + g) * NSTATE * Di;
 #pragma unroll
@@ -963,7 +966,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 }
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    if (spos(g) >= 0) {
+                    if (spos[g] >= 0) {
                         float (&h)[NSTATE] = hp[g % DP];
                         const float* dbc = dbc_s + g * NO;
                         const float gv = scan_update(h, dt_of<RR>(dbc, dtw, dtb), xs_s[g * S::XSR + d], dbc + RR,
