@@ -577,7 +577,7 @@ DEVI void fused_ln(const float* __restrict__ r_s, float* __restrict__ a_s, int d
 // as on 16.  One lane of d_model 256: 6.8k cycles a step.
 template <int Di, int NFX, int NO, int G>
 struct XRows {
-    static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : 4;
+    static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : NG > 8 ? 8 : 4;
     static_assert(G <= 2 && NFX <= 4 && FNW == 8, "a wave per (fragment, row)");
     f32x4 ring[PG][4];
     DEVI static bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
