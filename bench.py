@@ -78,10 +78,11 @@ def per_byte_work(D: int = D_MODEL, L: int = N_LAYERS):
     return proj, mixer, trans
 
 
-def state_bytes_per_lane(D: int = D_MODEL, L: int = N_LAYERS):
-    """FP32 conv window (3 taps) and scan state (16 per channel) of one stream
-    over all layers."""
-    return L * 2 * D * (3 + 16) * 4
+def state_bytes_per_step(D: int = D_MODEL, L: int = N_LAYERS):
+    """FP32 state traffic of one decoding step of one stream over all layers:
+    the conv window's 3 taps read and 1 written (a ring), the scan state (16
+    per channel) read and written."""
+    return L * 2 * D * (3 + 1 + 16 + 16) * 4
 
 
 def traffic_record(kernel: str, workload: str):
@@ -407,7 +408,7 @@ def main():
         g = tuned["fused_lanes"]
         kname = f"k_dec_fused<{ {'f32': 0, 'bf16': 1, 'fp8': 2}[args.dtype] }, {Dm}, {2 * Dm}, " \
                 f"{(Dm + 15) // 16}, {g}, {'true' if g == 1 and Dm <= 256 else 'false'}>"
-        per_pos = 2.0 * state_bytes_per_lane(Dm, Lm) + 1.0 + coded * 1.0 / positions
+        per_pos = float(state_bytes_per_step(Dm, Lm)) + 1.0 + coded * 1.0 / positions
         hbm = per_pos * positions
         achieved = hbm / avg_s / 1e9
         rec = traffic_record(kname, f"{args.dtype}_{n_chunks}x{args.len_lo // 1024}-{args.len_hi // 1024}KiB")
@@ -416,8 +417,8 @@ def main():
             "frac": achieved / HBM_PEAK, "traffic": rec["hbm_bytes_per_launch"] if rec else None,
             "kernel": kname, "avg_launch_us": avg_s * 1e6, "positions_per_launch": positions,
             "bytes_per_position": per_pos, "work_per_launch": hbm,
-            "bytes_note": "per decoded byte: FP32 conv window and scan state of every layer read and written "
-                          f"({2 * state_bytes_per_lane(Dm, Lm)} B), the decoded byte, the payload bits / 8",
+            "bytes_note": "per decoded byte: FP32 conv window and scan state of every layer, as read and written "
+                          f"({state_bytes_per_step(Dm, Lm)} B), the decoded byte, the payload bits / 8",
             "mfma": {"flops_per_position": proj, "achieved_tflops": proj * positions / avg_s / 1e12,
                      "peak_tflops": PEAK[args.dtype], "frac": proj * positions / avg_s / 1e12 / PEAK[args.dtype]},
             "exp_valu": {"transcendentals_per_position": trans, "achieved_per_s": trans * positions / avg_s,
@@ -436,7 +437,7 @@ def main():
                            "unit": "TFLOP/s", "frac": achieved / pk, "traffic": None,
                            "kernel": f"{phase} {KIND_NAMES[kind]}", "avg_launch_us": avg_s * 1e6}
     # the round trip against the per-byte ceilings of the method's own work
-    hbm_dec = HBM_PEAK * 1e9 / (2.0 * state_bytes_per_lane(Dm, Lm)) / 1e6
+    hbm_dec = HBM_PEAK * 1e9 / state_bytes_per_step(Dm, Lm) / 1e6
     res["ceilings_MBps"] = {"mfma": PEAK[args.dtype] * 1e12 / proj / 1e6, "exp_valu": EXP_PEAK / trans / 1e6,
                             "decode_hbm_state": hbm_dec, "decode_frac_of_hbm_state": dec_MBps / hbm_dec,
                             "decode_frac_of_exp_valu": dec_MBps / (EXP_PEAK / trans / 1e6),
