@@ -18,7 +18,8 @@
 //                  (f32: 16x16x4 in k steps of 4; bf16: 16x16x32 in k steps of
 //                  32; fp8: 16x16x32 fp8 with the same per-row and per-tensor
 //                  scales; from zero), the lane's row placed in a 16-row tile
-//                  whose other rows are zero (MFMA rows are independent);
+//                  (MFMA rows are independent), or for f32 and one or two
+//                  lanes the fmaf sequence that this MFMA is;
 //   conv, x_proj, dt, scan, gate, histogram, coder: the shared device
 //                  functions with the same operands in the same order.
 //
@@ -131,10 +132,6 @@ DEVI float4 gld(const float4* p) {
     const f32x4 v = *(const __attribute__((address_space(1))) f32x4*)p;
     return make_float4(v.x, v.y, v.z, v.w);
 }
-DEVI uint4 gld(const uint4* p) {
-    const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)p;
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 DEVI uint2 gld(const uint2* p) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     const u32x2 v = *(const __attribute__((address_space(1))) u32x2*)p;
@@ -158,8 +155,6 @@ DEVI float4 bf4(uint2 v) {
     return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                        __uint_as_float(v.y & 0xFFFF0000u));
 }
-DEVI float4 xq_f(float4 v) { return v; }
-DEVI float4 xq_f(uint2 v) { return bf4(v); }
 // dt_proj weights of channel d: float [R][Di] copy, or in BF16 mode the bf16
 // parameter [Di][R] (R / 4 loads of four)
 template <int DT, int RR>
@@ -191,13 +186,6 @@ struct DtW {
     }
 };
 static_assert(sizeof(uint16_t) == 2, "bf16 bits");
-
-// base + an unsigned 32-bit byte offset: a scalar base and a per-lane offset
-// map onto the scalar-base addressing mode of the global loads
-template <typename T>
-DEVI T gld_off(const T* base, uint32_t byte_off) {
-    return gld(reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_off));
-}
 
 constexpr int FNT = 512;              // threads per workgroup
 constexpr int FNW = FNT / 64;         // waves
@@ -706,7 +694,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
     uint8_t* g8_s = reinterpret_cast<uint8_t*>(sm + S::g8);
     float* cst_s = sm + S::total;                                  // SL only
     float* hst_s = cst_s + (size_t)a.n_layers * G * (KCONV - 1) * Di;
-    __shared__ int pos_s[G], chunk_s[G];
+    __shared__ int pos_s[G];
     __shared__ float hb_s[VOCAB];                 // head bias, read every step
     __shared__ unsigned am_ln[G], am_g[G];        // fp8: row maxima of the LayerNorm output and of g
     // wave index as a wave-uniform (scalar) value: weight addresses that depend
@@ -767,7 +755,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 const float* er = a.E + (long long)y * D;
                 for (int kk = wl; kk < D; kk += 64) r_s[gl * D + kk] = er[kk];
             }
-            if (wl == 0) { pos_s[gl] = q.pos; chunk_s[gl] = q.c; }
+            if (wl == 0) pos_s[gl] = q.pos;
         }
     }
     __syncthreads();
@@ -1069,10 +1057,7 @@ __global__ __launch_bounds__(FNT) void k_dec_fused(FusedArgs a) {
                 const float* er = a.E + (long long)ny * D;
                 for (int kk = wl; kk < D; kk += 64) r_s[gl * D + kk] = er[kk];
             }
-            if (wl == 0) {
-                pos_s[gl] = npos;
-                chunk_s[gl] = nc;
-            }
+            if (wl == 0) pos_s[gl] = npos;
             q.c = nc;
             q.pos = npos;
             ++q.lstep;
