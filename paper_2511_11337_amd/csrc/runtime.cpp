@@ -998,6 +998,23 @@ int decode_fused(const boa_model* m, const boa_run_opts& o, const DecHost& H, co
     DecBufs B;
     Arena meas;
     B.carve(meas, m, F, n);
+    // Up to 511 lanes a region too small for lane state in device memory may
+    // still hold the call with one lane per workgroup, its state in LDS (two
+    // rounds of workgroups past 256 lanes).
+    if (ws && ws_bytes < meas.used && o.fused_lanes == 0 && F.G == 2 && F.P.lanes < 512) {
+        boa_run_opts one = o;
+        one.fused_lanes = 1;
+        FusedShape F1;
+        rc = fused_shape(m, one, H.steps, F1);
+        if (rc) return rc;
+        Arena m1;
+        DecBufs B1;
+        B1.carve(m1, m, F1, n);
+        if (m1.used <= ws_bytes) {
+            F = std::move(F1);
+            meas = m1;
+        }
+    }
     DevBuf own;
     Arena A;
     if (ws) {

@@ -43,3 +43,20 @@ def test_decode_lanes_around_a_full_chip(lanes):
     data = records_f32_mix(int(lens.sum()), lanes)
     print(f"[gpu] decode of {lanes} lanes", flush=True)
     assert np.array_equal(_round_trip(m, data, lens, "bf16"), data)
+
+
+def test_small_region_takes_one_lane_per_workgroup():
+    """300 lanes choose two lanes per workgroup and state in device memory; a region that holds only the one-lane
+    form (state in LDS) still decodes, one byte less is refused."""
+    import paper_2511_11337_amd as boa
+    cfg = ModelConfig(64, 2)
+    m = boa.Model(cfg, init_weights(cfg, 5))
+    lens = np.full(300, 11, dtype=np.uint64)
+    data = records_f32_mix(int(lens.sum()), 9)
+    small = boa.workspace_size(m, lens, "decode", dtype="bf16", fused_lanes=1)
+    assert small < boa.workspace_size(m, lens, "decode", dtype="bf16")
+    print(f"[gpu] decode of 300 lanes in {small} bytes", flush=True)
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    assert np.array_equal(_round_trip(m, data, lens, "bf16", workspace=ws), data)
+    with pytest.raises(boa.BoaError):
+        _round_trip(m, data, lens, "bf16", workspace=ws[:small - 1])
