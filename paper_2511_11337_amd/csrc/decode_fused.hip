@@ -216,6 +216,15 @@ template <> struct BLoad<0> { using T = float4; static constexpr int KPL = 16; }
 template <> struct BLoad<1> { using T = uint4; static constexpr int KPL = 32; };
 template <> struct BLoad<2> { using T = uint4; static constexpr int KPL = 64; };   // fp8: two k steps of 32
 
+// A wave without work issues the same loads as the others (a branch would keep
+// its ring's registers alive around it, and spilled up to 1.4 KB a thread): its
+// vector offset is the buffer's range, so that the range check, which counts
+// the vector offset, drops them and they read as zero; its scalar offset is
+// that of an in-range load, because whether the check counts the scalar offset
+// is the hardware's matter.  load_ok: every 16 bytes of a load at (vo, so) lie
+// in the range or are dropped; checked for every wave when this is compiled.
+constexpr bool load_ok(int vo, int so, int range) { return vo >= range || (so >= 0 && vo >= 0 && vo + so + 16 <= range); }
+
 // The NF fragments of W are dealt to the waves (wave w owns w, w + 8, ...),
 // at most 8 per pass.  issue() requests the first ring of B loads of the
 // wave's first pass; it can be called a phase early so the loads arrive while
@@ -236,18 +245,30 @@ struct FGemm {
 
     // Weight loads are raw buffer loads: the fragment offset (wave-uniform,
     // f0 comes from a scalar) goes in a scalar register, the lane offset is
-    // the one vector register, so a load costs no address arithmetic;
-    // fragments past the matrix (nf >= NF) lie outside the buffer's range and
-    // read as zero.
+    // the one vector register, so a load costs no address arithmetic.
     static constexpr int ES = DT == 0 ? 4 : (DT == 1 ? 2 : 1);   // bytes per weight
+    static constexpr int RANGE = 16 * NF * K * ES;               // the whole fragment-ordered matrix (16 NF x K)
+    static_assert(NF % FNW == 0 || NF < FNW, "a wave has work in every fragment of a pass or in none");
+    __host__ __device__ static constexpr bool idle(int f0) { return NF < FNW && f0 >= NF; }
+    __host__ __device__ static constexpr int voff(int f0, int wl) { return idle(f0) ? RANGE : wl * (int)sizeof(BT); }
+    __host__ __device__ static constexpr int soff(int f0, int st, int j) {
+        return (((idle(f0) ? 0 : f0) + FNW * j) * SK + st) * 64 * (int)sizeof(BT);
+    }
+    static constexpr bool loads_ok() {
+        for (int p = 0; p < FALL; p += FPW)
+            for (int wv = 0; wv < FNW; ++wv)
+                for (int j = 0; j < FPW; ++j)
+                    for (int wl = 0; wl < 64; wl += 63)
+                        if (!load_ok(voff(wv + FNW * p, wl), soff(wv + FNW * p, SK - 1, j), RANGE)) return false;
+        return true;
+    }
     DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
-        // base, stride 0, range = the whole fragment-ordered matrix (16 NF x K)
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, 16 * NF * K * ES, 0x00020000);
+        static_assert(loads_ok(), "loads past the matrix");
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, RANGE, 0x00020000);   // base, stride 0
     }
     DEVI static BT ld(__amdgpu_buffer_rsrc_t r, int f0, int st, int j, int wl) {
-        const int nf = f0 + FNW * j;
         typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(r, wl * (int)sizeof(BT), (nf * SK + st) * 64 * (int)sizeof(BT), 0);
+        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(f0, wl), soff(f0, st, j), 0);
         BT o;
         __builtin_memcpy(&o, &v, sizeof(BT));
         return o;
@@ -385,34 +406,47 @@ struct RGemm {
     static constexpr int SK = K / 16, PW = 4 / SP, P = PW < SK ? PW : SK;
     static_assert(NF % 4 == 0 && (NS <= FNW || NS % FNW == 0) && SPW % SP == 0 && SK % P == 0, "whole sets and rings");
     f32x4 ring[P][SP][4];
-    DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, 16 * NF * K * 4, 0x00020000);
+    static constexpr int RANGE = 16 * NF * K * 4;
+    __host__ __device__ static constexpr bool idle(int wv) { return wv >= NS; }
+    __host__ __device__ static constexpr int voff(int wv, int wl) {
+        return idle(wv) ? RANGE : ((wl >> 4) * SK * 64 + (wl & 15)) * 16;
     }
-    DEVI static f32x4 ld(__amdgpu_buffer_rsrc_t r, int set, int q, int lk, int voff) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, ((4 * set * SK + q) * 64 + 16 * lk) * 16, 0);
+    __host__ __device__ static constexpr int soff(int wv, int s, int q, int lk) {   // set wv + 8 s
+        return ((4 * ((idle(wv) ? 0 : wv) + FNW * s) * SK + q) * 64 + 16 * lk) * 16;
+    }
+    static constexpr bool loads_ok() {
+        for (int wv = 0; wv < FNW; ++wv)
+            for (int s = 0; s < SPW; ++s)
+                for (int wl = 0; wl < 64; wl += 63)
+                    if (!load_ok(voff(wv, wl), soff(wv, s, SK - 1, 3), RANGE)) return false;
+        return true;
+    }
+    DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
+        static_assert(loads_ok(), "loads past the matrix");
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, RANGE, 0x00020000);
+    }
+    DEVI static f32x4 ld(__amdgpu_buffer_rsrc_t r, int wv, int s, int q, int lk, int vo) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, vo, soff(wv, s, q, lk), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
         return o;
     }
-    DEVI static int voff(int wl) { return ((wl >> 4) * SK * 64 + (wl & 15)) * 16; }
-    // (waves without a set load past the buffer's range, which reads as zero:
-    // a branch here would keep the ring's registers alive around it)
     DEVI void issue(const void* Wf, int wv, int wl) {
         const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
-        const int vo = voff(wl);
+        const int vo = voff(wv, wl);
 #pragma unroll
         for (int u = 0; u < P; ++u)
 #pragma unroll
             for (int s = 0; s < SP; ++s)
 #pragma unroll
-                for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv + FNW * s, u, lk, vo);
+                for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv, s, u, lk, vo);
     }
     template <class F>
     DEVI void run(const float* __restrict__ A, int as, const void* __restrict__ Wf, int wl, int wv, const unsigned*,
                   const int*, F&& f) {
-        if (wv >= NS) return;
+        if (idle(wv)) return;
         const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
-        const int vo = voff(wl);
+        const int vo = voff(wv, wl);
 #pragma unroll 1
         for (int p = 0; p < SPW; p += SP) {
             float acc[SP][G];
@@ -433,7 +467,7 @@ struct RGemm {
 #pragma unroll
                         for (int s = 0; s < SP; ++s)
 #pragma unroll
-                            for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv + FNW * (pn + s), qn + u, lk, vo);
+                            for (int lk = 0; lk < 4; ++lk) ring[u][s][lk] = ld(r, wv, pn + s, qn + u, lk, vo);
                     }
 #pragma unroll
                     for (int g = 0; g < G; ++g)
@@ -568,13 +602,25 @@ struct XRows {
     static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : NG > 8 ? 8 : 4;
     static_assert(G <= 2 && NFX <= 4 && FNW == 8, "a wave per (fragment, row)");
     f32x4 ring[PG][4];
-    DEVI static bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
+    static constexpr int RANGE = 16 * NFX * Di * 4;
+    __host__ __device__ static constexpr bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
+    __host__ __device__ static constexpr int voff(int wv, int wl) {
+        return mine(wv) ? ((wl >> 4) * 64 + (wl & 15)) * 16 : RANGE;
+    }
+    __host__ __device__ static constexpr int soff(int wv, int i, int lk) {
+        return (((mine(wv) ? wv & 3 : 0) * SQ + 4 * i) * 64 + 16 * lk) * 16;
+    }
+    static constexpr bool loads_ok() {
+        for (int wv = 0; wv < FNW; ++wv)
+            for (int wl = 0; wl < 64; wl += 63)
+                if (!load_ok(voff(wv, wl), soff(wv, NG - 1, 3), RANGE)) return false;
+        return true;
+    }
     DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int lk) {
+        static_assert(loads_ok(), "loads past the matrix");
         const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, 16 * NFX * Di * 4, 0x00020000);
-        const int f = mine(wv) ? wv & 3 : NFX;               // past the range: reads as zero
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, ((wl >> 4) * 64 + (wl & 15)) * 16,
-                                                              ((f * SQ + 4 * i) * 64 + 16 * lk) * 16, 0);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, RANGE, 0x00020000);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wv, wl), soff(wv, i, lk), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
         return o;
@@ -618,11 +664,23 @@ template <int Di, int NFX, int NO, int G>
 struct XTile {
     static constexpr int SQ = Di / 16, NG = SQ / 4, PG = NG < 4 ? NG : 4, PN = 16 * NFX;
     f32x4 ring[PG][2];
-    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {   // fragments past NFX read as zero
+    static constexpr int RANGE = 16 * NFX * Di * 4;
+    __host__ __device__ static constexpr bool mine(int wv) { return (wv & 3) < NFX; }
+    __host__ __device__ static constexpr int voff(int wv, int wl) { return mine(wv) ? wl * 16 : RANGE; }
+    __host__ __device__ static constexpr int soff(int wv, int i, int c) {
+        return ((mine(wv) ? wv & 3 : 0) * SQ + 4 * i + 2 * (wv >> 2) + c) * 1024;
+    }
+    static constexpr bool loads_ok() {
+        for (int wv = 0; wv < FNW; ++wv)
+            for (int wl = 0; wl < 64; wl += 63)
+                if (!load_ok(voff(wv, wl), soff(wv, NG - 1, 1), RANGE)) return false;
+        return true;
+    }
+    DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {
+        static_assert(loads_ok(), "loads past the matrix");
         const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, 16 * NFX * Di * 4, 0x00020000);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, wl * 16,
-                                                              ((wv & 3) * SQ + 4 * i + 2 * (wv >> 2) + c) * 1024, 0);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, RANGE, 0x00020000);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wv, wl), soff(wv, i, c), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
         return o;
@@ -634,7 +692,7 @@ struct XTile {
             for (int c = 0; c < 2; ++c) ring[i][c] = ld(Wf, wv, wl, i, c);
     }
     DEVI void run(const float* xs, int xsr, const float* Wf, int wv, int wl, int tid, float* part, float* dbc) {
-        if ((wv & 3) < NFX) {
+        if (mine(wv)) {
             const int li = wl & 15, lk = wl >> 4;
             const float* x = xs + (li < G ? li : 0) * xsr + 32 * (wv >> 2) + lk;
             v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
