@@ -249,8 +249,11 @@ int boa_payload_layout(const uint64_t* h_chunk_len, uint64_t n, uint64_t* h_chun
  * sum -log2(f(s)/M) over each chunk's coded symbols; pass NULL to skip.
  * d_ws (device, ws_bytes >= boa_workspace_size(..., BOA_WS_ENCODE), owned by
  * the caller, contents need not be initialised) holds every buffer of the
- * call; with d_ws NULL the library allocates them for the call.  The range
- * coder runs on a second stream the call creates, ordered after `stream`.
+ * call; with d_ws NULL the library allocates them for the call.  A smaller
+ * d_ws is used with shorter tiles and gives the same bytes (so a region sized
+ * for the largest batch also takes smaller ones of fewer lanes), down to about
+ * half of a tile's activations; below that the call is refused (BOA_E_ARG).  The
+ * range coder runs on a second stream the call creates, ordered after `stream`.
  */
 int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const uint64_t* h_chunk_off,
                    const uint64_t* h_chunk_len, uint64_t n_chunks, const boa_run_opts* opts,

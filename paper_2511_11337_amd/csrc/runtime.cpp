@@ -585,8 +585,9 @@ struct Work {
     int lanes = 0, T = 0;
     Arena own_arena;
     DevBuf own_mem;
-    // every buffer as a piece of A
-    void carve(Arena& A, const boa_model* m, int lanes_, int T_) {
+    // every buffer as a piece of A (kept: with what the mixer's kernels pass on
+    // between them; without it the pieces only measure)
+    void carve(Arena& A, const boa_model* m, int lanes_, int T_, bool kept = true) {
         lanes = lanes_;
         T = T_;
         const Layout& L = m->lay;
@@ -594,7 +595,7 @@ struct Work {
         r.carve(A, M * L.D * 4);
         xz.carve(A, M * 2 * L.Di * 4);
         g.carve(A, M * L.Di * 4);
-        if (T > 1) {                           // the mixer's intermediates
+        if (T > 1 && kept) {                   // the mixer's intermediates
             dbc.carve(A, M * (L.R + 2 * L.N) * 4);
             if (mixer_few(L.Di, lanes)) {
                 xs.carve(A, M * L.Di * 4);
@@ -727,15 +728,19 @@ int forward_tile(const boa_model* m, Work& W, int dtype, const uint8_t* bytes, c
 // Steps per tile: about 2^17 rows, in tiles of equal length -- the rows past the
 // last step cost what live ones do (384 lanes of 1040 steps: four tiles of 341
 // are 31 % of idle rows, 32.0 ms; four of 260 take 27.0).
-int pick_tile(int lanes, long long total_steps, uint32_t req) {
+int longest_tile(int lanes, long long total_steps, uint32_t req) {
     long long T = req ? (long long)req : std::max<long long>(1, (1LL << 17) / std::max(1, lanes));
     T = std::min<long long>(T, std::max<long long>(1, total_steps));
-    T = std::min<long long>(T, 4096);
-    if (!req && total_steps > 0) {
-        const long long tiles = (total_steps + T - 1) / T;
-        T = (total_steps + tiles - 1) / tiles;
-    }
-    return (int)T;
+    return (int)std::min<long long>(T, 4096);
+}
+int equal_tile(int T, long long total_steps) {
+    if (total_steps <= 0) return T;
+    const long long tiles = (total_steps + T - 1) / T;
+    return (int)((total_steps + tiles - 1) / tiles);
+}
+int pick_tile(int lanes, long long total_steps, uint32_t req) {
+    const int T = longest_tile(lanes, total_steps, req);
+    return req ? T : equal_tile(T, total_steps);
 }
 
 bool dtype_ok(uint32_t d) { return d == BOA_DTYPE_F32 || d == BOA_DTYPE_BF16 || d == BOA_DTYPE_FP8; }
@@ -761,11 +766,11 @@ struct EncBufs {
     DevBuf d_poff, d_pcap;
     Work W;
     DevBuf cfb[2], rcb[2], rpb[2];
-    void carve(Arena& A, const boa_model* m, const HostPlan& P, size_t n_chunks, int T) {
+    void carve(Arena& A, const boa_model* m, const HostPlan& P, size_t n_chunks, int T, bool kept = true) {
         carve_plan(A, P, n_chunks, PD);
         d_poff.carve(A, n_chunks * sizeof(long long));
         d_pcap.carve(A, n_chunks * sizeof(long long));
-        W.carve(A, m, P.lanes, T);
+        W.carve(A, m, P.lanes, T, kept);
         const size_t M = (size_t)P.lanes * T;
         for (int b = 0; b < 2; ++b) {
             cfb[b].carve(A, M * 2 * 4);
@@ -781,15 +786,35 @@ std::vector<long long> chunk_steps(const uint64_t* h_chunk_len, uint64_t n) {
     return steps;
 }
 
+size_t encode_bytes(const boa_model* m, const HostPlan& P, size_t n_chunks, int T, bool kept = true) {
+    Arena meas;
+    EncBufs B;
+    B.carve(meas, m, P, n_chunks, T, kept);
+    return meas.used;
+}
 // Workspace bytes of an encode call (0 when no chunk has a coded byte).
 size_t encode_ws_bytes(const boa_model* m, const std::vector<long long>& steps, const boa_run_opts& o) {
     HostPlan P = build_plan(steps, plan_lanes(o, steps));
     if (P.lanes == 0) return 0;
-    const int T = pick_tile(P.lanes, P.total_steps, o.tile_t);
-    Arena meas;
-    EncBufs B;
-    B.carve(meas, m, P, steps.size(), T);
-    return meas.used;
+    return encode_bytes(m, P, steps.size(), pick_tile(P.lanes, P.total_steps, o.tile_t));
+}
+// The tile of a call in a region of ws_bytes that is too small for tile T; 0: the
+// region is refused.  What the mixer's kernels pass on between them makes a
+// call of few lanes up to 1.77 times as large, and tiles of equal length may be
+// little more than half of the longest, so a region sized for the largest batch
+// need not hold every smaller one with its preferred tile.  Results do not
+// depend on the tile: the longest that fits is taken, in any region that holds
+// half of the longest tile's rows without those pieces (every region sized for
+// as many bytes on more lanes does).
+int fit_tile(const boa_model* m, const HostPlan& P, size_t n_chunks, int T, uint32_t req, size_t ws_bytes) {
+    const int half = (longest_tile(P.lanes, P.total_steps, req) + 1) / 2;
+    if (ws_bytes < encode_bytes(m, P, n_chunks, half, false) || ws_bytes < encode_bytes(m, P, n_chunks, 1)) return 0;
+    int lo = 1, hi = T;                        // lo fits, hi does not
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        (encode_bytes(m, P, n_chunks, mid) <= ws_bytes ? lo : hi) = mid;
+    }
+    return req ? lo : equal_tile(lo, P.total_steps);
 }
 }  // namespace
 
@@ -820,21 +845,21 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
     if (d_ideal_bits) HIPCHK(hipMemsetAsync(d_ideal_bits, 0, n_chunks * 8, s));
     HostPlan P = build_plan(steps, plan_lanes(o, steps));
     if (P.lanes == 0) { HIPCHK(hipStreamSynchronize(s)); return BOA_OK; }
-    const int T = pick_tile(P.lanes, P.total_steps, o.tile_t);
+    int T = pick_tile(P.lanes, P.total_steps, o.tile_t);
     // device memory: the caller's workspace, else one allocation of the measured size
     EncBufs B;
-    Arena meas;
-    B.carve(meas, m, P, n_chunks, T);
+    const size_t need = encode_bytes(m, P, n_chunks, T);
     DevBuf own;
     Arena A;
     if (d_ws) {
-        if (ws_bytes < meas.used)
+        if (ws_bytes < need) T = fit_tile(m, P, n_chunks, T, o.tile_t, (size_t)ws_bytes);
+        if (T == 0)
             return fail(BOA_E_ARG, "workspace of " + std::to_string(ws_bytes) + " bytes, this call needs " +
-                                       std::to_string(meas.used) + " (boa_workspace_size)");
+                                       std::to_string(need) + " (boa_workspace_size)");
         A = Arena{static_cast<uint8_t*>(d_ws), (size_t)ws_bytes, 0, false};
     } else {
-        ALLOC(own, meas.used);
-        A = Arena{own.as<uint8_t>(), meas.used, 0, false};
+        ALLOC(own, need);
+        A = Arena{own.as<uint8_t>(), need, 0, false};
     }
     B.carve(A, m, P, n_chunks, T);
     int rc = fill_plan(P, off, steps, B.PD, s);
