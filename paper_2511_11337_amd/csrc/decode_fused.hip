@@ -398,12 +398,16 @@ struct FGemm {
 // lane % 16 of fragment lane / 16) and reads the fragment order's k = 4 j + lk
 // values as four float4; sets of four fragments are dealt to the waves.  A step
 // of one lane took 101 us with the MFMA and takes 60 so (two lanes: 123 and
-// 101; four: 135 and 148).
+// 84; four: 135 and 148).
 template <int G, int K, int NF>
 struct RGemm {
     static constexpr int NS = NF / 4, SPW = NS > FNW ? NS / FNW : 1;   // sets; per wave
     static constexpr int SP = SPW < 2 ? SPW : 2;                       // per pass
-    static constexpr int SK = K / 16, PW = 4 / SP, P = PW < SK ? PW : SK;
+    // k groups in flight; with two rows and a product of at most two rings' length
+    // one, since the compiler lays both rings and the rows' operands out at once: at
+    // d_model 128 that spilled 118 registers, 49.6 us a step of 256 workgroups
+    // (31.5 with a ring of two, 28.6 with one, 32.3 on the MFMA; d_model 64: 17.4 and 16.3)
+    static constexpr int SK = K / 16, PW = 4 / SP, P = G == 2 && SK <= 8 ? 1 : PW < SK ? PW : SK;
     static_assert(NF % 4 == 0 && (NS <= FNW || NS % FNW == 0) && SPW % SP == 0 && SK % P == 0, "whole sets and rings");
     f32x4 ring[P][SP][4];
     static constexpr int RANGE = 16 * NF * K * 4;
