@@ -920,21 +920,67 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
 
 // =================================================================== decode
 namespace {
-// Lanes per workgroup of the fused decoder.  A CU holds one workgroup (its
-// registers), and a workgroup beyond the 256th starts when another has decoded
-// all its lanes, so the fewest lanes whose workgroups are all resident at once
-// win: a step costs 33 / 54 / 72 / 103 / 187 us at 1 / 2 / 4 / 8 / 16 lanes
-// (bf16, d_model 256), 130 / 162 / 207 / 279 at 1 / 2 / 4 / 8 (fp8, 512), always
-// less than two rounds of half as many.  (384 lanes of the latter, 1022 steps:
-// 261 ms at one lane a workgroup, 164 at two.)  With more lanes than fit, the most that LDS holds.
-int pick_fused_lanes(int D, int lanes, int n_layers) {
-    int best = 1;
-    for (int g : {1, 2, 4, 8, 16}) {
-        if (g * D > 16 * 256 || fused_lds_bytes(D, g, n_layers, false) + 2048 > get_max_lds()) break;
-        best = g;
-        if ((lanes + g - 1) / g <= 256) break;
+// A step of the fused decoder in us at 1, 2, 4, 8, 16 lanes a workgroup, 256
+// workgroups (2, 2, 3, 4 layers; only the ratios within a row matter).
+constexpr float FUSED_STEP_US[3][4][5] = {
+    {{12.3f, 17.0f, 23.7f, 35.0f, 63.0f}, {19.5f, 29.4f, 40.0f, 56.3f, 86.0f},       // f32; d_model 64, 128,
+     {64.6f, 93.0f, 137.f, 162.f, 282.f}, {259.f, 292.f, 509.f, 570.f, 0.f}},        // 256, 512
+    {{11.3f, 12.5f, 17.3f, 27.2f, 58.6f}, {13.2f, 17.3f, 25.1f, 42.2f, 74.2f},       // bf16
+     {33.6f, 51.3f, 79.0f, 110.f, 191.f}, {163.f, 188.f, 236.f, 317.f, 0.f}},
+    {{12.0f, 14.7f, 21.4f, 33.3f, 66.2f}, {13.6f, 19.1f, 27.6f, 46.0f, 84.2f},       // fp8
+     {30.2f, 45.4f, 69.4f, 101.f, 184.f}, {123.f, 145.f, 204.f, 284.f, 0.f}}};
+// Workgroups that a CU holds: one of 8 waves by their registers, but two of the
+// one-lane form at d_model 64 in bf16 and fp8 (at most 128 registers; its step
+// above is the one of 512 workgroups, 9.0 and 10.2 us at 256).
+int fused_slots(int dtype, int D, int g) { return g == 1 && D == 64 && dtype != BOA_DTYPE_F32 ? 512 : 256; }
+
+// Lanes per workgroup of the fused decoder: a workgroup runs until the longest
+// of its lanes ends, and one that no CU has room for starts when another has
+// ended, in order.  The number whose workgroups, so scheduled, end first is
+// taken (the fewest among equals), from the measured steps above.  384 lanes of equal
+// length (fp8, d_model 512, 1022 steps): 261 ms at one lane a workgroup, in two rounds,
+// 164 at two.  384 lanes of 8 to 128 steps, longest first (f32, d_model 128): the second
+// round fits behind the first one's short lanes, 2.6 ms at one, 3.9 at two.  5000
+// equal lanes (bf16, d_model 256): 332 us a step at 16, in two rounds, 296 at 8, in three.
+int pick_fused_lanes(int dtype, int D, const std::vector<long long>& load, int n_layers, size_t max_lds) {
+    const int lanes = (int)load.size(), di = D == 64 ? 0 : D == 128 ? 1 : D == 256 ? 2 : 3;
+    if (lanes <= 256) return 1;
+    int best = 1, top = 0;
+    while (top < 4 && (2 << top) * D <= 16 * 256 && fused_lds_bytes(D, 2 << top, n_layers, false) + 2048 <= max_lds) ++top;
+    double best_us = 1e300;
+    std::vector<long long> wg;
+    for (int k = top; k >= 0; --k) {
+        const int g = 1 << k, slots = fused_slots(dtype, D, g);
+        const double us = FUSED_STEP_US[dtype == BOA_DTYPE_BF16 ? 1 : dtype == BOA_DTYPE_FP8 ? 2 : 0][di][k];
+        wg.clear();
+        for (int l = 0; l < lanes; l += g)
+            wg.push_back(*std::max_element(load.begin() + l, load.begin() + std::min(lanes, l + g)));
+        long long end = *std::max_element(wg.begin(), wg.end());
+        // no schedule ends before the longest workgroup or the average slot does
+        const long long sum = std::accumulate(wg.begin(), wg.end(), 0LL);
+        if (us * (double)std::max(end, sum / slots) > best_us) continue;
+        if ((int)wg.size() > slots) {
+            std::priority_queue<long long, std::vector<long long>, std::greater<long long>> busy(
+                std::greater<long long>(), std::vector<long long>(wg.begin(), wg.begin() + slots));   // ends of the running ones
+            for (size_t i = slots; i < wg.size(); ++i) {
+                const long long at = busy.top() + wg[i];
+                busy.pop();
+                busy.push(at);
+                end = std::max(end, at);
+            }
+        }
+        if (us * (double)end <= best_us) { best = g; best_us = us * (double)end; }
     }
     return best;
+}
+// steps of every lane of a schedule
+std::vector<long long> lane_loads(const HostPlan& P, const std::vector<long long>& steps) {
+    std::vector<long long> v(P.lanes);
+    for (int l = 0; l < P.lanes; ++l) {
+        const int last = P.lane_first[l] + P.lane_cnt[l] - 1;
+        v[l] = P.ent_start[last] + steps[P.ent_chunk[last]];
+    }
+    return v;
 }
 
 // Schedule and launch shape of the fused decoder for these chunks.
@@ -950,7 +996,7 @@ int fused_shape(const boa_model* m, const boa_run_opts& o, const std::vector<lon
     if (F.P.lanes == 0) return BOA_OK;
     if (L.L > MAX_LAYERS) return fail(BOA_E_UNSUPPORTED, "too many layers for the fused decoder");
     int G = (int)o.fused_lanes;
-    if (G == 0) G = pick_fused_lanes(L.D, F.P.lanes, L.L);
+    if (G == 0) G = pick_fused_lanes((int)o.dtype, L.D, lane_loads(F.P, steps), L.L, get_max_lds());
     if (G != 1 && G != 2 && G != 4 && G != 8 && G != 16)
         return fail(BOA_E_ARG, "fused_lanes must be 1, 2, 4, 8 or 16");
     if (G * L.D > 16 * 256) return fail(BOA_E_ARG, "fused_lanes x d_model exceeds 16 x 256");
@@ -1004,6 +1050,12 @@ struct DecHost {
 size_t decode_ws_bytes(const boa_model* m, const boa_run_opts& o, const std::vector<long long>& steps) {
     FusedShape F;
     if (fused_shape(m, o, steps, F)) return 0;
+    // Past 256 lanes the automatic choice depends on how even the lanes are;
+    // the size does not, so that a region serves every call of as many lanes.
+    if (o.fused_lanes == 0 && F.P.lanes > 256 && F.G == 1) {
+        F.G = 2;
+        F.state_lds = false;
+    }
     Arena meas;
     DecBufs B;
     B.carve(meas, m, F, steps.size());
@@ -1026,7 +1078,7 @@ int decode_fused(const boa_model* m, const boa_run_opts& o, const DecHost& H, co
     // Up to 511 lanes a region too small for lane state in device memory may
     // still hold the call with one lane per workgroup, its state in LDS (two
     // rounds of workgroups past 256 lanes).
-    if (ws && ws_bytes < meas.used && o.fused_lanes == 0 && F.G == 2 && F.P.lanes < 512) {
+    if (ws && ws_bytes < meas.used && o.fused_lanes == 0 && F.G > 1 && F.P.lanes < 512) {
         boa_run_opts one = o;
         one.fused_lanes = 1;
         FusedShape F1;
@@ -1276,6 +1328,16 @@ extern "C" int boa_decode_dev(const boa_model* m, const uint8_t* d_payload, cons
     }
     HIPCHK(hipStreamSynchronize(s));
     return BOA_OK;
+}
+
+// The automatic lanes per workgroup of a schedule (host only), for the test of the choice; not part of the public ABI.
+extern "C" int boa_test_fused_lanes(uint32_t d_model, uint32_t n_layers, uint32_t dtype, const uint64_t* h_chunk_len,
+                                    uint64_t n_chunks, uint32_t max_lanes, uint64_t lds_bytes) {
+    const std::vector<long long> steps = chunk_steps(h_chunk_len, n_chunks);
+    boa_run_opts o{};
+    o.max_lanes = max_lanes;
+    const HostPlan P = build_plan(steps, plan_lanes(o, steps));
+    return pick_fused_lanes((int)dtype, (int)d_model, lane_loads(P, steps), (int)n_layers, lds_bytes);
 }
 
 // =================================================================== workspace and host helpers
