@@ -217,13 +217,14 @@ template <> struct BLoad<1> { using T = uint4; static constexpr int KPL = 32; };
 template <> struct BLoad<2> { using T = uint4; static constexpr int KPL = 64; };   // fp8: two k steps of 32
 
 // A wave without work issues the same loads as the others (a branch would keep
-// its ring's registers alive around it, and spilled up to 1.4 KB a thread): its
-// vector offset is the buffer's range, so that the range check, which counts
-// the vector offset, drops them and they read as zero; its scalar offset is
-// that of an in-range load, because whether the check counts the scalar offset
-// is the hardware's matter.  load_ok: every 16 bytes of a load at (vo, so) lie
-// in the range or are dropped; checked for every wave when this is compiled.
-constexpr bool load_ok(int vo, int so, int range) { return vo >= range || (so >= 0 && vo >= 0 && vo + so + 16 <= range); }
+// its ring's registers alive around it, and spilled up to 1.4 KB a thread), of the
+// first fragments, which it does not use.  Every load lies in its matrix: the
+// range check drops what a vector offset takes past the range, but whether it
+// counts the scalar offset is the hardware's matter, and a vector offset out of
+// range costs a register more than a load of what other waves load too (16 lanes of
+// d_model 256 in bf16: 193 us a step against 185).  load_ok: the 16 bytes at (vo,
+// so) lie in the range; checked for every wave when this is compiled.
+constexpr bool load_ok(int vo, int so, int range) { return so >= 0 && vo >= 0 && vo + so + 16 <= range; }
 
 // The NF fragments of W are dealt to the waves (wave w owns w, w + 8, ...),
 // at most 8 per pass.  issue() requests the first ring of B loads of the
@@ -250,7 +251,6 @@ struct FGemm {
     static constexpr int RANGE = 16 * NF * K * ES;               // the whole fragment-ordered matrix (16 NF x K)
     static_assert(NF % FNW == 0 || NF < FNW, "a wave has work in every fragment of a pass or in none");
     __host__ __device__ static constexpr bool idle(int f0) { return NF < FNW && f0 >= NF; }
-    __host__ __device__ static constexpr int voff(int f0, int wl) { return idle(f0) ? RANGE : wl * (int)sizeof(BT); }
     __host__ __device__ static constexpr int soff(int f0, int st, int j) {
         return (((idle(f0) ? 0 : f0) + FNW * j) * SK + st) * 64 * (int)sizeof(BT);
     }
@@ -259,7 +259,7 @@ struct FGemm {
             for (int wv = 0; wv < FNW; ++wv)
                 for (int j = 0; j < FPW; ++j)
                     for (int wl = 0; wl < 64; wl += 63)
-                        if (!load_ok(voff(wv + FNW * p, wl), soff(wv + FNW * p, SK - 1, j), RANGE)) return false;
+                        if (!load_ok(wl * (int)sizeof(BT), soff(wv + FNW * p, SK - 1, j), RANGE)) return false;
         return true;
     }
     DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
@@ -268,7 +268,7 @@ struct FGemm {
     }
     DEVI static BT ld(__amdgpu_buffer_rsrc_t r, int f0, int st, int j, int wl) {
         typedef unsigned int u4v __attribute__((ext_vector_type(4)));
-        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(f0, wl), soff(f0, st, j), 0);
+        const u4v v = __builtin_amdgcn_raw_buffer_load_b128(r, wl * (int)sizeof(BT), soff(f0, st, j), 0);
         BT o;
         __builtin_memcpy(&o, &v, sizeof(BT));
         return o;
@@ -412,9 +412,7 @@ struct RGemm {
     f32x4 ring[P][SP][4];
     static constexpr int RANGE = 16 * NF * K * 4;
     __host__ __device__ static constexpr bool idle(int wv) { return wv >= NS; }
-    __host__ __device__ static constexpr int voff(int wv, int wl) {
-        return idle(wv) ? RANGE : ((wl >> 4) * SK * 64 + (wl & 15)) * 16;
-    }
+    __host__ __device__ static constexpr int voff(int wl) { return ((wl >> 4) * SK * 64 + (wl & 15)) * 16; }
     __host__ __device__ static constexpr int soff(int wv, int s, int q, int lk) {   // set wv + 8 s
         return ((4 * ((idle(wv) ? 0 : wv) + FNW * s) * SK + q) * 64 + 16 * lk) * 16;
     }
@@ -422,7 +420,7 @@ struct RGemm {
         for (int wv = 0; wv < FNW; ++wv)
             for (int s = 0; s < SPW; ++s)
                 for (int wl = 0; wl < 64; wl += 63)
-                    if (!load_ok(voff(wv, wl), soff(wv, s, SK - 1, 3), RANGE)) return false;
+                    if (!load_ok(voff(wl), soff(wv, s, SK - 1, 3), RANGE)) return false;
         return true;
     }
     DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
@@ -437,7 +435,7 @@ struct RGemm {
     }
     DEVI void issue(const void* Wf, int wv, int wl) {
         const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
-        const int vo = voff(wv, wl);
+        const int vo = voff(wl);
 #pragma unroll
         for (int u = 0; u < P; ++u)
 #pragma unroll
@@ -450,7 +448,7 @@ struct RGemm {
                   const int*, F&& f) {
         if (idle(wv)) return;
         const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
-        const int vo = voff(wv, wl);
+        const int vo = voff(wl);
 #pragma unroll 1
         for (int p = 0; p < SPW; p += SP) {
             float acc[SP][G];
@@ -608,23 +606,21 @@ struct XRows {
     f32x4 ring[PG][4];
     static constexpr int RANGE = 16 * NFX * Di * 4;
     __host__ __device__ static constexpr bool mine(int wv) { return (wv & 3) < NFX && (wv >> 2) < G; }
-    __host__ __device__ static constexpr int voff(int wv, int wl) {
-        return mine(wv) ? ((wl >> 4) * 64 + (wl & 15)) * 16 : RANGE;
-    }
+    __host__ __device__ static constexpr int voff(int wl) { return ((wl >> 4) * 64 + (wl & 15)) * 16; }
     __host__ __device__ static constexpr int soff(int wv, int i, int lk) {
         return (((mine(wv) ? wv & 3 : 0) * SQ + 4 * i) * 64 + 16 * lk) * 16;
     }
     static constexpr bool loads_ok() {
         for (int wv = 0; wv < FNW; ++wv)
             for (int wl = 0; wl < 64; wl += 63)
-                if (!load_ok(voff(wv, wl), soff(wv, NG - 1, 3), RANGE)) return false;
+                if (!load_ok(voff(wl), soff(wv, NG - 1, 3), RANGE)) return false;
         return true;
     }
     DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int lk) {
         static_assert(loads_ok(), "loads past the matrix");
         const __amdgpu_buffer_rsrc_t r =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, RANGE, 0x00020000);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wv, wl), soff(wv, i, lk), 0);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wl), soff(wv, i, lk), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
         return o;
@@ -670,21 +666,20 @@ struct XTile {
     f32x4 ring[PG][2];
     static constexpr int RANGE = 16 * NFX * Di * 4;
     __host__ __device__ static constexpr bool mine(int wv) { return (wv & 3) < NFX; }
-    __host__ __device__ static constexpr int voff(int wv, int wl) { return mine(wv) ? wl * 16 : RANGE; }
     __host__ __device__ static constexpr int soff(int wv, int i, int c) {
         return ((mine(wv) ? wv & 3 : 0) * SQ + 4 * i + 2 * (wv >> 2) + c) * 1024;
     }
     static constexpr bool loads_ok() {
         for (int wv = 0; wv < FNW; ++wv)
             for (int wl = 0; wl < 64; wl += 63)
-                if (!load_ok(voff(wv, wl), soff(wv, NG - 1, 1), RANGE)) return false;
+                if (!load_ok(wl * 16, soff(wv, NG - 1, 1), RANGE)) return false;
         return true;
     }
     DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int c) {
         static_assert(loads_ok(), "loads past the matrix");
         const __amdgpu_buffer_rsrc_t r =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, RANGE, 0x00020000);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wv, wl), soff(wv, i, c), 0);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, wl * 16, soff(wv, i, c), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
         return o;
