@@ -597,7 +597,7 @@ struct Work {
         g.carve(A, M * L.Di * 4);
         if (T > 1 && kept) {                   // the mixer's intermediates
             dbc.carve(A, M * (L.R + 2 * L.N) * 4);
-            if (mixer_few(L.Di, lanes)) {
+            if (mixer_few(L.Di, lanes, T)) {
                 xs.carve(A, M * L.Di * 4);
                 dt.carve(A, M * L.Di * 4);
                 hsub.carve(A, mixer_hsub_floats(L.Di, lanes, T) * 4);
