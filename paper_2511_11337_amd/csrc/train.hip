@@ -1830,21 +1830,26 @@ int scan_bwd(const float* x, const float* dt, const float* A_log, const float* b
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
     const long long rows = (long long)B * T;
     const ScanCut q = scan_cut(B, T, Di, Tc);
-    Buf hsub, ghb, pbc, pA, pD;
-    TCHK(hsub.alloc(scan_hsub_floats(q, B, Di) * sizeof(float)));
-    TCHK(ghb.alloc(scan_block_floats(q, B, Di) * sizeof(float)));
-    TCHK(pbc.alloc((size_t)dblk * rows * 2 * NSTATE * sizeof(float)));
-    TCHK(pA.alloc(scan_block_floats(q, B, Di) * sizeof(float)));
-    TCHK(pD.alloc(scan_block_floats(q, B, Di) / NSTATE * sizeof(float)));
-    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, q.Tc, q.NC, hsave, hsub.f(), SCAN_SUB, q.nsub, nullptr, 1,
+    // one region for the call: an allocation and its release cost 45 + 80 to 170 us
+    // each (64 x 128 steps, d_inner 1024: 1.06 ms of 1.33 in five of them)
+    Buf region;
+    size_t at = 0;
+    auto piece = [&](size_t floats) { const size_t o = at; at += (floats + 63) / 64 * 64; return o; };
+    const size_t o_hsub = piece(scan_hsub_floats(q, B, Di)), o_ghb = piece(scan_block_floats(q, B, Di)),
+                 o_pbc = piece((size_t)dblk * rows * 2 * NSTATE), o_pA = piece(scan_block_floats(q, B, Di)),
+                 o_pD = piece(scan_block_floats(q, B, Di) / NSTATE);
+    TCHK(region.alloc(at * sizeof(float)));
+    float *hsub = region.f() + o_hsub, *ghb = region.f() + o_ghb, *pbc = region.f() + o_pbc, *pA = region.f() + o_pA,
+          *pD = region.f() + o_pD;
+    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, q.Tc, q.NC, hsave, hsub, SCAN_SUB, q.nsub, nullptr, 1,
                      s));
-    TCHK(scan_grads(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, dy, B, T, Di, q, hsub.f(), ghb.f(), nullptr, dx, ddt, pbc.f(),
-                    pA.f(), pD.f(), nullptr, s));
-    hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, pbc.f(), dblk, rows, dbc,
+    TCHK(scan_grads(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, dy, B, T, Di, q, hsub, ghb, nullptr, dx, ddt, pbc,
+                    pA, pD, nullptr, s));
+    hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, pbc, dblk, rows, dbc,
                        2 * NSTATE, 0);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, pA.f(), B * q.NBS,
+    hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, pA, B * q.NBS,
                        (long long)Di * NSTATE, (long long)Di * NSTATE, dA_log, 1);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, pD.f(), B * q.NBS, (long long)Di, (long long)Di,
+    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, pD, B * q.NBS, (long long)Di, (long long)Di,
                        dD, 1);
     TCHK(hipGetLastError());
     TCHK(hipStreamSynchronize(s));
