@@ -847,14 +847,16 @@ DEVI long long scan_slot(int b, int NC, int c, int n_per, int k) { return ((long
 // few channel blocks to fill the GPU.  Bound by the chain of one step (two
 // dependent operations) and by issue: the rows of a block are staged in LDS
 // while the previous block is walked.  The state before step t goes to
-// hsub slot t / sub of its chunk, and with hsave to hsave[b][t / Tsave].  AL:
+// hsub slot t / sub of its chunk, and with hsave to hsave[b][t / Tsave].  The
+// state at the start of chunk c is h0[b][c h0s] of h0n per sequence (null: zero).  AL:
 // sub and Tsave are multiples of 8 (the check then runs once per 8 rows).
 template <int NPT, bool AL>
 __global__ __launch_bounds__(256) void k_tr_states(const float* __restrict__ xs, const float* __restrict__ dt,
                                                    const float* __restrict__ dbc, int NO, int R,
                                                    const float* __restrict__ A_log, int Tn, int Di, int Tc, int NC,
-                                                   const float* __restrict__ h0, float* __restrict__ hsub, int sub,
-                                                   int nsub, float* __restrict__ hsave, int Tsave, int nsave) {
+                                                   const float* __restrict__ h0, int h0n, int h0s,
+                                                   float* __restrict__ hsub, int sub, int nsub,
+                                                   float* __restrict__ hsave, int Tsave, int nsave) {
     constexpr int WS = 4 * NPT, NG = NSTATE / WS;             // states and workgroups per channel block
     constexpr int RPW = SCAN_SB / 4;
     __shared__ float dt_s[SCAN_SB][SCAN_CH], x_s[SCAN_SB][SCAN_CH];
@@ -869,7 +871,7 @@ __global__ __launch_bounds__(256) void k_tr_states(const float* __restrict__ xs,
 #pragma unroll
     for (int i = 0; i < NPT; ++i) {
         A2[i] = on ? -expf(A_log[d * NSTATE + n0 + i]) * LOG2E_F : 0.f;
-        h[i] = on && h0 ? h0[(scan_slot(b, NC, c, NSTATE, n0 + i)) * Di + d] : 0.f;
+        h[i] = on && h0 ? h0[(((long long)b * h0n + (long long)c * h0s) * NSTATE + n0 + i) * Di + d] : 0.f;
     }
     float rd[RPW], rx[RPW], rb[(SCAN_SB * WS + 255) / 256];
     auto fetch = [&](int s0) {
@@ -1682,17 +1684,18 @@ struct ScanCut {
 // Blocks of 256 steps read the boundary states least; shorter ones are taken
 // until there are 4096 waves (four per SIMD) or the block is 32 steps, where
 // the 16 exponentials of a wave's start begin to show.
+int scan_blocks(int Tn, int Tc, int NC, int TB) {                // of one sequence
+    return (NC - 1) * ((Tc + TB - 1) / TB) + (Tn - (NC - 1) * Tc + TB - 1) / TB;
+}
 ScanCut scan_cut(int B, int Tn, int Di, int Tc) {
     ScanCut q;
     q.Tc = std::min(Tc, Tn);
     q.NC = (Tn + q.Tc - 1) / q.Tc;
     q.nsub = (q.Tc + SCAN_SUB - 1) / SCAN_SUB;
     const long long dblk = (Di + SCAN_CH - 1) / SCAN_CH;
-    const int last = Tn - (q.NC - 1) * q.Tc;
-    auto count = [&](int TB) { return (q.NC - 1) * ((q.Tc + TB - 1) / TB) + (last + TB - 1) / TB; };
-    for (q.TB = 256; q.TB > 32 && dblk * B * count(q.TB) < 4096; q.TB /= 2) {}
+    for (q.TB = 256; q.TB > 32 && dblk * B * scan_blocks(Tn, q.Tc, q.NC, q.TB) < 4096; q.TB /= 2) {}
     q.nblk = (q.Tc + q.TB - 1) / q.TB;
-    q.NBS = count(q.TB);
+    q.NBS = scan_blocks(Tn, q.Tc, q.NC, q.TB);
     return q;
 }
 size_t scan_hsub_floats(const ScanCut& q, int B, int Di) { return (size_t)B * q.NC * q.nsub * NSTATE * Di; }
@@ -1704,12 +1707,12 @@ size_t scan_block_floats(const ScanCut& q, int B, int Di) { return (size_t)B * q
 // with 256 workgroups and more the four-state form reads dt and x once instead of
 // four times).
 hipError_t scan_states(const float* x, const float* dt, const float* dbc, int NO, int R, const float* A_log, int B,
-                       int Tn, int Di, int Tc, int NC, const float* h0, float* hsub, int sub, int nsub, float* hsave,
-                       int Tsave, hipStream_t s) {
+                       int Tn, int Di, int Tc, int NC, const float* h0, int h0n, int h0s, float* hsub, int sub,
+                       int nsub, float* hsave, int Tsave, hipStream_t s) {
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH, nsave = hsave ? (Tn + Tsave - 1) / Tsave : 0;
     const bool few = (long long)dblk * NC * B < 256, al = sub % 8 == 0 && (!hsave || Tsave % 8 == 0);
 #define STATES(NPT, AL) hipLaunchKernelGGL((k_tr_states<NPT, AL>), dim3(dblk * (4 / NPT), NC, B), dim3(256), 0, s, x, \
-                                           dt, dbc, NO, R, A_log, Tn, Di, Tc, NC, h0, hsub, sub, nsub, hsave, Tsave, nsave)
+                                           dt, dbc, NO, R, A_log, Tn, Di, Tc, NC, h0, h0n, h0s, hsub, sub, nsub, hsave, Tsave, nsave)
     if (few && al) STATES(1, true);
     else if (few) STATES(1, false);
     else if (al) STATES(4, true);
@@ -1728,13 +1731,10 @@ hipError_t scan_y(const float* x, const float* dt, const float* dbc, int NO, int
                        A_log, Dsk, xz, Tn, Di, TB, nslot, per, hsub, y, g);
     return hipGetLastError();
 }
-// Gradients from the states of every SCAN_SUB steps; ghb and the partials are
-// scratch (scan_block_floats floats for ghb and pA, a 16th of it for pD).
-hipError_t scan_grads(const float* x, const float* dt, const float* dbc, int NO, int R, const float* A_log,
-                      const float* Dsk, const float* dy, int B, int Tn, int Di, const ScanCut& q, const float* hsub,
-                      float* ghb, const float* dtr, float* dx, float* ddt, float* pbc, float* pA, float* pD, float* pT,
-                      hipStream_t s) {
-    const int dblk = (Di + SCAN_CH - 1) / SCAN_CH, w = std::min(4, dblk);
+// The adjoint states at the ends of the blocks (scan_block_floats floats).
+hipError_t scan_gstates(const float* dt, const float* dbc, int NO, int R, const float* A_log, const float* dy, int B,
+                        int Tn, int Di, const ScanCut& q, float* ghb, hipStream_t s) {
+    const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
     const bool few = (long long)dblk * B < 256, al = q.NC == 1 || q.Tc % 8 == 0;
 #define GSTATES(NPT, AL) hipLaunchKernelGGL((k_tr_gstates<NPT, AL>), dim3(dblk * (4 / NPT), 1, B), dim3(256), 0, s, dt, \
                                             dbc, NO, R, A_log, dy, Tn, Di, q.Tc, q.NC, q.TB, q.nblk, q.NBS, ghb)
@@ -1743,6 +1743,16 @@ hipError_t scan_grads(const float* x, const float* dt, const float* dbc, int NO,
     else if (al) GSTATES(4, true);
     else GSTATES(4, false);
 #undef GSTATES
+    return hipGetLastError();
+}
+// Gradients from the states of every SCAN_SUB steps and from the adjoint states;
+// pbc, pA, pD and pT are the partial sums (scan_block_floats floats for pA, a 16th of
+// it for pD and pT).
+hipError_t scan_grads(const float* x, const float* dt, const float* dbc, int NO, int R, const float* A_log,
+                      const float* Dsk, const float* dy, int B, int Tn, int Di, const ScanCut& q, const float* hsub,
+                      const float* ghb, const float* dtr, float* dx, float* ddt, float* pbc, float* pA, float* pD,
+                      float* pT, hipStream_t s) {
+    const int dblk = (Di + SCAN_CH - 1) / SCAN_CH, w = std::min(4, dblk);
     hipLaunchKernelGGL(k_tr_scan_bwd, dim3((dblk + w - 1) / w, q.NBS, B), dim3(64 * w),
                        (size_t)q.TB * 2 * NSTATE * sizeof(float), s, x, dt, dbc, NO, R, A_log, Dsk, dy, (long long)B * Tn,
                        Tn, Di, q.Tc, q.NC, q.TB, q.nblk, hsub, q.nsub, ghb, dtr, dx, ddt, pbc, pA, pD, pT);
@@ -1809,6 +1819,7 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
 // Standalone selective scan (autograd binding): B and C packed as [rows][32].
 int scan_fwd(const float* x, const float* dt, const float* A_log, const float* bc, const float* Dsk, int B, int T,
              int Di, int Tc, float* y, float* hsave, hipStream_t s, std::string& err) {
+    Tc = std::min(Tc, T);
     // the states the caller keeps also start the blocks of the output pass,
     // unless they lie so far apart that few blocks would run
     Buf fine;
@@ -1818,39 +1829,85 @@ int scan_fwd(const float* x, const float* dt, const float* A_log, const float* b
         TCHK(fine.alloc((size_t)B * nslot * NSTATE * Di * sizeof(float)));
         hsub = fine.f();
     }
-    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, T, 1, nullptr, hsub, sub, nslot,
+    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, T, 1, nullptr, 1, 1, hsub, sub, nslot,
                      sub != Tc ? hsave : nullptr, Tc, s));
     TCHK(scan_y(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, nullptr, B, T, Di, hsub, sub, nslot, y, nullptr, s));
     TCHK(hipStreamSynchronize(s));
     return BOA_OK;
 }
+// How the backward scan of a call is cut for its scratch memory: `seqs` sequences
+// at a time and, one at a time, `chunks` of their chunks.
+struct BwdPart {
+    int seqs, chunks;
+};
+size_t bwd_floats(const ScanCut& q, int seqs, int chunks, int T, int Di) {
+    const long long rows = (long long)seqs * (chunks == q.NC ? T : chunks * q.Tc);
+    return (size_t)seqs * chunks * q.nsub * NSTATE * Di + (size_t)(Di + SCAN_CH - 1) / SCAN_CH * rows * 2 * NSTATE +
+           scan_block_floats(q, seqs, Di) * 2 + scan_block_floats(q, seqs, Di) / NSTATE + 5 * 64;
+}
+// Within the memory of one chunk's states of every sequence and the partial sums
+// of every row (256 MiB are always granted: 2 x 20000 steps at d_inner 512 took 2.2 ms
+// whole and 3.1 in parts), the most sequences, else the most chunks.
+BwdPart bwd_part(const ScanCut& q, int B, int T, int Di, int Tc) {
+    const size_t rows = (size_t)B * T, dblk = (Di + SCAN_CH - 1) / SCAN_CH;
+    const size_t budget = std::max<size_t>((size_t)B * Tc * NSTATE * Di + dblk * rows * 2 * NSTATE, (size_t)64 << 20);
+    if (q.NBS <= 32768)
+        for (int parts = 1; parts <= B; ++parts) {
+            const int seqs = (B + parts - 1) / parts;
+            if (bwd_floats(q, seqs, q.NC, T, Di) <= budget) return {seqs, q.NC};
+        }
+    int chunks = std::max(1, std::min(q.NC, 32768 / q.nblk));
+    while (chunks > 1 && bwd_floats(q, 1, chunks, T, Di) > budget) chunks = (chunks + 1) / 2;
+    return {1, chunks};
+}
 int scan_bwd(const float* x, const float* dt, const float* A_log, const float* bc, const float* Dsk, const float* dy,
              int B, int T, int Di, int Tc, const float* hsave, float* dx, float* ddt, float* dbc, float* dA_log,
              float* dD, hipStream_t s, std::string& err) {
+    Tc = std::min(Tc, T);
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
-    const long long rows = (long long)B * T;
-    const ScanCut q = scan_cut(B, T, Di, Tc);
+    // chunks of less than 32 steps go together (a chunk costs its states at its start
+    // and at its blocks' ends), to a multiple of 8 steps
+    const int nsave = (T + Tc - 1) / Tc;
+    int m = (32 + Tc - 1) / Tc;
+    while (m > 1 && m * Tc % 8) ++m;
+    const ScanCut q = scan_cut(B, T, Di, (int)std::min<long long>((long long)m * Tc, T));
+    const BwdPart part = bwd_part(q, B, T, Di, Tc);
     // one region for the call: an allocation and its release cost 45 + 80 to 170 us
     // each (64 x 128 steps, d_inner 1024: 1.06 ms of 1.33 in five of them)
     Buf region;
     size_t at = 0;
     auto piece = [&](size_t floats) { const size_t o = at; at += (floats + 63) / 64 * 64; return o; };
-    const size_t o_hsub = piece(scan_hsub_floats(q, B, Di)), o_ghb = piece(scan_block_floats(q, B, Di)),
-                 o_pbc = piece((size_t)dblk * rows * 2 * NSTATE), o_pA = piece(scan_block_floats(q, B, Di)),
-                 o_pD = piece(scan_block_floats(q, B, Di) / NSTATE);
+    const long long prow = (long long)part.seqs * std::min<long long>(T, (long long)part.chunks * q.Tc);
+    const size_t o_hsub = piece((size_t)part.seqs * part.chunks * q.nsub * NSTATE * Di),
+                 o_ghb = piece(scan_block_floats(q, part.seqs, Di)), o_pbc = piece((size_t)dblk * prow * 2 * NSTATE),
+                 o_pA = piece(scan_block_floats(q, part.seqs, Di)), o_pD = piece(scan_block_floats(q, part.seqs, Di) / NSTATE);
     TCHK(region.alloc(at * sizeof(float)));
     float *hsub = region.f() + o_hsub, *ghb = region.f() + o_ghb, *pbc = region.f() + o_pbc, *pA = region.f() + o_pA,
           *pD = region.f() + o_pD;
-    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, q.Tc, q.NC, hsave, hsub, SCAN_SUB, q.nsub, nullptr, 1,
-                     s));
-    TCHK(scan_grads(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, dy, B, T, Di, q, hsub, ghb, nullptr, dx, ddt, pbc,
-                    pA, pD, nullptr, s));
-    hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, pbc, dblk, rows, dbc,
-                       2 * NSTATE, 0);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, pA, B * q.NBS,
-                       (long long)Di * NSTATE, (long long)Di * NSTATE, dA_log, 1);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, pD, B * q.NBS, (long long)Di, (long long)Di,
-                       dD, 1);
+    for (int b0 = 0; b0 < B; b0 += part.seqs) {
+        const int nb = std::min(part.seqs, B - b0);
+        const long long r0 = (long long)b0 * T;
+        TCHK(scan_gstates(dt + r0 * Di, bc + r0 * 2 * NSTATE, 2 * NSTATE, 0, A_log, dy + r0 * Di, nb, T, Di, q, ghb, s));
+        for (int c0 = 0; c0 < q.NC; c0 += part.chunks) {         // all of them unless nb is 1
+            ScanCut p = q;
+            p.NC = std::min(part.chunks, q.NC - c0);
+            const int Tn = std::min(T - c0 * q.Tc, p.NC * q.Tc);
+            p.NBS = scan_blocks(Tn, q.Tc, p.NC, q.TB);
+            const long long r = r0 + (long long)c0 * q.Tc, rows = (long long)nb * Tn, blk = (long long)c0 * q.nblk;
+            TCHK(scan_states(x + r * Di, dt + r * Di, bc + r * 2 * NSTATE, 2 * NSTATE, 0, A_log, nb, Tn, Di, q.Tc, p.NC,
+                             hsave + ((long long)b0 * nsave + (long long)c0 * m) * NSTATE * Di, nsave, m, hsub, SCAN_SUB,
+                             q.nsub, nullptr, 1, s));
+            TCHK(scan_grads(x + r * Di, dt + r * Di, bc + r * 2 * NSTATE, 2 * NSTATE, 0, A_log, Dsk, dy + r * Di, nb, Tn,
+                            Di, p, hsub, ghb + blk * NSTATE * Di, nullptr, dx + r * Di, ddt + r * Di, pbc,
+                            pA + blk * NSTATE * Di, pD + blk * Di, nullptr, s));
+            hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, pbc, dblk, rows,
+                               dbc + r * 2 * NSTATE, 2 * NSTATE, 0);
+        }
+        hipLaunchKernelGGL(k_sum_slices, dim3(blocks((long long)Di * NSTATE, 64)), dim3(256), 0, s, pA, nb * q.NBS,
+                           (long long)Di * NSTATE, (long long)Di * NSTATE, dA_log, 1);
+        hipLaunchKernelGGL(k_sum_slices, dim3(blocks(Di, 64)), dim3(256), 0, s, pD, nb * q.NBS, (long long)Di, (long long)Di,
+                           dD, 1);
+    }
     TCHK(hipGetLastError());
     TCHK(hipStreamSynchronize(s));
     return BOA_OK;
@@ -1903,7 +1960,7 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
             p.C2 = c->dt[l].f();
             TCHK(lin(dt, w[WF_DT], wf, c->dbc[l].f(), NO, rows, c->dtr[l].f(), Di, p, ws, s));
         }
-        TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, Tn, 1, nullptr,
+        TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, Tn, 1, nullptr, 1, 1,
                          c->hs[l].f(), SCAN_SUB, cut.nsub, nullptr, 1, s));
         TCHK(scan_y(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->xz[l].f(), B, Tn, Di,
                     c->hs[l].f(), SCAN_SUB, cut.nsub, c->y[l].f(), c->g[l].f(), s));
@@ -1959,6 +2016,7 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
             p.ldc2 = 2 * Di;
             TCHK(lin(dt, w[WF_OUT_T], wf, dr, D, rows, c->dyb.f(), Di, p, ws, s));
         }
+        TCHK(scan_gstates(c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, c->dyb.f(), B, Tn, Di, cut, c->ghb.f(), s));
         TCHK(scan_grads(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->dyb.f(), B, Tn,
                         Di, cut, c->hs[l].f(), c->ghb.f(), c->dtr[l].f(), c->dxs.f(), c->ddtr.f(), c->pbc.f(), c->pA.f(),
                         c->pD.f(), c->pT.f(), s));
@@ -2079,6 +2137,7 @@ uint64_t splitmix64(uint64_t& x) {
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
     return z ^ (z >> 31);
 }
+int scan_chunk(uint32_t chunk_t) { return chunk_t ? (int)std::min<uint32_t>(chunk_t, INT32_MAX) : 256; }
 bool train_dtype_ok(uint32_t d) { return d == BOA_DTYPE_F32 || d == BOA_DTYPE_BF16; }
 uint64_t fnv1a64(const void* data, size_t n, uint64_t h) {
     const uint8_t* p = static_cast<const uint8_t*>(data);
@@ -2285,8 +2344,8 @@ extern "C" int boa_scan_fwd_dev(const float* d_x, const float* d_dt, const float
     if (!d_x || !d_dt || !d_A_log || !d_bc || !d_Dskip || !d_y || !d_hsave || B == 0 || T == 0 || Di == 0)
         return set_error(BOA_E_ARG, "bad argument");
     std::string err;
-    int rc = scan_fwd(d_x, d_dt, d_A_log, d_bc, d_Dskip, (int)B, (int)T, (int)Di, chunk_t ? (int)chunk_t : 256, d_y,
-                      d_hsave, (hipStream_t)stream, err);
+    int rc = scan_fwd(d_x, d_dt, d_A_log, d_bc, d_Dskip, (int)B, (int)T, (int)Di, scan_chunk(chunk_t), d_y, d_hsave,
+                      (hipStream_t)stream, err);
     return rc ? set_error(rc, err) : BOA_OK;
 }
 
@@ -2298,7 +2357,7 @@ extern "C" int boa_scan_bwd_dev(const float* d_x, const float* d_dt, const float
         !d_dA_log || !d_dDskip || B == 0 || T == 0 || Di == 0)
         return set_error(BOA_E_ARG, "bad argument");
     std::string err;
-    int rc = scan_bwd(d_x, d_dt, d_A_log, d_bc, d_Dskip, d_dy, (int)B, (int)T, (int)Di, chunk_t ? (int)chunk_t : 256,
-                      d_hsave, d_dx, d_ddt, d_dbc, d_dA_log, d_dDskip, (hipStream_t)stream, err);
+    int rc = scan_bwd(d_x, d_dt, d_A_log, d_bc, d_Dskip, d_dy, (int)B, (int)T, (int)Di, scan_chunk(chunk_t), d_hsave,
+                      d_dx, d_ddt, d_dbc, d_dA_log, d_dDskip, (hipStream_t)stream, err);
     return rc ? set_error(rc, err) : BOA_OK;
 }
