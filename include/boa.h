@@ -406,8 +406,10 @@ typedef struct {
  * the float32 master weights, in the flat weight layout (d_grad: device
  * float32, boa_param_count entries).  The selective scan keeps its state every
  * 8 steps and recomputes it in between in the backward pass (Appendix A: the
- * scan evaluated over the sequence during training); chunk_t (0 = 256) does
- * not change the result.  dtype selects the
+ * scan evaluated over the sequence during training); from four layers on about
+ * half of the layers keep it every chunk_t steps (0 = 256) only, and make the
+ * closer ones again, unless chunk_t is 8 or less.  chunk_t trades memory for
+ * that time and does not change the result.  dtype selects the
  * projections' operands: BOA_DTYPE_F32, or BOA_DTYPE_BF16 (activations,
  * gradients and weights rounded to bf16 as they enter the matrix cores, FP32
  * accumulation); everything else is FP32.  Every reduction has a fixed order

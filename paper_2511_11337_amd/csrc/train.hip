@@ -847,7 +847,8 @@ DEVI long long scan_slot(int b, int NC, int c, int n_per, int k) { return ((long
 // few channel blocks to fill the GPU.  Bound by the chain of one step (two
 // dependent operations) and by issue: the rows of a block are staged in LDS
 // while the previous block is walked.  The state before step t goes to
-// hsub slot t / sub of its chunk, and with hsave to hsave[b][t / Tsave].  The
+// hsub slot t / sub of its chunk (chunk c of a sequence from slot c nsub of its
+// nseq on), and with hsave to hsave[b][t / Tsave].  The
 // state at the start of chunk c is h0[b][c h0s] of h0n per sequence (null: zero).  AL:
 // sub and Tsave are multiples of 8 (the check then runs once per 8 rows).
 template <int NPT, bool AL>
@@ -855,7 +856,7 @@ __global__ __launch_bounds__(256) void k_tr_states(const float* __restrict__ xs,
                                                    const float* __restrict__ dbc, int NO, int R,
                                                    const float* __restrict__ A_log, int Tn, int Di, int Tc, int NC,
                                                    const float* __restrict__ h0, int h0n, int h0s,
-                                                   float* __restrict__ hsub, int sub, int nsub,
+                                                   float* __restrict__ hsub, int sub, int nsub, int nseq,
                                                    float* __restrict__ hsave, int Tsave, int nsave) {
     constexpr int WS = 4 * NPT, NG = NSTATE / WS;             // states and workgroups per channel block
     constexpr int RPW = SCAN_SB / 4;
@@ -924,7 +925,7 @@ __global__ __launch_bounds__(256) void k_tr_states(const float* __restrict__ xs,
                 if (!AL || j == 0) {                  // aligned: states fall on group starts only
                     if (t == next && t < t1) {
                         if (on && hsub) {
-                            float* o = hsub + (scan_slot(b, NC, c, nsub, slot) * NSTATE + n0) * Di + d;
+                            float* o = hsub + (((long long)b * nseq + (long long)c * nsub + slot) * NSTATE + n0) * Di + d;
 #pragma unroll
                             for (int i = 0; i < NPT; ++i) o[(long long)i * Di] = h[i];
                         }
@@ -1403,6 +1404,24 @@ size_t gemm_ws_floats(int M, int N, long long K) {
 
 }  // namespace
 
+// States of the forward scan that a training call keeps for its backward pass:
+// every SCAN_SUB steps (2 d_inner floats a row) in the layers from `fine` on, and
+// every `every` steps in the others, whose backward pass makes the closer ones
+// again in one buffer of a layer.  All layers keep the close ones while these take
+// no more than L + 3 d_inner floats a row; else as many as that leaves beside the
+// one buffer, so that a deep model's batch stays within what it takes with states
+// every chunk_t steps (16 layers: 19 d_inner floats a row instead of 32).  chunk_t up to
+// SCAN_SUB asks for all of them.
+struct KeptStates {
+    int every = SCAN_SUB, fine = 0;
+    static KeptStates of(int L, int Tc) {
+        KeptStates k;
+        k.every = (Tc + SCAN_SUB - 1) / SCAN_SUB * SCAN_SUB;
+        if (k.every > SCAN_SUB && 2 * L > L + 3) k.fine = L - (L + 1) / 2;
+        return k;
+    }
+};
+
 // Training context kept on the model: optimizer moments, step count, the
 // activation and gradient buffers of the last (B, T) shape, and scratch.
 struct TrainCtx {
@@ -1410,8 +1429,10 @@ struct TrainCtx {
     long long step = 0;
     // activations (per layer) and backward temporaries, sized for rows x widths
     int B = 0, T = 0, Tc = 0;
+    KeptStates kept;
     std::vector<Buf> rin, a, st, xz, xs, dbc, dtr, dt, y, g, hs;
     std::vector<Buf> fr, fu, fg, ff, fst;   // feed-forward: input r, W1 r + b1, GELU of it, W2 . + b2, LN stats
+    Buf hsub;                               // fine states of one layer (KeptStates)
     Buf fdu;                                // feed-forward backward: gradient of the hidden row
     Buf wf;                                 // prepared weight matrices of the step
     Buf rfin, rf, stf, logits, rowloss;
@@ -1708,11 +1729,11 @@ size_t scan_block_floats(const ScanCut& q, int B, int Di) { return (size_t)B * q
 // four times).
 hipError_t scan_states(const float* x, const float* dt, const float* dbc, int NO, int R, const float* A_log, int B,
                        int Tn, int Di, int Tc, int NC, const float* h0, int h0n, int h0s, float* hsub, int sub,
-                       int nsub, float* hsave, int Tsave, hipStream_t s) {
+                       int nsub, int nseq, float* hsave, int Tsave, hipStream_t s) {
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH, nsave = hsave ? (Tn + Tsave - 1) / Tsave : 0;
     const bool few = (long long)dblk * NC * B < 256, al = sub % 8 == 0 && (!hsave || Tsave % 8 == 0);
 #define STATES(NPT, AL) hipLaunchKernelGGL((k_tr_states<NPT, AL>), dim3(dblk * (4 / NPT), NC, B), dim3(256), 0, s, x, \
-                                           dt, dbc, NO, R, A_log, Tn, Di, Tc, NC, h0, h0n, h0s, hsub, sub, nsub, hsave, Tsave, nsave)
+                                           dt, dbc, NO, R, A_log, Tn, Di, Tc, NC, h0, h0n, h0s, hsub, sub, nsub, nseq, hsave, Tsave, nsave)
     if (few && al) STATES(1, true);
     else if (few) STATES(1, false);
     else if (al) STATES(4, true);
@@ -1769,6 +1790,7 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
     const size_t rows = (size_t)B * Tn, F = sizeof(float);
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
     const ScanCut q = scan_cut(B, Tn, Di, Tn);
+    const KeptStates kept = KeptStates::of(L.L, std::min(Tc, Tn));
     c->B = c->T = c->Tc = 0;
     c->rin.resize(L.L); c->a.resize(L.L); c->st.resize(L.L); c->xz.resize(L.L); 
     c->xs.resize(L.L); c->dbc.resize(L.L); c->dtr.resize(L.L); c->dt.resize(L.L); c->y.resize(L.L);
@@ -1788,8 +1810,10 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
         TCHK(c->xs[l].ensure(rows * Di * F)); TCHK(c->dbc[l].ensure(rows * NO * F));
         TCHK(c->dtr[l].ensure(rows * Di * F)); TCHK(c->dt[l].ensure(rows * Di * F));
         TCHK(c->y[l].ensure(rows * Di * F)); TCHK(c->g[l].ensure(rows * Di * F));
-        TCHK(c->hs[l].ensure(scan_hsub_floats(q, B, Di) * F));
+        TCHK(c->hs[l].ensure((l < kept.fine ? (size_t)B * ((Tn + kept.every - 1) / kept.every) * NSTATE * Di
+                                            : scan_hsub_floats(q, B, Di)) * F));
     }
+    if (kept.fine) TCHK(c->hsub.ensure(scan_hsub_floats(q, B, Di) * F));
     TCHK(c->wf.ensure(wfrag_bytes(L)));
     TCHK(c->rfin.ensure(rows * D * F));
     TCHK(c->rf.ensure(rows * D * F)); TCHK(c->stf.ensure(rows * 2 * F)); TCHK(c->logits.ensure(rows * 256 * F));
@@ -1813,6 +1837,7 @@ int train_ensure_buffers(boa_model* m, int B, int T, int Tc, std::string& err) {
         for (int K : {D, Di, L.R, 2 * Di, NO, 256, Hs}) ws = std::max(ws, gemm_ws_floats((int)R, N, K));
     TCHK(c->gws.ensure(std::max<size_t>(ws, 1) * F));
     c->B = B; c->T = T; c->Tc = Tc;
+    c->kept = kept;
     return BOA_OK;
 }
 
@@ -1829,7 +1854,7 @@ int scan_fwd(const float* x, const float* dt, const float* A_log, const float* b
         TCHK(fine.alloc((size_t)B * nslot * NSTATE * Di * sizeof(float)));
         hsub = fine.f();
     }
-    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, T, 1, nullptr, 1, 1, hsub, sub, nslot,
+    TCHK(scan_states(x, dt, bc, 2 * NSTATE, 0, A_log, B, T, Di, T, 1, nullptr, 1, 1, hsub, sub, nslot, nslot,
                      sub != Tc ? hsave : nullptr, Tc, s));
     TCHK(scan_y(x, dt, bc, 2 * NSTATE, 0, A_log, Dsk, nullptr, B, T, Di, hsub, sub, nslot, y, nullptr, s));
     TCHK(hipStreamSynchronize(s));
@@ -1896,7 +1921,7 @@ int scan_bwd(const float* x, const float* dt, const float* A_log, const float* b
             const long long r = r0 + (long long)c0 * q.Tc, rows = (long long)nb * Tn, blk = (long long)c0 * q.nblk;
             TCHK(scan_states(x + r * Di, dt + r * Di, bc + r * 2 * NSTATE, 2 * NSTATE, 0, A_log, nb, Tn, Di, q.Tc, p.NC,
                              hsave + ((long long)b0 * nsave + (long long)c0 * m) * NSTATE * Di, nsave, m, hsub, SCAN_SUB,
-                             q.nsub, nullptr, 1, s));
+                             q.nsub, p.NC * q.nsub, nullptr, 1, s));
             TCHK(scan_grads(x + r * Di, dt + r * Di, bc + r * 2 * NSTATE, 2 * NSTATE, 0, A_log, Dsk, dy + r * Di, nb, Tn,
                             Di, p, hsub, ghb + blk * NSTATE * Di, nullptr, dx + r * Di, ddt + r * Di, pbc,
                             pA + blk * NSTATE * Di, pD + blk * Di, nullptr, s));
@@ -1960,10 +1985,12 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
             p.C2 = c->dt[l].f();
             TCHK(lin(dt, w[WF_DT], wf, c->dbc[l].f(), NO, rows, c->dtr[l].f(), Di, p, ws, s));
         }
-        TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, Tn, 1, nullptr, 1, 1,
-                         c->hs[l].f(), SCAN_SUB, cut.nsub, nullptr, 1, s));
+        const bool fine = l >= c->kept.fine;
+        float* hsub = fine ? c->hs[l].f() : c->hsub.f();
+        TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, Tn, 1, nullptr, 1, 1, hsub,
+                         SCAN_SUB, cut.nsub, cut.nsub, fine ? nullptr : c->hs[l].f(), c->kept.every, s));
         TCHK(scan_y(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->xz[l].f(), B, Tn, Di,
-                    c->hs[l].f(), SCAN_SUB, cut.nsub, c->y[l].f(), c->g[l].f(), s));
+                    hsub, SCAN_SUB, cut.nsub, c->y[l].f(), c->g[l].f(), s));
         TCHK(lin(dt, w[WF_OUT], wf, c->g[l].f(), Di, rows, L.H ? c->fr[l].f() : rnext, D, add_to(c->rin[l].f()), ws, s));
         if (L.H) {            // r <- LayerNorm(W2 GELU(W1 r + b1) + b2)
             const int H = L.H;
@@ -2016,9 +2043,16 @@ int loss_grad(boa_model* m, const uint8_t* tok, int B, int T, int Tc, int dt_, d
             p.ldc2 = 2 * Di;
             TCHK(lin(dt, w[WF_OUT_T], wf, dr, D, rows, c->dyb.f(), Di, p, ws, s));
         }
+        float* hsub = c->hs[l].f();
+        if (l < c->kept.fine) {                          // the states every SCAN_SUB steps again
+            const int every = c->kept.every, n = (Tn + every - 1) / every;
+            hsub = c->hsub.f();
+            TCHK(scan_states(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, B, Tn, Di, every, n,
+                             c->hs[l].f(), n, 1, hsub, SCAN_SUB, every / SCAN_SUB, cut.nsub, nullptr, 1, s));
+        }
         TCHK(scan_gstates(c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, c->dyb.f(), B, Tn, Di, cut, c->ghb.f(), s));
         TCHK(scan_grads(c->xs[l].f(), c->dt[l].f(), c->dbc[l].f(), NO, R, Wt + o.A_log, Wt + o.Dsk, c->dyb.f(), B, Tn,
-                        Di, cut, c->hs[l].f(), c->ghb.f(), c->dtr[l].f(), c->dxs.f(), c->ddtr.f(), c->pbc.f(), c->pA.f(),
+                        Di, cut, hsub, c->ghb.f(), c->dtr[l].f(), c->dxs.f(), c->ddtr.f(), c->pbc.f(), c->pA.f(),
                         c->pD.f(), c->pT.f(), s));
         hipLaunchKernelGGL(k_tr_dbc_reduce, dim3(blocks(rows * 2 * NSTATE)), dim3(256), 0, s, c->pbc.f(), dblk, rows,
                            c->ddbc.f(), NO, R);
