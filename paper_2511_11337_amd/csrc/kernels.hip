@@ -1827,33 +1827,36 @@ __global__ void k_decode_tables(const uint8_t* __restrict__ payload, const long 
     Dec d;
     dec_reset(d, in, len);
     long long base = sym_off[lane_id];
+    // (every thread of the wave holds the same state; the next 8 payload bytes are
+    // requested, one per thread, before the table)
     for (long long j = 0; j < nsym[lane_id]; ++j) {
+        const int pbyte = wl < 8 ? (int)dec_byte(in, len, d.cur + wl) : 0;
         const uint16_t* f = freq + (base + j) * 256;
-        int fl[4] = {f[4 * wl], f[4 * wl + 1], f[4 * wl + 2], f[4 * wl + 3]};
+        const int fl[4] = {f[4 * wl], f[4 * wl + 1], f[4 * wl + 2], f[4 * wl + 3]};
         int loc = ((fl[0] + fl[1]) + fl[2]) + fl[3];
         int incl = wave_incl_scan_i(loc, wl);
         int c = incl - loc;
         const uint64_t v = dec_v(d);
         int hit = -1, hc = 0, hf = 0;
+#pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (fl[i] && dec_from(v, d.D, (uint32_t)c) && dec_upto(v, d.D, (uint32_t)(c + fl[i]))) { hit = 4 * wl + i; hc = c; hf = fl[i]; }
+            const bool in_i = (fl[i] != 0) & dec_from(v, d.D, (uint32_t)c) & dec_upto(v, d.D, (uint32_t)(c + fl[i]));
+            hit = in_i ? 4 * wl + i : hit;
+            hc = in_i ? c : hc;
+            hf = in_i ? fl[i] : hf;
             c += fl[i];
         }
         unsigned long long bal = __ballot(hit >= 0);
-        int src = bal ? (__ffsll((long long)bal) - 1) : 0;
-        int s = __shfl(hit, src, 64);
-        hc = __shfl(hc, src, 64);
-        hf = __shfl(hf, src, 64);
+        const int src = bal ? (__ffsll((long long)bal) - 1) : 0;
+        int s = __builtin_amdgcn_readlane(hit, src);
+        hc = __builtin_amdgcn_readlane(hc, src);
+        hf = __builtin_amdgcn_readlane(hf, src);
         if (s < 0) { s = 0; hc = 0; hf = f[0]; }
-        if (wl == 0) {
-            dec_update(d, (uint32_t)hc, (uint32_t)hf, in, len);
-            sym[base + j] = (uint8_t)s;
-        }
-        // broadcast the updated state from wave lane 0
-        d.L = __shfl(d.L, 0, 64);
-        d.D = __shfl(d.D, 0, 64);
-        d.X = __shfl(d.X, 0, 64);
-        d.cur = __shfl(d.cur, 0, 64);
+        uint64_t pf = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pf |= (uint64_t)(uint32_t)__builtin_amdgcn_readlane(pbyte, i) << (8 * i);
+        dec_update(d, (uint32_t)hc, (uint32_t)hf, in, len, pf, true);
+        if (wl == 0) sym[base + j] = (uint8_t)s;
     }
 }
 hipError_t launch_decode_tables(const uint8_t* payload, const long long* pay_off, const long long* pay_len,
