@@ -1912,7 +1912,9 @@ __global__ __launch_bounds__(256) void k_crc32(const uint8_t* __restrict__ data,
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), wl = threadIdx.x & 63;
     if (i >= n) return;
     const long long ln = len[i];
-    const long long S = ((ln + 63) / 64 + 3) & ~3LL;     // bytes per piece
+    long long S = ((ln + 63) / 64 + 3) & ~3LL;           // bytes per piece, at least 32:
+    S = S < 32 ? 32 : S;                                 // a join costs what a lane's table takes for as many
+    const long long joins = (ln + S - 1) / S;            // pieces that hold bytes, the last `joins` lanes'
     long long b0 = ln - (64 - wl) * S, b1 = b0 + S;
     uint32_t c = b0 <= 0 && b1 > 0 ? 0xFFFFFFFFu : 0u;
     b0 = b0 < 0 ? 0 : b0;
@@ -1928,13 +1930,18 @@ __global__ __launch_bounds__(256) void k_crc32(const uint8_t* __restrict__ data,
             c = tab[3][c & 255] ^ tab[2][(c >> 8) & 255] ^ tab[1][(c >> 16) & 255] ^ tab[0][c >> 24];
         }
     }
-    for (; b0 < b1; ++b0) c = (c >> 8) ^ tab[0][(c ^ p[b0]) & 255];
+    uint8_t t[4 * U];                                    // what is left, requested together
+#pragma unroll
+    for (int u = 0; u < 4 * U; ++u) t[u] = b0 + u < b1 ? p[b0 + u] : 0;
+#pragma unroll
+    for (int u = 0; u < 4 * U; ++u)
+        if (b0 + u < b1) c = (c >> 8) ^ tab[0][(c ^ t[u]) & 255];
     // x^(8 S): the product of the powers of S's bits
     uint32_t xs = (S >> wl) & 1 ? kCrcPow.v[wl] : CRC_ONE;
 #pragma unroll 1
-    for (int o = 1; o < 64; o <<= 1) xs = crc_mul(xs, __shfl_xor(xs, o));
+    for (int o = 1; o < 64 && joins > 1; o <<= 1) xs = crc_mul(xs, __shfl_xor(xs, o));
 #pragma unroll 1
-    for (int o = 1; o < 64; o <<= 1) {                   // lanes with the wave's low bits set hold a right piece
+    for (int o = 1; o < joins; o <<= 1) {                // lanes with the wave's low bits set hold a right piece
         const uint32_t left = __shfl_up(c, o);
         if ((wl & (2 * o - 1)) == 2 * o - 1) c ^= crc_mul(left, xs);
         xs = crc_mul(xs, xs);
