@@ -8,12 +8,13 @@ numerics contract, so any choice produces the same bitstream (checked by the
 tile- and lane-independence tests).  The tuner times the candidates on a
 prefix of the real chunks with the library's own HIP-event kernel timer off,
 using wall time around device-level calls, and caches the winner per
-(model shape, dtype, device, lane count) in a JSON file.  Shapes tuned ahead
-of time for a device ship in tuned.json beside this module and are used
-without a sweep (use_table=False sweeps anyway).
+(model shape, dtype, device, chunk count, lane count, library build) in a JSON
+file.  Shapes tuned ahead of time for a device ship in tuned.json beside this
+module and are used without a sweep (use_table=False sweeps anyway).
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import os
 import time
@@ -28,7 +29,7 @@ MAX_TILE_ROWS = 1 << 21          # lanes x tile rows per encoder launch (~20 GiB
 
 
 def _key(model, dtype, lanes):
-    """Table / cache key: the device by ISA and compute-unit count (its
+    """Table key: the device by ISA and compute-unit count (its
     marketing name depends on the host's id tables), the model shape, the
     dtype and the lane count rounded up to a power of two."""
     import torch
@@ -36,6 +37,17 @@ def _key(model, dtype, lanes):
     dev = f"{getattr(p, 'gcnArchName', p.name).split(':')[0]}x{p.multi_processor_count}"
     c = model.cfg
     return f"v3|{dev}|d{c.d_model}|l{c.n_layers}|{dtype}|lanes{1 << max(0, int(lanes - 1).bit_length())}"
+
+
+def _cache_key(model, dtype, lens):
+    """Cache key: the table's, the exact chunk and lane counts (how many lanes a
+    workgroup should decode changes at counts that are no powers of two), and the
+    library's content, since another build's kernels have other best shapes."""
+    import paper_2511_11337_amd as boa
+    from . import _lib
+    with open(_lib.LIB_PATH, "rb") as f:
+        build = hashlib.sha256(f.read()).hexdigest()[:16]
+    return f"{_key(model, dtype, len(lens))}|{len(lens)}x{boa.plan_lanes(lens)}|{build}"
 
 
 def in_table(model, dtype, lanes) -> bool:
@@ -71,6 +83,7 @@ def tune(model, d_data, chunk_lens, dtype="f32", sample_bytes=2048, use_cache=Tr
         table = _load(TABLE)
         if key in table:
             return dict(table[key])
+    key = _cache_key(model, dtype, lens)
     cache = _load() if use_cache else {}
     if key in cache:
         return cache[key]
