@@ -405,7 +405,7 @@ def main():
         # in HBM: that stream, the decoded byte and the payload read are the
         # kernel's algorithmic HBM bytes, and HBM is its roofline.
         positions = coded_positions                      # one launch decodes every chunk
-        g = tuned["fused_lanes"]
+        g = tuned["fused_lanes"] or "auto"               # "auto": the library's choice for these lanes
         kname = f"k_dec_fused<{ {'f32': 0, 'bf16': 1, 'fp8': 2}[args.dtype] }, {Dm}, {2 * Dm}, " \
                 f"{(Dm + 15) // 16}, {g}, {'true' if g == 1 and Dm <= 256 else 'false'}>"
         per_pos = float(state_bytes_per_step(Dm, Lm)) + 1.0 + coded * 1.0 / positions

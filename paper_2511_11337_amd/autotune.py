@@ -10,7 +10,9 @@ prefix of the real chunks with the library's own HIP-event kernel timer off,
 using wall time around device-level calls, and caches the winner per
 (model shape, dtype, device, chunk count, lane count, library build) in a JSON
 file.  Shapes tuned ahead of time for a device ship in tuned.json beside this
-module and are used without a sweep (use_table=False sweeps anyway).
+module and are used without a sweep (use_table=False sweeps anyway): the tile
+for every chunk count that rounds up to the entry's, the lanes per workgroup
+for the entry's own count (others leave them to the library).
 """
 from __future__ import annotations
 
@@ -82,7 +84,10 @@ def tune(model, d_data, chunk_lens, dtype="f32", sample_bytes=2048, use_cache=Tr
     if use_table:
         table = _load(TABLE)
         if key in table:
-            return dict(table[key])
+            res = dict(table[key])
+            if not key.endswith(f"|lanes{len(lens)}"):
+                res["fused_lanes"] = 0      # timed at another count: the library chooses for this one's lanes
+            return res
     key = _cache_key(model, dtype, lens)
     cache = _load() if use_cache else {}
     if key in cache:

@@ -68,3 +68,14 @@ def test_cached_shapes_are_for_one_library_and_one_lane_count(tmp_path, monkeypa
     other.write_bytes(b"another build")
     monkeypatch.setattr(_lib, "LIB_PATH", str(other))
     assert key([4096] * 300) != a
+
+
+def test_table_lanes_are_for_the_entrys_own_count(monkeypatch):
+    import torch
+    dev = SimpleNamespace(name="card", gcnArchName="gfx950", multi_processor_count=256)
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda i: dev)
+    model = SimpleNamespace(cfg=SimpleNamespace(d_model=256, n_layers=3))
+    entry = autotune._load(autotune.TABLE)["v3|gfx950x256|d256|l3|bf16|lanes8192"]
+    assert autotune.tune(model, _Data(), [4096] * 8192, dtype="bf16") == entry
+    # 5000 lanes in workgroups of 16 leave most of a second round of the chip empty
+    assert autotune.tune(model, _Data(), [4096] * 5000, dtype="bf16") == {**entry, "fused_lanes": 0}
