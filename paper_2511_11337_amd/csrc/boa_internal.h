@@ -75,7 +75,7 @@ struct LayerDev {
 struct FusedLayer {
     const float* norm_w; const float* norm_b;
     const void* in_frag;                 // fragment-ordered in_proj (dtype of the launch)
-    const float* convT; const float* conv_b; const float* xw; const float* dtwT; const float* dtb;
+    const float* convT; const float* conv_b; const float* dtwT; const float* dtb;
     const float* A2T; const float* Dsk;
     const uint16_t* dtw16;               // BF16 mode: bf16 dt_proj [Di, R]
     const float* xw_frag;                // fragment-ordered f32 x_proj of the launch's numerics (xwF / xwF_r)

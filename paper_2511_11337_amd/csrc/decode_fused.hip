@@ -231,9 +231,9 @@ constexpr bool load_ok(int vo, int so, int range) { return so >= 0 && vo >= 0 &&
 // wave's first pass; it can be called a phase early so the loads arrive while
 // other work runs.  run() completes the product and calls f(row, n, v) for
 // every output (fp8: rescaled by the row and weight scales).
-// A8 (fp8 only): the A rows are already E4M3 bytes (row stride 4 * as bytes,
-// scaled by 2^-ea of their row) instead of floats quantised here per k step.
-template <int DT, int G, int K, int NF, bool A8 = false>
+// fp8: the A rows are E4M3 bytes (row stride 4 * as bytes, scaled by 2^-ea of
+// their row).
+template <int DT, int G, int K, int NF>
 struct FGemm {
     using BT = typename BLoad<DT>::T;
     static constexpr int FALL = (NF + FNW - 1) / FNW;      // fragments per wave
@@ -288,8 +288,6 @@ struct FGemm {
         const int li = wl & 15, lk = wl >> 4;
         const bool arow = li < G;
         const __amdgpu_buffer_rsrc_t rs = rsrc(Wf);
-        // fp8: this lane's A row scale 2^-ea (rows >= G are zero)
-        const int ea = (DT == 2 && !A8 && arow) ? fp8_exp(__uint_as_float(amax_rows[li])) : 0;
         v4f acc[FPW];
 #pragma unroll
         for (int j = 0; j < FPW; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -324,18 +322,9 @@ struct FGemm {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         uint64_t a8 = 0;
-                        if (arow && A8) {
+                        if (arow)
                             a8 = *reinterpret_cast<const uint64_t*>(reinterpret_cast<const uint8_t*>(A) + li * 4 * as +
                                                                     32 * (2 * st + h) + 8 * lk);
-                        } else if (arow) {
-                            const float* src = A + li * as + 32 * (2 * st + h) + 8 * lk;
-                            const float4 x0 = *reinterpret_cast<const float4*>(src);
-                            const float4 x1 = *reinterpret_cast<const float4*>(src + 4);
-                            const float xv[8] = {ldexpf(x0.x, -ea), ldexpf(x0.y, -ea), ldexpf(x0.z, -ea),
-                                                 ldexpf(x0.w, -ea), ldexpf(x1.x, -ea), ldexpf(x1.y, -ea),
-                                                 ldexpf(x1.z, -ea), ldexpf(x1.w, -ea)};
-                            a8 = fp8_pack8(xv);
-                        }
 #pragma unroll
                         for (int j = 0; j < FPW; ++j) {
                             const uint4 c4 = *reinterpret_cast<const uint4*>(&cur[j]);
@@ -495,7 +484,7 @@ struct RGemm {
     }
 };
 template <int DT, int G, int K, int NF>
-using Gemm = typename std::conditional<DT == 0 && G <= 2, RGemm<(G <= 2 ? G : 1), K, NF>, FGemm<DT, G, K, NF, DT == 2>>::type;
+using Gemm = typename std::conditional<DT == 0 && G <= 2, RGemm<(G <= 2 ? G : 1), K, NF>, FGemm<DT, G, K, NF>>::type;
 
 // LayerNorm of the G residual rows into a_s.  With G >= 8 a wave takes whole
 // rows (w, w + 8); with fewer rows the waves share them, wave w normalising the

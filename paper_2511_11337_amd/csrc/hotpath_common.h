@@ -67,16 +67,7 @@ DEVI int fp8_exp(float amax) {
     const float f = frexpf(amax, &E);          // amax = f * 2^E, f in [0.5, 1)
     return E - 9 + (2.0f * f > 1.75f ? 1 : 0);
 }
-// eight values (already multiplied by 2^-e) -> eight E4M3 bytes, element j in
-// bits 8j .. 8j + 7
-DEVI uint64_t fp8_pack8(const float* v) {
-    uint32_t lo = 0, hi = 0;
-    lo = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], (int)lo, false);
-    lo = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], (int)lo, true);
-    hi = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[4], v[5], (int)hi, false);
-    hi = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(v[6], v[7], (int)hi, true);
-    return (uint64_t)lo | ((uint64_t)hi << 32);
-}
+// a value (already multiplied by 2^-e) as an E4M3 byte
 DEVI uint8_t fp8_byte(float v) { return (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(v, 0.0f, 0, false) & 0xFF); }
 
 // ---------------------------------------------------------------- elementwise functions

@@ -1127,7 +1127,7 @@ int decode_fused(const boa_model* m, const boa_run_opts& o, const DecHost& H, co
         f.in_frag = pick(w.in_f32f, w.in_b16f, w.in_f8f);
         f.in_ew = w.in_ew;
         f.out_ew = w.out_ew;
-        f.convT = w.convT; f.conv_b = w.conv_b; f.xw = w.xw; f.dtwT = w.dtwT; f.dtb = w.dtb;
+        f.convT = w.convT; f.conv_b = w.conv_b; f.dtwT = w.dtwT; f.dtb = w.dtb;
         f.A2T = w.A2T; f.Dsk = w.Dsk;
         f.dtw16 = w.dtw16;
         f.xw_frag = o.dtype == BOA_DTYPE_BF16 ? w.xwF_r : w.xwF;
