@@ -17,8 +17,8 @@ range coding) and decode it again (fused persistent decoder: model step,
 histogram, range decoding, feedback of the decoded byte), each with a
 workspace allocated once before the timed region.  The round trip is checked
 for byte identity outside the timed region.  No warm-up step by default: one
-step takes about two minutes, the encoder's kernels are launched thousands of
-times in it, and the decoder is one launch of a minute (so its own first-launch
+step takes about 70 seconds, the encoder's kernels are launched thousands of
+times in it, and the decoder is one launch of 50 seconds (so its own first-launch
 cost is noise); the timed decoder launch is then the only launch of its kernel
 in the run, which a kernel trace of this command can be checked against.
 Launch shapes come from the tuned table shipped for this device

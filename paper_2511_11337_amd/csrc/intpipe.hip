@@ -380,7 +380,10 @@ struct QShared {
     ll lnc[17];         // the exponential's and logarithm's tables, read with divergent indexes
 };
 
-// DM = d_model: every loop bound below is a compile-time constant
+// DM = d_model: every loop bound below is a compile-time constant.  Four waves
+// per SIMD (128 registers) cost 36 spilled registers a thread at d_model 256 (44,
+// 41 and 81 at 64, 128 and 512): the state loads ahead are held beside the
+// exponentials' values.
 template <int DM>
 __global__ __launch_bounds__(NT, 4) void k_int_chunk(QArgs a, QJob j, int mode) {
     __shared__ QShared sh;

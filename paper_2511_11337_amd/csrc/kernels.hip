@@ -986,8 +986,10 @@ hipError_t launch_mid(const LayerDev& w, int Di, int R, const float* xz, float* 
 // KEEP: the conv output and Delta = softplus(dt_proj) of every row are written
 // too.  The first weight fragments are requested before phase 1.  Bound by the
 // f32 MFMA (NF fragments of Di / 4 steps per 16 rows) and the x read.
-// 131072 rows: 121 us at d_inner 512; at 1024 332 us, where one wave per
-// fragment and a window fetched per element took 1008 us.
+// 131072 rows in bf16 tiles: at d_inner 512 122 us from 256 lanes and 139 from
+// 4096, half a copy's rate (294 MB, 62 us; the MFMA 41 us): the two phases of a
+// workgroup follow one another.  At d_inner 1024 about 350 us, where one wave
+// per fragment and a window fetched per element took 1008 us.
 template <int Di, int RR, bool KEEP>
 __global__ __launch_bounds__(256) void k_convx(LayerDev w, const float* __restrict__ xz, int T,
                                                const int* __restrict__ row_pos,
@@ -1534,8 +1536,8 @@ hipError_t launch_diag(const float* logits, int M, const uint8_t* data, const Pl
 }
 
 // ============================================================== range coder
-// State per lane: L (32-bit base), R (width in [1, 2^32], kept in 64 bits),
-// byte cursor.  Paper, Range coding: encoder update, renormalisation while the
+// State per lane: L (32-bit base), D = R - 1 in 32 bits (R, the width, lies in
+// [1, 2^32]), byte cursor.  Paper, Range coding: encoder update, renormalisation while the
 // top byte of L and E = L + R - 1 agree; readings: R is not reduced mod 2^32,
 // straddle fix R <- 2^16 - (L mod 2^16), flush with at most 2 bytes.
 // Encoder lanes: one thread per lane walks its rows of the tile in order.  A

@@ -1166,7 +1166,7 @@ DEVI float wave_sum32_tail(float (&v)[NSTATE], int lane) {
 // dA_log and dD (sums over time) are written per (sequence, block) slot as
 // pA[slot][d][n], pD[slot][d].  With dtr, dt = softplus(dtr): ddt receives the
 // gradient of dtr, and pT[slot][d] its sum (the dt_proj bias).  VALU bound: about 26 instructions per state
-// and step.
+// and step.  13 of its registers are spilled (52 B a thread) at two waves per SIMD.
 __global__ __launch_bounds__(256, 2) void k_tr_scan_bwd(
     const float* __restrict__ xs, const float* __restrict__ dt, const float* __restrict__ dbc, int NO, int R,
     const float* __restrict__ A_log, const float* __restrict__ Dsk, const float* __restrict__ dy, long long rows, int Tn,
