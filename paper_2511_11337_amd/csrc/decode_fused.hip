@@ -222,9 +222,12 @@ template <> struct BLoad<2> { using T = uint4; static constexpr int KPL = 64; };
 // range check drops what a vector offset takes past the range, but whether it
 // counts the scalar offset is the hardware's matter, and a vector offset out of
 // range costs a register more than a load of what other waves load too (16 lanes of
-// d_model 256 in bf16: 193 us a step against 185).  load_ok: the 16 bytes at (vo,
-// so) lie in the range; checked for every wave when this is compiled.
-constexpr bool load_ok(int vo, int so, int range) { return so >= 0 && vo >= 0 && vo + so + 16 <= range; }
+// d_model 256 in bf16: 193 us a step against 185).  Where that load costs time (RGemm
+// at two lanes: 89.0 us a step of d_model 256, 86.8 without; XRows at d_model 128:
+// 12.0 and 11.9) such a wave's range is empty besides, and the memory system drops it;
+// with 16 lanes the empty range costs up to 7 %.  load_ok: the 16 bytes at (vo, so)
+// lie in the matrix; checked for every wave when this is compiled.
+constexpr bool load_ok(int vo, int so, int bytes) { return so >= 0 && vo >= 0 && vo + so + 16 <= bytes; }
 
 // The NF fragments of W are dealt to the waves (wave w owns w, w + 8, ...),
 // at most 8 per pass.  issue() requests the first ring of B loads of the
@@ -412,9 +415,10 @@ struct RGemm {
                     if (!load_ok(voff(wl), soff(wv, s, SK - 1, 3), RANGE)) return false;
         return true;
     }
-    DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf) {
+    DEVI static __amdgpu_buffer_rsrc_t rsrc(const void* Wf, int wv) {
         static_assert(loads_ok(), "loads past the matrix");
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, RANGE, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(Wf), (short)0, G == 2 && idle(wv) ? 0 : RANGE,
+                                                 0x00020000);
     }
     DEVI static f32x4 ld(__amdgpu_buffer_rsrc_t r, int wv, int s, int q, int lk, int vo) {
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, vo, soff(wv, s, q, lk), 0);
@@ -423,7 +427,7 @@ struct RGemm {
         return o;
     }
     DEVI void issue(const void* Wf, int wv, int wl) {
-        const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
+        const __amdgpu_buffer_rsrc_t r = rsrc(Wf, wv);
         const int vo = voff(wl);
 #pragma unroll
         for (int u = 0; u < P; ++u)
@@ -436,7 +440,7 @@ struct RGemm {
     DEVI void run(const float* __restrict__ A, int as, const void* __restrict__ Wf, int wl, int wv, const unsigned*,
                   const int*, F&& f) {
         if (idle(wv)) return;
-        const __amdgpu_buffer_rsrc_t r = rsrc(Wf);
+        const __amdgpu_buffer_rsrc_t r = rsrc(Wf, wv);
         const int vo = voff(wl);
 #pragma unroll 1
         for (int p = 0; p < SPW; p += SP) {
@@ -608,7 +612,7 @@ struct XRows {
     DEVI static f32x4 ld(const float* Wf, int wv, int wl, int i, int lk) {
         static_assert(loads_ok(), "loads past the matrix");
         const __amdgpu_buffer_rsrc_t r =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, RANGE, 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Wf), (short)0, mine(wv) ? RANGE : 0, 0x00020000);
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff(wl), soff(wv, i, lk), 0);
         f32x4 o;
         __builtin_memcpy(&o, &v, sizeof o);
