@@ -920,18 +920,25 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
 
 // =================================================================== decode
 namespace {
-// A step of the fused decoder in us at 1, 2, 4, 8, 16 lanes a workgroup, 256
-// workgroups (2, 2, 3, 4 layers; only the ratios within a row matter).
-constexpr float FUSED_STEP_US[3][4][5] = {
-    {{12.3f, 17.0f, 23.7f, 35.0f, 63.0f}, {19.5f, 29.4f, 40.0f, 56.3f, 86.0f},       // f32; d_model 64, 128,
-     {64.6f, 93.0f, 137.f, 162.f, 282.f}, {259.f, 292.f, 509.f, 570.f, 0.f}},        // 256, 512
-    {{11.3f, 12.5f, 17.3f, 27.2f, 58.6f}, {13.2f, 17.3f, 25.1f, 42.2f, 74.2f},       // bf16
-     {33.6f, 51.3f, 79.0f, 110.f, 191.f}, {163.f, 188.f, 236.f, 317.f, 0.f}},
-    {{12.0f, 14.7f, 21.4f, 33.3f, 66.2f}, {13.6f, 19.1f, 27.6f, 46.0f, 84.2f},       // fp8
-     {30.2f, 45.4f, 69.4f, 101.f, 184.f}, {123.f, 145.f, 204.f, 284.f, 0.f}}};
+// A step of the fused decoder in us at 1, 2, 4, 8, 16 lanes a workgroup: alone, and
+// what 256 running workgroups add in proportion to their number (they share the
+// caches' and the memory's rate).  2, 2, 3, 4 layers; only the ratios within a row matter.
+struct StepUs { float alone, chip; };
+constexpr StepUs FUSED_STEP_US[3][4][5] = {
+    {{{11.3f, 0.1f}, {14.5f, 0.8f}, {20.9f, 2.2f}, {27.0f, 5.7f}, {42.2f, 14.3f}},        // f32; d_model 64,
+     {{17.9f, 0.3f}, {26.6f, 0.6f}, {34.7f, 4.1f}, {41.9f, 10.5f}, {63.2f, 16.5f}},       // 128,
+     {{55.4f, 7.3f}, {80.2f, 7.9f}, {121.f, 12.7f}, {142.f, 14.6f}, {189.f, 43.3f}},      // 256,
+     {{238.f, 12.9f}, {261.f, 21.4f}, {485.f, 21.1f}, {536.f, 28.2f}, {0.f, 0.f}}},       // 512
+    {{{8.1f, 0.95f}, {10.7f, 0.7f}, {14.5f, 2.1f}, {20.5f, 4.8f}, {39.0f, 13.1f}},         // bf16
+     {{12.1f, 0.4f}, {15.0f, 1.7f}, {19.9f, 4.0f}, {26.1f, 12.0f}, {47.7f, 20.7f}},
+     {{32.3f, 0.6f}, {41.8f, 7.4f}, {48.0f, 24.2f}, {69.8f, 32.8f}, {110.f, 67.6f}},
+     {{143.f, 12.4f}, {163.f, 18.0f}, {196.f, 32.8f}, {234.f, 69.4f}, {0.f, 0.f}}},
+    {{{9.0f, 0.85f}, {12.6f, 0.8f}, {18.6f, 2.0f}, {26.1f, 4.5f}, {46.5f, 12.2f}},         // fp8
+     {{12.3f, 0.5f}, {16.8f, 2.1f}, {23.5f, 3.2f}, {31.2f, 9.8f}, {57.4f, 16.8f}},
+     {{28.7f, 0.5f}, {39.3f, 4.7f}, {55.4f, 10.4f}, {77.2f, 20.2f}, {118.f, 59.7f}},
+     {{108.f, 8.7f}, {131.f, 7.1f}, {176.f, 21.4f}, {215.f, 58.9f}, {0.f, 0.f}}}};
 // Workgroups that a CU holds: one of 8 waves by their registers, but two of the
-// one-lane form at d_model 64 in bf16 and fp8 (at most 128 registers; its step
-// above is the one of 512 workgroups, 9.0 and 10.2 us at 256).
+// one-lane form at d_model 64 in bf16 and fp8 (at most 128 registers).
 int fused_slots(int dtype, int D, int g) { return g == 1 && D == 64 && dtype != BOA_DTYPE_F32 ? 512 : 256; }
 
 // Lanes per workgroup of the fused decoder: a workgroup runs until the longest
@@ -942,6 +949,8 @@ int fused_slots(int dtype, int D, int g) { return g == 1 && D == 64 && dtype != 
 // 164 at two.  384 lanes of 8 to 128 steps, longest first (f32, d_model 128): the second
 // round fits behind the first one's short lanes, 2.6 ms at one, 3.9 at two.  5000
 // equal lanes (bf16, d_model 256): 332 us a step at 16, in two rounds, 296 at 8, in three.
+// 2514 equal lanes (fp8, d_model 128): 13.3 ms at 16, the chip half full, 15.2 at 4, in
+// three rounds.
 int pick_fused_lanes(int dtype, int D, const std::vector<long long>& load, int n_layers, size_t max_lds) {
     const int lanes = (int)load.size(), di = D == 64 ? 0 : D == 128 ? 1 : D == 256 ? 2 : 3;
     if (lanes <= 256) return 1;
@@ -951,14 +960,16 @@ int pick_fused_lanes(int dtype, int D, const std::vector<long long>& load, int n
     std::vector<long long> wg;
     for (int k = top; k >= 0; --k) {
         const int g = 1 << k, slots = fused_slots(dtype, D, g);
-        const double us = FUSED_STEP_US[dtype == BOA_DTYPE_BF16 ? 1 : dtype == BOA_DTYPE_FP8 ? 2 : 0][di][k];
+        const StepUs us = FUSED_STEP_US[dtype == BOA_DTYPE_BF16 ? 1 : dtype == BOA_DTYPE_FP8 ? 2 : 0][di][k];
         wg.clear();
         for (int l = 0; l < lanes; l += g)
             wg.push_back(*std::max_element(load.begin() + l, load.begin() + std::min(lanes, l + g)));
         long long end = *std::max_element(wg.begin(), wg.end());
-        // no schedule ends before the longest workgroup or the average slot does
+        // every step costs a workgroup alone, and its share of the chip for each that runs
         const long long sum = std::accumulate(wg.begin(), wg.end(), 0LL);
-        if (us * (double)std::max(end, sum / slots) > best_us) continue;
+        const double shared = us.chip * (double)sum / 256;
+        // (no schedule ends before the longest workgroup or the average slot does)
+        if (us.alone * (double)std::max(end, sum / slots) + shared > best_us) continue;
         if ((int)wg.size() > slots) {
             std::priority_queue<long long, std::vector<long long>, std::greater<long long>> busy(
                 std::greater<long long>(), std::vector<long long>(wg.begin(), wg.begin() + slots));   // ends of the running ones
@@ -969,7 +980,8 @@ int pick_fused_lanes(int dtype, int D, const std::vector<long long>& load, int n
                 end = std::max(end, at);
             }
         }
-        if (us * (double)end <= best_us) { best = g; best_us = us * (double)end; }
+        const double all = us.alone * (double)end + shared;
+        if (all <= best_us) { best = g; best_us = all; }
     }
     return best;
 }

@@ -50,3 +50,13 @@ def test_lds_bounds_the_choice():
     fn = _lib.load().boa_test_fused_lanes
     cl = np.full(4096, 50, dtype=np.uint64)
     assert fn(256, 3, 1, cl.ctypes.data_as(_lib.U64P), cl.size, 4096, 65536) < 16
+
+
+@pytest.mark.parametrize("D,dtype,lens,want", [
+    (128, "fp8", np.full(2514, 200), 16),                # 4 lanes: 15.2 ms, 8: 14.7, 16: 13.3
+    (512, "bf16", np.linspace(158, 436, 1746), 8),       # 4: 123, 8: 117
+    (128, "bf16", np.linspace(69, 902, 2824), 8),        # 4: 33.9, 8: 29.0, 16: 48.7
+    (64, "fp8", np.linspace(28, 96, 7237), 16)])         # 8: 7.5, 16: 7.1
+def test_a_last_round_of_few_workgroups_steps_faster(D, dtype, lens, want):
+    """A step's time depends on how many workgroups run beside it."""
+    assert _choice(lens.astype(np.uint64), D, dtype, layers={64: 2, 128: 2, 256: 3, 512: 4}[D]) == want
