@@ -178,9 +178,9 @@ hipError_t launch_mid(const LayerDev& w, int Di, int R, const float* xz, float* 
                       int lanes_per_wg, const int* row_pos, float* conv_state, float* hstate,
                       hipStream_t s);
 // The encoder's mixer over a tile of T rows per lane.  dbc [M][R + 32] is
-// scratch; with few lanes and long tiles (mixer_few) so are xs, dt [M][Di] and hsub
-// (mixer_hsub_floats), else they may be null.  g_bf16: the gated rows are
-// written as bf16 bits.
+// scratch, and so are xs, dt [M][Di] and hsub (mixer_hsub_floats): with them blocks
+// of rows run side by side, which pays with few lanes and long tiles (mixer_few);
+// they may be null.  g_bf16: the gated rows are written as bf16 bits.
 bool mixer_few(int Di, int lanes, int T);
 size_t mixer_hsub_floats(int Di, int lanes, int T);
 hipError_t launch_mid_tiled(const LayerDev& w, int Di, int R, const float* xz, float* xs, float* dbc, float* dt,

@@ -1386,17 +1386,18 @@ __global__ __launch_bounds__(Di < 256 ? Di : 256) void k_scan_rows(LayerDev w, c
 // One thread per (lane, channel) fills the GPU with two waves per SIMD from
 // 2048 waves on; below MIXER_FEW waves the blocks of rows run side by side, if the
 // tile is long enough for that to pay for a kernel more and the operands passed
-// on: from 48 rows, and one more for every two waves that k_scan would have.  One
-// 4096-step stream, d_inner 512: k_scan_states 188 us + k_scan_rows 21 us, where a
-// workgroup walking the lane took 3905 us; 256 lanes have enough waves for k_scan,
-// which computes each exponential once.  Two tiles through three layers, blocks
-// of rows against k_scan: d_inner 512, one lane, 48 rows 602 against 631 us, 24
-// rows 607 against 548; 16 lanes, 128 rows 1202 against 1382, 32 rows 721 against 673;
-// d_inner 128, 128 lanes, 256 rows 1565 against 1835, 128 rows 1201 against 1035.
+// on.  One 4096-step stream, d_inner 512: k_scan_states 188 us + k_scan_rows 21 us,
+// where a workgroup walking the lane took 3905 us; 256 lanes have enough waves for
+// k_scan, which computes each exponential once.  The shortest such tile comes from
+// calls of one tile through three layers (blocks of rows against k_scan): d_inner
+// 128, 32 lanes, 24 rows equal, 48 rows 269 us against 298; d_inner 512, one lane, 32 rows
+// equal, 64 rows 269 against 317; d_inner 1024, 16 lanes, 80 rows 723 against 709, 128
+// rows 936 against 984; the more waves k_scan has, the longer: d_inner 512, 64 lanes (512
+// waves), 128 rows 796 against 780, 256 rows equal.
 constexpr int MIXER_FEW = 1024;
 bool mixer_few(int Di, int lanes, int T) {
     const long long waves = (long long)lanes * Di / 64;
-    return waves < MIXER_FEW && T >= 48 + waves / 2;
+    return waves < MIXER_FEW && T >= 32 + Di / 32 + waves * waves / 2048;
 }
 size_t mixer_hsub_floats(int Di, int lanes, int T) {
     return (size_t)lanes * ((T + SCAN_RB - 1) / SCAN_RB) * NSTATE * Di;
@@ -1409,7 +1410,7 @@ hipError_t launch_mid_tiled(const LayerDev& w, int Di, int R, const float* xz, f
     const int nt = Di < 256 ? Di : 256;
 #define MX_CASE(DI, RV)                                                                                             \
     if (Di == DI && R == RV) {                                                                                      \
-        if (mixer_few(Di, lanes, T)) {                                                                              \
+        if (xs) {                                                                                                   \
             BOA_LAUNCH((k_convx<DI, RV, true>), g1, dim3(256), 0, s, w, xz, T, row_pos, conv_state, dbc, xs, dt);   \
             BOA_LAUNCH((k_scan_states<DI, RV>), dim3(DI / 64 * 4, lanes), dim3(256), 0, s, w, xs, dt, dbc, T,       \
                        row_pos, hstate, hsub);                                                                      \

@@ -578,6 +578,19 @@ int upload_plan(const HostPlan& P, const std::vector<long long>& off, const std:
     return BOA_OK;
 }
 
+// What the mixer's kernels pass on between them: all that its fastest form for
+// the tile wants, what k_scan needs, or nothing (for measuring only).
+enum class Mixer { best, scan, none };
+// The form of a call that allocates `size(form)` bytes for itself.  Releasing more
+// than 64 MiB takes 230 us (6 us below), more than blocks of rows gain over k_scan
+// in a call with 128 waves of channels or more whose bytes they take past that
+// (d_inner 256, 64 lanes of 128 rows: 679 us against 458).
+template <class F>
+Mixer own_mixer(int Di, int lanes, F&& size) {
+    constexpr size_t SLAB = (size_t)64 << 20;
+    return (long long)lanes * Di / 64 > 128 && size(Mixer::best) > SLAB && size(Mixer::scan) <= SLAB ? Mixer::scan : Mixer::best;
+}
+
 // Per-call activation and state buffers for `lanes` lanes and tiles of T rows.
 struct Work {
     DevBuf r, xz, g, logits, cf, row_chunk, row_pos, conv, h, coder, step, xs, dbc, dt, hsub;
@@ -585,9 +598,8 @@ struct Work {
     int lanes = 0, T = 0;
     Arena own_arena;
     DevBuf own_mem;
-    // every buffer as a piece of A (kept: with what the mixer's kernels pass on
-    // between them; without it the pieces only measure)
-    void carve(Arena& A, const boa_model* m, int lanes_, int T_, bool kept = true) {
+    // every buffer as a piece of A
+    void carve(Arena& A, const boa_model* m, int lanes_, int T_, Mixer mx = Mixer::best) {
         lanes = lanes_;
         T = T_;
         const Layout& L = m->lay;
@@ -595,9 +607,9 @@ struct Work {
         r.carve(A, M * L.D * 4);
         xz.carve(A, M * 2 * L.Di * 4);
         g.carve(A, M * L.Di * 4);
-        if (T > 1 && kept) {                   // the mixer's intermediates
+        if (T > 1 && mx != Mixer::none) {      // the mixer's intermediates
             dbc.carve(A, M * (L.R + 2 * L.N) * 4);
-            if (mixer_few(L.Di, lanes, T)) {
+            if (mx == Mixer::best && mixer_few(L.Di, lanes, T)) {
                 xs.carve(A, M * L.Di * 4);
                 dt.carve(A, M * L.Di * 4);
                 hsub.carve(A, mixer_hsub_floats(L.Di, lanes, T) * 4);
@@ -618,11 +630,16 @@ struct Work {
     }
     // every buffer in one allocation owned by this Work
     int alloc(const boa_model* m, int lanes_, int T_) {
-        Arena meas;
-        carve(meas, m, lanes_, T_);
-        ALLOC(own_mem, meas.used);
-        own_arena = Arena{own_mem.as<uint8_t>(), meas.used, 0, false};
-        carve(own_arena, m, lanes_, T_);
+        auto size = [&](Mixer mx) {
+            Arena meas;
+            Work{}.carve(meas, m, lanes_, T_, mx);
+            return meas.used;
+        };
+        const Mixer mx = own_mixer(m->lay.Di, lanes_, size);
+        const size_t need = size(mx);
+        ALLOC(own_mem, need);
+        own_arena = Arena{own_mem.as<uint8_t>(), need, 0, false};
+        carve(own_arena, m, lanes_, T_, mx);
         return BOA_OK;
     }
 };
@@ -766,11 +783,11 @@ struct EncBufs {
     DevBuf d_poff, d_pcap;
     Work W;
     DevBuf cfb[2], rcb[2], rpb[2];
-    void carve(Arena& A, const boa_model* m, const HostPlan& P, size_t n_chunks, int T, bool kept = true) {
+    void carve(Arena& A, const boa_model* m, const HostPlan& P, size_t n_chunks, int T, Mixer mx = Mixer::best) {
         carve_plan(A, P, n_chunks, PD);
         d_poff.carve(A, n_chunks * sizeof(long long));
         d_pcap.carve(A, n_chunks * sizeof(long long));
-        W.carve(A, m, P.lanes, T, kept);
+        W.carve(A, m, P.lanes, T, mx);
         const size_t M = (size_t)P.lanes * T;
         for (int b = 0; b < 2; ++b) {
             cfb[b].carve(A, M * 2 * 4);
@@ -786,10 +803,10 @@ std::vector<long long> chunk_steps(const uint64_t* h_chunk_len, uint64_t n) {
     return steps;
 }
 
-size_t encode_bytes(const boa_model* m, const HostPlan& P, size_t n_chunks, int T, bool kept = true) {
+size_t encode_bytes(const boa_model* m, const HostPlan& P, size_t n_chunks, int T, Mixer mx = Mixer::best) {
     Arena meas;
     EncBufs B;
-    B.carve(meas, m, P, n_chunks, T, kept);
+    B.carve(meas, m, P, n_chunks, T, mx);
     return meas.used;
 }
 // Workspace bytes of an encode call (0 when no chunk has a coded byte).
@@ -808,7 +825,7 @@ size_t encode_ws_bytes(const boa_model* m, const std::vector<long long>& steps, 
 // as many bytes on more lanes does).
 int fit_tile(const boa_model* m, const HostPlan& P, size_t n_chunks, int T, uint32_t req, size_t ws_bytes) {
     const int half = (longest_tile(P.lanes, P.total_steps, req) + 1) / 2;
-    if (ws_bytes < encode_bytes(m, P, n_chunks, half, false) || ws_bytes < encode_bytes(m, P, n_chunks, 1)) return 0;
+    if (ws_bytes < encode_bytes(m, P, n_chunks, half, Mixer::none) || ws_bytes < encode_bytes(m, P, n_chunks, 1)) return 0;
     int lo = 1, hi = T;                        // lo fits, hi does not
     while (hi - lo > 1) {
         const int mid = (lo + hi) / 2;
@@ -848,7 +865,9 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
     int T = pick_tile(P.lanes, P.total_steps, o.tile_t);
     // device memory: the caller's workspace, else one allocation of the measured size
     EncBufs B;
-    const size_t need = encode_bytes(m, P, n_chunks, T);
+    auto size = [&](Mixer x) { return encode_bytes(m, P, n_chunks, T, x); };
+    const Mixer mx = d_ws ? Mixer::best : own_mixer(m->lay.Di, P.lanes, size);
+    const size_t need = size(mx);
     DevBuf own;
     Arena A;
     if (d_ws) {
@@ -861,7 +880,7 @@ extern "C" int boa_encode_dev(const boa_model* m, const uint8_t* d_data, const u
         ALLOC(own, need);
         A = Arena{own.as<uint8_t>(), need, 0, false};
     }
-    B.carve(A, m, P, n_chunks, T);
+    B.carve(A, m, P, n_chunks, T, mx);
     int rc = fill_plan(P, off, steps, B.PD, s);
     if (rc) return rc;
     HIPCHK(copy_in(B.d_poff, poff, s));
