@@ -1890,10 +1890,12 @@ int scan_bwd(const float* x, const float* dt, const float* A_log, const float* b
              float* dD, hipStream_t s, std::string& err) {
     Tc = std::min(Tc, T);
     const int dblk = (Di + SCAN_CH - 1) / SCAN_CH;
-    // chunks of less than 32 steps go together (a chunk costs its states at its start
-    // and at its blocks' ends), to a multiple of 8 steps
-    const int nsave = (T + Tc - 1) / Tc;
-    int m = (32 + Tc - 1) / Tc;
+    // short chunks go together, to a multiple of 8 steps: to 16 at least, and to 32
+    // where they are many enough to fill the chip (a chunk costs its states at its start
+    // and at its blocks' ends; 4 x 2000 steps at d_inner 512: 740 us in chunks of 16, 400
+    // of 32; 64 steps at d_inner 64: 178 and 203, for the longer chains)
+    const int nsave = (T + Tc - 1) / Tc, least = (long long)B * T * Di > 1 << 20 ? 32 : 16;
+    int m = (least + Tc - 1) / Tc;
     while (m > 1 && m * Tc % 8) ++m;
     const ScanCut q = scan_cut(B, T, Di, (int)std::min<long long>((long long)m * Tc, T));
     const BwdPart part = bwd_part(q, B, T, Di, Tc);
